@@ -93,6 +93,7 @@ int restore_snapshot(vuda_world* w, const Snapshot& s) {
   if (e == hipSuccess) e = hipMemcpy(w->dev.state[1], d + st, st, hipMemcpyDeviceToDevice);
   if (e == hipSuccess) e = hipMemcpy(w->dev.env_flags, d + 2 * st, fl, hipMemcpyDeviceToDevice);
   if (e != hipSuccess) return hip_fail(e, "snapshot restore");
+  __atomic_store_n(w->any_flag, 1u, __ATOMIC_RELEASE);  // the restored flags may hold some
   w->env_parity = s.parity;
   std::fill(w->setup_ok.begin(), w->setup_ok.end(), 0);  // the scratch may hold another state's setup
   std::fill(w->step_ev.begin(), w->step_ev.end(), -1);

@@ -1207,9 +1207,9 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     const bool fin = isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(v.x) &&
                      isfinite(v.y) && isfinite(v.z) && isfinite(w.x) && isfinite(w.y) &&
                      isfinite(w.z) && isfinite(qw) && isfinite(qx) && isfinite(qy) && isfinite(qz);
-    if (!fin) atomicOr(&W.env_flags[env], kFlagNonFinite);
+    if (!fin) raise_flag(W, env, kFlagNonFinite);
   }
-  if (bad && tid == 0 && env >= 0) atomicOr(&W.env_flags[env], kFlagContactOverflow);
+  if (bad && tid == 0 && env >= 0) raise_flag(W, env, kFlagContactOverflow);
 }
 
 // FR: friction; EE: edge-edge points of box pairs; SUP: the step's candidate

@@ -697,7 +697,7 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   const int nwhole = misc[2];
   const int npieces = min(misc[3], kClipRecs);
   const int nrec = nwhole + npieces;
-  if (tid == 0 && misc[3] > kClipRecs) atomicOr(&W.env_flags[cam.env], kFlagClipOverflow);
+  if (tid == 0 && misc[3] > kClipRecs) raise_flag(W, cam.env, kFlagClipOverflow);
   // record r: whole triangle vis[r], or piece cvis[r - nwhole]; vid its
   // face's vertices in face order
   const auto record_tri = [&](int r, int* pr, int* body, int vid[3], Tri* t) {

@@ -187,6 +187,7 @@ struct WorldDev {
   int32_t* contacts;   // nullable
   int32_t pair_cap;
   uint32_t* env_flags;
+  uint32_t* any_flag;       // pinned host word: nonzero once any env flag was raised
   const Templates* tpl;
   const uint8_t* texture;   // textured worlds: RGB8 texels [tex_h][tex_w][3]; nullptr: none
   unsigned char* rscratch;  // raster scratch of every camera (CamDev::rs_off)
@@ -196,6 +197,15 @@ struct WorldDev {
   uint8_t* act_on;
   int32_t act_dim;
 };
+
+// Raise a sticky flag of an env, and then the host's word, so that the host
+// learns without a copy that there is a flag to read (system-scope store: it
+// is in host memory before the kernel's completion is seen).
+__device__ __forceinline__ void raise_flag(const WorldDev& w, int32_t env, uint32_t flag) {
+  atomicOr(&w.env_flags[env], flag);
+  __threadfence_system();
+  __hip_atomic_store(w.any_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Host-side launchers (implemented next to the kernels).
 struct PhysLaunch {

@@ -111,6 +111,12 @@ struct MetricCam {
 hipError_t launch_depth_metric(const uint32_t* depth, const MetricCam* cams, int32_t ncams, int64_t max_pix,
                                float* out, hipStream_t s);
 
+// State rows [nb][13] of the bodies b0 .. b0 + nb of a state buffer (13
+// arrays of `cap` floats), out of it and into it.  The rows are device or
+// pinned host memory.
+hipError_t launch_state_gather(const float* state, int64_t cap, int64_t b0, int64_t nb, float* rows, hipStream_t s);
+hipError_t launch_state_scatter(const float* rows, float* state, int64_t cap, int64_t b0, int64_t nb, hipStream_t s);
+
 // Hidden sizes: up to kPolicyHeadMax the per-env head kernel runs layers 2
 // and 3; above it (multiples of 64) they run as batched products.
 constexpr int32_t kPolicyHeadMax = 1024, kPolicyHiddenMax = 8192;
@@ -199,6 +205,13 @@ struct vuda_world {
   int64_t metric_cams_cap = 0;
   float* metric_buf = nullptr;
   int64_t metric_buf_cap = 0;
+  // pinned host memory: the word the kernels raise with an env flag
+  // (WorldDev::any_flag), and the rows of state loads and host fetches,
+  // grown on demand up to kPinMax (larger ones go through it in pieces)
+  uint32_t* any_flag = nullptr;
+  unsigned char* pin = nullptr;
+  size_t pin_cap = 0;
+  hipEvent_t ev_order = nullptr;  // orders the null stream after the serial one
 
   std::map<std::tuple<int, int32_t, int32_t>, vuda::WorkList> lists;
   std::map<std::tuple<int, int32_t, int32_t, int>, hipGraphExec_t> graphs;
@@ -245,6 +258,11 @@ struct vuda_world {
   int launch_kernel(int kind, const vuda::WorkList& L, int parity, int32_t lo, int32_t hi, hipStream_t s,
                     int32_t* queue);
   int check_flags();
+  // the null stream waits for everything enqueued on the world's streams
+  int order_null();
+  int fetch_state(int32_t lo, int32_t hi, float* dst, bool on_device);
+  int scatter_state(int32_t lo, int32_t hi, const float* src);
+  int reserve_pin(size_t bytes);
   int32_t active_midpoint();
   // events that complete when everything enqueued so far on the world's
   // streams has run (one per stream in use); returns how many were recorded

@@ -243,7 +243,7 @@ def env_batch(keep: _Keep, scene, state: Optional[Dict[str, np.ndarray]] = None)
 
 
 def state_to_aos(st: Dict[str, np.ndarray]) -> np.ndarray:
-    return np.concatenate([st["pos"], st["vel"], st["quat"], st["omega"]], axis=1).astype(np.float32)
+    return np.concatenate([st["pos"], st["vel"], st["quat"], st["omega"]], axis=1).astype(np.float32, copy=False)
 
 
 def aos_to_state(a: np.ndarray) -> Dict[str, np.ndarray]:
@@ -409,7 +409,7 @@ class World:
         dt = {FETCH_STATE: np.float32, FETCH_RGB: np.uint8, FETCH_DEPTH: np.uint32,
               FETCH_CONTACTS: np.int32, FETCH_WINNERS: np.int32, FETCH_COVERAGE: np.int32,
               FETCH_FLAGS: np.uint32, FETCH_ACTIONS: np.float32, FETCH_DEPTH_METRIC: np.float32}[what]
-        buf = np.zeros(nbytes // np.dtype(dt).itemsize, dt)
+        buf = np.empty(nbytes // np.dtype(dt).itemsize, dt)
         check(lib().vuda_fetch(self._w, what, lo, hi, _p(buf), C.c_size_t(nbytes), 0))
         return buf
 
