@@ -281,6 +281,13 @@ int vuda_fetch_bytes(vuda_world* w, int32_t what, int32_t env_lo, int32_t env_hi
 int vuda_load_state(vuda_world* w, int32_t env_lo, int32_t env_hi, const float* src,
                     size_t src_bytes);
 
+/* The same from four host arrays, as an env batch holds them: positions
+ * [n][3], velocities [n][3], quaternions [n][4] (w, x, y, z) and angular
+ * velocities [n][3] of n bodies, at least those of the active envs in
+ * [env_lo, env_hi) (VUDA_EINVAL otherwise). */
+int vuda_load_state_parts(vuda_world* w, int32_t env_lo, int32_t env_hi, const float* pos, const float* vel,
+                          const float* quat, const float* omega, int64_t n);
+
 /* The HIP stream (hipStream_t) of a phase, for interop (e.g. an external
  * stream object in PyTorch).  Valid until the next vuda_cosched call. */
 int vuda_get_stream(vuda_world* w, int32_t phase, void** hip_stream);

@@ -115,7 +115,10 @@ hipError_t launch_depth_metric(const uint32_t* depth, const MetricCam* cams, int
 // arrays of `cap` floats), out of it and into it.  The rows are device or
 // pinned host memory.
 hipError_t launch_state_gather(const float* state, int64_t cap, int64_t b0, int64_t nb, float* rows, hipStream_t s);
-hipError_t launch_state_scatter(const float* rows, float* state, int64_t cap, int64_t b0, int64_t nb, hipStream_t s);
+// parts: the rows lie as four arrays one after the other, [nb][3] positions,
+// [nb][3] velocities, [nb][4] quaternions, [nb][3] angular velocities.
+hipError_t launch_state_scatter(const float* rows, bool parts, float* state, int64_t cap, int64_t b0, int64_t nb,
+                                hipStream_t s);
 
 // Hidden sizes: up to kPolicyHeadMax the per-env head kernel runs layers 2
 // and 3; above it (multiples of 64) they run as batched products.
@@ -131,6 +134,11 @@ struct Policy {
   float* w3p = nullptr;     // [H][A rounded up to 64] (hidden a multiple of 64)
   float* partial = nullptr;
   int64_t partial_cap = 0;  // floats
+};
+
+// Host state to load: rows of 13 floats (part[1] null), or the four arrays.
+struct StateParts {
+  const float* part[4];
 };
 
 }  // namespace vuda
@@ -211,7 +219,6 @@ struct vuda_world {
   uint32_t* any_flag = nullptr;
   unsigned char* pin = nullptr;
   size_t pin_cap = 0;
-  hipEvent_t ev_order = nullptr;  // orders the null stream after the serial one
 
   std::map<std::tuple<int, int32_t, int32_t>, vuda::WorkList> lists;
   std::map<std::tuple<int, int32_t, int32_t, int>, hipGraphExec_t> graphs;
@@ -258,10 +265,8 @@ struct vuda_world {
   int launch_kernel(int kind, const vuda::WorkList& L, int parity, int32_t lo, int32_t hi, hipStream_t s,
                     int32_t* queue);
   int check_flags();
-  // the null stream waits for everything enqueued on the world's streams
-  int order_null();
   int fetch_state(int32_t lo, int32_t hi, float* dst, bool on_device);
-  int scatter_state(int32_t lo, int32_t hi, const float* src);
+  int scatter_state(int32_t lo, int32_t hi, const vuda::StateParts& src);
   int reserve_pin(size_t bytes);
   int32_t active_midpoint();
   // events that complete when everything enqueued so far on the world's

@@ -50,6 +50,7 @@ EXPORTS = [
     "vuda_autotune", "vuda_serve_create", "vuda_serve_destroy", "vuda_serve_submit",
     "vuda_serve_tick", "vuda_serve_completed", "vuda_serve_result", "vuda_serve_stats",
     "vuda_serve_world", "vuda_kernel_times", "vuda_policy_set", "vuda_act", "vuda_act_noalloc",
+    "vuda_load_state_parts",
 ]
 SCHED_SERIAL, SCHED_INTERSTEP, SCHED_INTERTRAJ, SCHED_PIPELINED = 0, 1, 2, 3
 SCHED_NAMES = {SCHED_SERIAL: "serial", SCHED_INTERSTEP: "interstep", SCHED_INTERTRAJ: "intertraj",
@@ -418,6 +419,14 @@ class World:
 
     def load_state(self, st: Dict[str, np.ndarray], lo: int = 0, hi: Optional[int] = None):
         hi = self.n_envs if hi is None else hi
+        parts = [st[k] for k in ("pos", "vel", "quat", "omega")]
+        if all(isinstance(a, np.ndarray) and a.dtype in (np.float32, np.float64) and
+               a.shape == (len(parts[0]), width) for a, width in zip(parts, (3, 3, 4, 3))):
+            # joining the arrays into rows here took longer than the load
+            # (0.4 ms for 32,768 bodies): the library takes them as they are
+            parts = [np.ascontiguousarray(a, np.float32) for a in parts]
+            check(lib().vuda_load_state_parts(self._w, lo, hi, *[_p(a) for a in parts], C.c_int64(len(parts[0]))))
+            return
         a = np.ascontiguousarray(state_to_aos(st))
         check(lib().vuda_load_state(self._w, lo, hi, _p(a), C.c_size_t(a.nbytes)))
 
