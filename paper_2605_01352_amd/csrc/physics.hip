@@ -570,9 +570,34 @@ __device__ __forceinline__ int popc_below(const uint64_t* row, int b) {
   return c;
 }
 
+// Barrier over the lanes of one env.  An env of one wave (or half of one)
+// needs no workgroup barrier: its wave's LDS accesses complete in order, so
+// only the compiler must not reorder them.  Two such envs can then share a
+// workgroup without waiting for each other.
+template <int N>
+__device__ __forceinline__ void env_sync() {
+  if constexpr (N > 64) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Whether any lane of the env's waves sets v (its wave's two envs at N = 32).
+template <int N>
+__device__ __forceinline__ bool env_any(bool v) {
+  if constexpr (N > 64) {
+    return __syncthreads_or(v ? 1 : 0) != 0;
+  } else {
+    env_sync<N>();
+    return __ballot(v) != 0ull;
+  }
+}
+
 template <int N, bool FR, bool EE, bool SUP>
 __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc, int env,
-                         int parity, int broadphase) {
+                         int parity, int nsteps, int broadphase) {
   constexpr int NW = PhysLDS<N>::NW;
   // Lanes of this env: N consecutive threads.  At N = 32 two envs share a
   // wave, each in one half: their compactions count within the half, a
@@ -595,7 +620,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
   const bool own = tid < n;
   const int64_t cap = W.cap_bodies;
   const float* in = W.state[parity];
-  float* out = W.state[parity ^ 1];
+  float* out = W.state[(parity + nsteps) & 1];
   const int gb = b0 + (own ? tid : 0);
 
   // owned body state in registers
@@ -646,15 +671,15 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
   const int T = 1 << tbits;
   const uint32_t hmask = (uint32_t)(T - 1);
   const f3 gvec = mk(pc.g[0], pc.g[1], pc.g[2]);
-  bool bad = false;
+  bool bad = false, fin = true;
   // broadphase choice: 0 auto (grid above 64 bodies), 1 grid, 2 all-pairs
   const bool use_grid = broadphase == 1 || (broadphase == 0 && n > 64);
   // the step's candidate superset (all-pairs path): pairs found at substep 0
   // within their bounding radii plus kSupMargin, by the lane that found them
-  const f3 p0 = p;
+  f3 p0 = p;
   uint64_t supM = 0ull;
 
-  for (int sub_i = 0; sub_i < pc.substeps; ++sub_i) {
+  for (int step = 0, sub_i = 0; step < nsteps;) {
     // 1. publish substep-start state
     M3 R = quat_to_rot(qw, qx, qy, qz);
     if (own) {
@@ -693,7 +718,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     }
     // the barrier that publishes the substep state also ORs the far-cell
     // test over every wave of the env
-    const bool grid = (__syncthreads_or(far_cell) == 0) && use_grid;
+    const bool grid = !env_any<N>(far_cell != 0) && use_grid;
     if (!grid && N <= 64) {
       // Substeps after the first retest only the step's superset while every
       // body of the env is within a quarter of the margin of its step-start
@@ -810,7 +835,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         const uint32_t h = grid_hash(cx, cy, cz, hmask);
         atomicOr((unsigned long long*)&s.bucket[h][tid >> 6], 1ull << (tid & 63));
       }
-      __syncthreads();
+      env_sync<N>();
       if (own) {
         uint64_t M[NW];
 #pragma unroll
@@ -846,7 +871,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         }
       }
     }
-    __syncthreads();
+    env_sync<N>();
     // 3. compaction of candidate rows into the sorted pair list
     int ccount = 0;
     if (own) {
@@ -870,7 +895,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       }
     }
     if (ctotal > PhysLDS<N>::CAPC) bad = true;
-    __syncthreads();
+    env_sync<N>();
     // 4a. narrowphase of the pairs with a sphere, one candidate per lane;
     // cube-cube pairs are queued.  A pair in contact takes the next free
     // slot (handed out per wave) and its candidate remembers it, so the
@@ -957,7 +982,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         s.gres[3][tid] = gs.Ti.x; s.gres[4][tid] = gs.Ti.y; s.gres[5][tid] = gs.Ti.z;
       }
     }
-    __syncthreads();
+    env_sync<N>();
     // 4b. cube-cube pairs, 16 lanes each: lane r of a group tests corner
     // r & 7 of cube i inside cube j (r < 8), then of j inside i -- the
     // oracle's point order -- and lanes 0..8 of the group then sum one
@@ -1051,7 +1076,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    __syncthreads();
+    env_sync<N>();
     if (s.kcnt > PhysLDS<N>::CAPK) bad = true;
     // 5. gather in sorted pair order, then the ground, then integrate.
     // Contacts are taken four at a time so that each level of lookups
@@ -1167,7 +1192,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       const float inv = 1.0f / sqrtf(n2);
       qw = qw * inv; qx = qx * inv; qy = qy * inv; qz = qz * inv;
     }
-    __syncthreads();
+    env_sync<N>();
     if (W.contacts) {
       // pairs of row tid in ascending j, then (tid, ground)
       int cnt = 0;
@@ -1197,16 +1222,22 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         if (gc && pos < W.pair_cap) { dst[1 + 2 * pos] = tid; dst[2 + 2 * pos] = kGroundPair; }
       }
     }
-    __syncthreads();
+    env_sync<N>();
+    if (++sub_i == pc.substeps) {
+      // the end of a step
+      sub_i = 0;
+      ++step;
+      p0 = p;
+      fin = fin && isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(v.x) && isfinite(v.y) &&
+            isfinite(v.z) && isfinite(w.x) && isfinite(w.y) && isfinite(w.z) && isfinite(qw) && isfinite(qx) &&
+            isfinite(qy) && isfinite(qz);
+    }
   }
   if (own) {
     out[PX * cap + gb] = p.x; out[PY * cap + gb] = p.y; out[PZ * cap + gb] = p.z;
     out[VX * cap + gb] = v.x; out[VY * cap + gb] = v.y; out[VZ * cap + gb] = v.z;
     out[QW * cap + gb] = qw; out[QX * cap + gb] = qx; out[QY * cap + gb] = qy; out[QZ * cap + gb] = qz;
     out[WX * cap + gb] = w.x; out[WY * cap + gb] = w.y; out[WZ * cap + gb] = w.z;
-    const bool fin = isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(v.x) &&
-                     isfinite(v.y) && isfinite(v.z) && isfinite(w.x) && isfinite(w.y) &&
-                     isfinite(w.z) && isfinite(qw) && isfinite(qx) && isfinite(qy) && isfinite(qz);
     if (!fin) raise_flag(W, env, kFlagNonFinite);
   }
   if (bad && tid == 0 && env >= 0) raise_flag(W, env, kFlagContactOverflow);
@@ -1235,7 +1266,8 @@ __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, Ph
     const int wi = blockIdx.x;
     if (P * wi >= L.n_work) return;
     const int item = P * wi + sub;
-    step_env<N, FR, EE, SUP>(sh[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity, L.broadphase);
+    step_env<N, FR, EE, SUP>(sh[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity, L.nsteps,
+                             L.broadphase);
     return;
   }
   for (;;) {
@@ -1245,7 +1277,8 @@ __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, Ph
     __syncthreads();
     if (P * wi >= L.n_work) return;
     const int item = P * wi + sub;
-    step_env<N, FR, EE, SUP>(sh[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity, L.broadphase);
+    step_env<N, FR, EE, SUP>(sh[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity, L.nsteps,
+                             L.broadphase);
   }
 }
 
@@ -1307,13 +1340,13 @@ static const void* physics_fn(bool fr, bool ee) {
 }
 
 template <int N, bool SUP>
-static void launch_n(bool fr, bool ee, LaunchEvents* ev, bool first, bool last, dim3 g, hipStream_t s,
+static void launch_n(bool fr, bool ee, LaunchEvents* ev, dim3 g, hipStream_t s,
                      const WorldDev& w, const PhysConsts& pc, const PhysLaunch& lt) {
   const dim3 b(N < 64 ? 64 : N);
-  if (!fr && !ee) timed_launch(ev, first, last, physics_kernel<N, false, false, SUP>, g, b, 0, s, w, pc, lt);
-  else if (!ee) timed_launch(ev, first, last, physics_kernel<N, true, false, SUP>, g, b, 0, s, w, pc, lt);
-  else if (!fr) timed_launch(ev, first, last, physics_kernel<N, false, true, SUP>, g, b, 0, s, w, pc, lt);
-  else timed_launch(ev, first, last, physics_kernel<N, true, true, SUP>, g, b, 0, s, w, pc, lt);
+  if (!fr && !ee) timed_launch(ev, true, true, physics_kernel<N, false, false, SUP>, g, b, 0, s, w, pc, lt);
+  else if (!ee) timed_launch(ev, true, true, physics_kernel<N, true, false, SUP>, g, b, 0, s, w, pc, lt);
+  else if (!fr) timed_launch(ev, true, true, physics_kernel<N, false, true, SUP>, g, b, 0, s, w, pc, lt);
+  else timed_launch(ev, true, true, physics_kernel<N, true, true, SUP>, g, b, 0, s, w, pc, lt);
 }
 
 hipError_t launch_physics(const WorldDev& w, const PhysConsts& pc, const PhysLaunch& l,
@@ -1333,23 +1366,17 @@ hipError_t launch_physics(const WorldDev& w, const PhysConsts& pc, const PhysLau
     const hipError_t e = persistent_grid(l.persistent, items, fn, N < 64 ? 64 : N, 0, &grid);
     if (e != hipSuccess) return e;
   }
-  for (int t = 0; t < l.nsteps; ++t) {
-    PhysLaunch lt = l;
-    lt.parity = (l.parity + t) & 1;
-    lt.persistent = l.persistent != 0 ? grid : 0;  // the kernel only tells 0 from the rest
-    if (l.persistent != 0) {
-      hipError_t e = launch_reset_queue(l.queue, s);
-      if (e != hipSuccess) return e;
-    }
-    const bool first = t == 0, last = t == l.nsteps - 1;
-    if (N == 32) launch_n<32, false>(fr, ee, ev, first, last, dim3(grid), s, w, pc, lt);
-    else if (N == 64 && l.max_bodies > 32) launch_n<64, true>(fr, ee, ev, first, last, dim3(grid), s, w, pc, lt);
-    else if (N == 64) launch_n<64, false>(fr, ee, ev, first, last, dim3(grid), s, w, pc, lt);
-    else launch_n<128, false>(fr, ee, ev, first, last, dim3(grid), s, w, pc, lt);
-    hipError_t e = hipGetLastError();
+  PhysLaunch lt = l;
+  lt.persistent = l.persistent != 0 ? grid : 0;  // the kernel only tells 0 from the rest
+  if (l.persistent != 0) {
+    hipError_t e = launch_reset_queue(l.queue, s);
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  if (N == 32) launch_n<32, false>(fr, ee, ev, dim3(grid), s, w, pc, lt);
+  else if (N == 64 && l.max_bodies > 32) launch_n<64, true>(fr, ee, ev, dim3(grid), s, w, pc, lt);
+  else if (N == 64) launch_n<64, false>(fr, ee, ev, dim3(grid), s, w, pc, lt);
+  else launch_n<128, false>(fr, ee, ev, dim3(grid), s, w, pc, lt);
+  return hipGetLastError();
 }
 
 }  // namespace vuda

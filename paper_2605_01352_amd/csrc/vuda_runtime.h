@@ -250,20 +250,20 @@ struct vuda_world {
   int get_list(int phase, int32_t lo, int32_t hi, const vuda::WorkList** out);
   int range_parity(int32_t lo, int32_t hi, int* parity);
   int check_range(int32_t lo, int32_t hi);
-  int enqueue_physics(const vuda::WorkList& L, int parity, hipStream_t s, vuda::LaunchEvents* ev = nullptr);
+  int enqueue_physics(const vuda::WorkList& L, int parity, int nsteps, hipStream_t s, vuda::LaunchEvents* ev);
   int raster_launch_of(const vuda::WorkList& L, int parity, int32_t* queue, vuda::RasterLaunch* out);
   // the fused raster launch of a render list; *lds = 0 when the two-kernel
   // path renders it (fused off, smooth shading, near-plane clipping, or an
   // env too large for LDS)
   int fused_launch_of(const vuda::WorkList& L, int parity, int32_t* queue, vuda::RasterLaunch* out, size_t* lds);
   size_t lds_fused_configured = 64 * 1024;
-  int enqueue_kernel(int kind, const vuda::WorkList& L, int parity, hipStream_t s, int32_t* queue,
+  int enqueue_kernel(int kind, const vuda::WorkList& L, int parity, int nsteps, hipStream_t s, int32_t* queue,
                      vuda::LaunchEvents* ev = nullptr);
   int run_kernel(int kind, const vuda::WorkList& L, int parity, int32_t lo, int32_t hi, hipStream_t s,
-                 int32_t* queue, hipEvent_t done = nullptr);
+                 int32_t* queue, hipEvent_t done = nullptr, int nsteps = 1);
   // the launch itself: direct, timed, or through a captured graph
   int launch_kernel(int kind, const vuda::WorkList& L, int parity, int32_t lo, int32_t hi, hipStream_t s,
-                    int32_t* queue);
+                    int32_t* queue, int nsteps);
   int check_flags();
   int fetch_state(int32_t lo, int32_t hi, float* dst, bool on_device);
   int scatter_state(int32_t lo, int32_t hi, const vuda::StateParts& src);
