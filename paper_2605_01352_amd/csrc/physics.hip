@@ -24,6 +24,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 
 #include "vuda_internal.h"
 
@@ -76,7 +77,8 @@ __device__ __forceinline__ M3 quat_to_rot(float w, float x, float y, float z) {
 }
 
 // LDS image of one env of up to N bodies (N = 32, 64 or 128 lanes): NW =
-// 64-bit words per body bitset row = waves per env.
+// 64-bit words per body bitset row = waves per env.  A body's published state
+// is six 16-byte quads, so that a lane takes a whole body in six loads.
 template <int N_>
 struct PhysLDS {
   static constexpr int N = N_;
@@ -84,15 +86,11 @@ struct PhysLDS {
   static constexpr int CAPC = 4 * N;  // candidate pairs
   static_assert(CAPC <= 1024 && N <= 2048, "cube-cube queue packing");
   static constexpr int CAPK = 2 * N;  // pairs in contact
-  float4 pr[N];  // position and bounding radius (the substep-start position of every phase)
-  float v[3][N];
-  float w[3][N];
-  float R[9][N];
-  float size[N];
-  float4 ext[N];   // half-extents along the body axes, 0 ((a, a, a) for a cube)
+  float4 pr[N];    // position and bounding radius (the substep-start position of every phase)
+  float4 vs[N];    // velocity and size
+  float4 wt[N];    // angular velocity and type (bits)
+  float4 R[3][N];  // rows of R(q), each with the half-extent along that axis ((a, a, a) for a cube)
   float inert[3][N];  // principal moments of a box
-  float rb[N];
-  int32_t type[N];
   // arrays of disjoint phases of a substep share their storage: the grid
   // buckets (broadphase), the sorted candidate pairs (compaction and the
   // narrowphase of pairs with a sphere) and the per-lane point terms of the
@@ -102,22 +100,21 @@ struct PhysLDS {
     uint32_t cand[CAPC];    // candidate pairs i | j << 16, sorted
     float stage[9][N];      // one contact point's terms per lane, before the ordered sum
   };
-  uint64_t rowCand[N][NW];
-  uint64_t rowC[N][NW];
-  uint64_t colC[N][NW];
+  uint64_t row[N][NW];    // grid broadphase: neighbours of each body; then the candidates j > i of body i
   int32_t cstart[N];      // candidate-list start of each row
-  int32_t gflag[N];       // body touches the ground
-  uint16_t kslot[CAPC];   // slot of each candidate in contact
+  uint16_t kslot[CAPC];   // slot of each candidate in contact, kNoSlot for the others
   uint32_t ccl[CAPC];     // candidates whose bodies are both cubes: k | i << 10 | j << 21
-  int32_t gcl[N];         // cubes closer to the ground than their bounding radius
+  uint8_t gsl[N];         // spheres touching the ground
+  uint8_t gcl[N];         // cubes with a corner below the ground
   float kres[9][CAPK];    // SF xyz, Ti xyz, Tj xyz of each pair in contact
   float estage[9][N / 16];        // terms of the edge-edge point of each 16-lane group
   float gres[6][N];       // ground force and torque of each body
   int32_t scan[NW + 1];
   float red[NW];
   int32_t work;
-  int32_t kcnt, ncc, ngc;
+  int32_t kcnt, ncc;
 };
+constexpr uint16_t kNoSlot = 0xFFFF;
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
@@ -202,32 +199,30 @@ struct Point {
   f3 xc;
 };
 
+__device__ __forceinline__ f3 xyz(float4 q) { return mk(q.x, q.y, q.z); }
 template <int N>
 __device__ __forceinline__ f3 ldsP(const PhysLDS<N>& s, int b) {
-  const float4 q = s.pr[b];
-  return mk(q.x, q.y, q.z);
+  return xyz(s.pr[b]);
 }
 template <int N>
 __device__ __forceinline__ f3 ldsV(const PhysLDS<N>& s, int b) {
-  return mk(s.v[0][b], s.v[1][b], s.v[2][b]);
+  return xyz(s.vs[b]);
 }
 template <int N>
 __device__ __forceinline__ f3 ldsW(const PhysLDS<N>& s, int b) {
-  return mk(s.w[0][b], s.w[1][b], s.w[2][b]);
+  return xyz(s.wt[b]);
 }
+// rotation and half-extents of a body
 template <int N>
-__device__ __forceinline__ M3 ldsR(const PhysLDS<N>& s, int b) {
+__device__ __forceinline__ M3 ldsRE(const PhysLDS<N>& s, int b, f3* e) {
+  const float4 q0 = s.R[0][b], q1 = s.R[1][b], q2 = s.R[2][b];
   M3 R;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) R.m[k] = s.R[k][b];
+  R.m[0] = q0.x; R.m[1] = q0.y; R.m[2] = q0.z;
+  R.m[3] = q1.x; R.m[4] = q1.y; R.m[5] = q1.z;
+  R.m[6] = q2.x; R.m[7] = q2.y; R.m[8] = q2.z;
+  *e = mk(q0.w, q1.w, q2.w);
   return R;
 }
-
-// Sum of one pair's contact forces, accumulated in point order.
-struct PairAcc {
-  f3 SF, Ti, Tj;
-  int npts;
-};
 
 // Force of one contact point on the pair's first body and the torques it
 // exerts on both bodies; a_first: body A (pushed along +n) is the pair's
@@ -269,24 +264,6 @@ __device__ __forceinline__ PointTerms point_terms(const Point& pt, bool a_first,
   return r;
 }
 
-// Add the force of one contact point to its pair's sums.
-template <bool FR>
-__device__ __forceinline__ void add_point(PairAcc& acc, const Point& pt, bool a_first, f3 pi,
-                                          f3 vi, f3 wi, f3 pj, f3 vj, f3 wj, bool ground,
-                                          const PhysConsts& pc) {
-  const PointTerms t = point_terms<FR>(pt, a_first, pi, vi, wi, pj, vj, wj, ground, pc);
-  acc.SF = add(acc.SF, t.Fi);
-  acc.Ti = add(acc.Ti, t.ti);
-  if (!ground) acc.Tj = add(acc.Tj, t.tj);
-  acc.npts += 1;
-}
-
-template <int N>
-__device__ __forceinline__ f3 ldsE(const PhysLDS<N>& s, int b) {
-  const float4 e = s.ext[b];
-  return mk(e.x, e.y, e.z);
-}
-
 // Corner k of a box of half-extents e (sign + on axis t iff bit t of k is
 // set): p + R w with w = (+-e.x, +-e.y, +-e.z).
 __device__ __forceinline__ f3 corner_vertex(f3 p, const M3& R, f3 e, int k) {
@@ -310,68 +287,54 @@ __device__ __forceinline__ f3 axis_unit(int m, float sgn) {
 
 __device__ __forceinline__ float pick(f3 u, int m) { return m == 0 ? u.x : (m == 1 ? u.y : u.z); }
 
-// Sphere (centre c, radius r) against box (p, R, half-extents a); normal
-// from the box to the sphere.  Returns true on contact.
-__device__ __forceinline__ bool sphere_cube(f3 c, float r, f3 p, const M3& R, f3 a, Point* pt) {
-  const f3 u = rotT(R, sub(c, p));
-  const f3 e = mk(fminf(fmaxf(u.x, -a.x), a.x), fminf(fmaxf(u.y, -a.y), a.y), fminf(fmaxf(u.z, -a.z), a.z));
-  const f3 rv = sub(u, e);
+// The contact point of body pair (i, j), i < j, one of them a sphere (the
+// other: `box`), or (ground) of sphere i with the ground; false without
+// contact.  *a_first: the point pushes body i along +n (else body j).  Sphere
+// against sphere and sphere against box (clamped to it in its own frame, the
+// normal from the box to the sphere) meet in one square root and one
+// division by the distance, so that a wave holding both runs them once.
+template <int N>
+__device__ __forceinline__ bool sphere_point(const PhysLDS<N>& s, int i, int j, bool box, bool ground, float4 pi, float4 pj,
+                                             float si, float sj, bool sfirst, Point* pt) {
+  if (ground) {
+    pt->n = mk(0.0f, 0.0f, 1.0f);
+    pt->delta = si - pi.z;
+    pt->xc = mk(pi.x, pi.y, pi.z - si);
+    return true;
+  }
+  const f3 c = xyz(sfirst ? pi : pj), o = xyz(sfirst ? pj : pi);
+  f3 rv = sub(c, o), u = rv, e = mk(0.0f, 0.0f, 0.0f), a = e;
+  M3 R{};
+  float lim = si + sj;
+  if (box) {
+    R = ldsRE(s, sfirst ? j : i, &a);
+    lim = sfirst ? si : sj;
+    u = rotT(R, rv);
+    e = mk(fminf(fmaxf(u.x, -a.x), a.x), fminf(fmaxf(u.y, -a.y), a.y), fminf(fmaxf(u.z, -a.z), a.z));
+    rv = sub(u, e);
+  }
   const float L2 = dot(rv, rv);
-  if (!(L2 < r * r)) return false;
-  f3 nl;
-  float delta;
+  if (!(L2 < lim * lim)) return false;
+  const float L = sqrtf(L2);
+  f3 nl = mk(0.0f, 0.0f, 1.0f);
+  float delta = lim - L;
   if (L2 > 0.0f) {
-    const float L = sqrtf(L2);
     nl = mk(rv.x / L, rv.y / L, rv.z / L);
-    delta = r - L;
-  } else {
+  } else if (box) {
     float dm;
     const int m = min_axis(u, a, &dm);
     nl = axis_unit(m, pick(u, m) >= 0.0f ? 1.0f : -1.0f);
-    delta = r + dm;
+    delta = lim + dm;
   }
-  pt->n = rot(R, nl);
   pt->delta = delta;
-  pt->xc = add(p, rot(R, e));
-  return true;
-}
-
-// Narrowphase + force sum of body pair (i, j), i < j, one of them a sphere.
-template <int N, bool FR>
-__device__ __noinline__ PairAcc pair_forces(const PhysLDS<N>& s, int i, int j,
-                                            const PhysConsts& pc) {
-  PairAcc acc;
-  acc.SF = mk(0.0f, 0.0f, 0.0f);
-  acc.Ti = acc.SF;
-  acc.Tj = acc.SF;
-  acc.npts = 0;
-  const f3 pi = ldsP(s, i), pj = ldsP(s, j);
-  const f3 vi = ldsV(s, i), vj = ldsV(s, j);
-  const f3 wi = ldsW(s, i), wj = ldsW(s, j);
-  const int ti = s.type[i], tj = s.type[j];
-  const float si = s.size[i], sj = s.size[j];
-  Point pt;
-  if (ti == 0 && tj == 0) {
-    const f3 d = sub(pi, pj);
-    const float d2 = dot(d, d);
-    const float sr = si + sj;
-    if (d2 < sr * sr) {
-      const float L = sqrtf(d2);
-      pt.n = L > 0.0f ? mk(d.x / L, d.y / L, d.z / L) : mk(0.0f, 0.0f, 1.0f);
-      pt.delta = sr - L;
-      pt.xc = add(pj, mul(pt.n, sj - 0.5f * pt.delta));
-      add_point<FR>(acc, pt, true, pi, vi, wi, pj, vj, wj, false, pc);
-    }
-  } else if (ti == 0 || tj == 0) {
-    // one path for both orders: the sphere is body i (pushed along +n, the
-    // pair's first body) or body j
-    const bool sfirst = ti == 0;
-    const int cb = sfirst ? j : i;
-    const M3 Rc = ldsR(s, cb);
-    if (sphere_cube(sfirst ? pi : pj, sfirst ? si : sj, sfirst ? pj : pi, Rc, ldsE(s, cb), &pt))
-      add_point<FR>(acc, pt, sfirst, pi, vi, wi, pj, vj, wj, false, pc);
+  if (box) {
+    pt->n = rot(R, nl);
+    pt->xc = add(o, rot(R, e));
+  } else {
+    pt->n = nl;
+    pt->xc = add(o, mul(nl, sj - 0.5f * delta));
   }
-  return acc;
+  return true;
 }
 
 // Two boxes (centres pa, pb, rotations Ra, Rb, half-extents ea, eb) that
@@ -409,18 +372,15 @@ __device__ __forceinline__ bool face_separated(f3 pa, const M3& Ra, f3 ea, f3 pb
   return sep;
 }
 
-// Corner k of box A strictly inside box B: the contact point, pushed out of
-// B along the normal of B's nearest face.
-__device__ __forceinline__ bool corner_in_box(f3 pa, const M3& Ra, f3 aa, int k, f3 pb, const M3& Rb,
-                                              f3 ab, Point* pt) {
-  const f3 vtx = corner_vertex(pa, Ra, aa, k);
-  const f3 u = rotT(Rb, sub(vtx, pb));
+// Whether the corner pt->xc of a box lies strictly inside box B: the contact
+// point then pushes it out of B along the normal of B's nearest face.
+__device__ __forceinline__ bool corner_in_box(f3 pb, const M3& Rb, f3 ab, Point* pt) {
+  const f3 u = rotT(Rb, sub(pt->xc, pb));
   if (!(fabsf(u.x) < ab.x && fabsf(u.y) < ab.y && fabsf(u.z) < ab.z)) return false;
   float dm;
   const int m = min_axis(u, ab, &dm);
   pt->n = rot(Rb, axis_unit(m, pick(u, m) >= 0.0f ? 1.0f : -1.0f));
   pt->delta = dm;
-  pt->xc = vtx;
   return true;
 }
 
@@ -456,8 +416,8 @@ constexpr float kEdgeBias = 0.95f;        // an edge axis wins below this fracti
 template <int N, bool FR>
 __device__ __forceinline__ bool edge_point(PhysLDS<N>& s, bool live, int r, int lane, int i, int j,
                                            const PhysConsts& pc) {
-  const M3 Ri = ldsR(s, i), Rj = ldsR(s, j);
-  const f3 ei = ldsE(s, i), ej = ldsE(s, j);
+  f3 ei, ej;
+  const M3 Ri = ldsRE(s, i, &ei), Rj = ldsRE(s, j, &ej);
   const f3 pi = ldsP(s, i), pj = ldsP(s, j);
   const f3 d = sub(pi, pj);
   f3 L = mk(0.0f, 0.0f, 0.0f);
@@ -539,23 +499,25 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Ordered sum, over the set bits l of the group mask gm (ascending), of
-// stage[c][base + l] for l < G: the terms of one pair's contact points in
-// point order.  The G values are loaded first, then added where selected.
-template <int G, int N>
-__device__ __forceinline__ float ordered_sum(const PhysLDS<N>& s, int c, int base, uint32_t gm) {
-  float v[G];
+// Ordered sum over l < 16 of stage[c][base + l]: the terms of one pair's (or
+// one ground cube's) contact points in point order.  Lanes without a point
+// stage zeros, which change no bit of a sum that starts at +0.
+template <int N>
+__device__ __forceinline__ float ordered_sum(const PhysLDS<N>& s, int c, int base, int count) {
+  float v[16];
   const float4* src = (const float4*)&s.stage[c][base];
 #pragma unroll
-  for (int l = 0; l < G / 4; ++l) {
+  for (int l = 0; l < 4; ++l) {
     const float4 x = src[l];
     v[4 * l] = x.x; v[4 * l + 1] = x.y; v[4 * l + 2] = x.z; v[4 * l + 3] = x.w;
   }
   float acc = 0.0f;
 #pragma unroll
-  for (int l = 0; l < G; ++l)
-    if ((gm >> l) & 1u) acc = acc + v[l];
-  return acc;
+  for (int l = 0; l < 8; ++l) acc = acc + v[l];
+  float all = acc;
+#pragma unroll
+  for (int l = 8; l < 16; ++l) all = all + v[l];
+  return count > 8 ? all : acc;
 }
 
 __device__ __forceinline__ uint64_t below_mask(int b) {
@@ -600,9 +562,9 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
                          int parity, int nsteps, int broadphase) {
   constexpr int NW = PhysLDS<N>::NW;
   // Lanes of this env: N consecutive threads.  At N = 32 two envs share a
-  // wave, each in one half: their compactions count within the half, a
-  // half's first lane does its atomics, and every loop holding a wave-wide
-  // operation runs the larger of the two halves' trip counts.
+  // wave, each in one half: their compactions count within the half, and
+  // every loop holding a wave-wide operation runs the larger of the two
+  // halves' trip counts.
   constexpr int LW = N < 64 ? N : 64;  // lanes of this env in one wave
   const int tid = (int)threadIdx.x % N;
   const int lane = lane_id();
@@ -612,10 +574,23 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     return __popcll(half(m) & ((1ull << (lane - lbase)) - 1ull));
   };
   const auto wmax = [&](int x) -> int { return N < 64 ? max(x, __shfl_xor(x, 32, 64)) : x; };
+  // the next slots of a list, one per set lane: an env of one wave counts in
+  // a register, the waves of a larger one through LDS
+  const auto take = [&](uint64_t m, int& count, int32_t* shared) -> int {
+    if constexpr (N <= 64) {
+      const int first = count;
+      count += __popcll(half(m));
+      return first + below(m);
+    } else {
+      int first = 0;
+      if (lane == 0 && m) first = atomicAdd(shared, __popcll(m));
+      return __builtin_amdgcn_readfirstlane(first) + below(m);
+    }
+  };
   EnvDev ed{};
   if (env >= 0) ed = uniform_copy(W.envs + env);  // a scalar load where the env is the wave's
   const int n = ed.n_bodies;
-  if (N >= 64 && n <= 0) return;  // a whole workgroup; a half-wave env of no bodies does nothing below
+  if (N >= 64 && n <= 0) return;  // all of the env's waves; a half-wave env of no bodies does nothing below
   const int b0 = ed.body_off;
   const bool own = tid < n;
   const int64_t cap = W.cap_bodies;
@@ -638,22 +613,16 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     a = W.size[gb];
     rbv = W.rbound[gb];
     ty = W.type[gb];
-    s.size[tid] = a;
     ex = ey = ez = a;
     if (ty == 2) {
       const float* bx = W.box + 6 * (int64_t)gb;
       ex = bx[0];
       ey = bx[1];
       ez = bx[2];
-      s.ext[tid] = make_float4(ex, ey, ez, 0.0f);
       s.inert[0][tid] = bx[3];
       s.inert[1][tid] = bx[4];
       s.inert[2][tid] = bx[5];
-    } else {
-      s.ext[tid] = make_float4(a, a, a, 0.0f);
     }
-    s.rb[tid] = rbv;
-    s.type[tid] = ty;
   }
   // the policy's force on this body, held over the substeps
   f3 fx = mk(0.0f, 0.0f, 0.0f);
@@ -674,51 +643,57 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
   bool bad = false, fin = true;
   // broadphase choice: 0 auto (grid above 64 bodies), 1 grid, 2 all-pairs
   const bool use_grid = broadphase == 1 || (broadphase == 0 && n > 64);
-  // the step's candidate superset (all-pairs path): pairs found at substep 0
-  // within their bounding radii plus kSupMargin, by the lane that found them
+  // the step's candidate superset (all-pairs path): the neighbours found at
+  // substep 0 within the bounding radii plus kSupMargin
   f3 p0 = p;
   uint64_t supM = 0ull;
+  const int nn = wmax(n);  // bodies of the larger env of the wave
 
   for (int step = 0, sub_i = 0; step < nsteps;) {
     // 1. publish substep-start state
-    M3 R = quat_to_rot(qw, qx, qy, qz);
+    const M3 R = quat_to_rot(qw, qx, qy, qz);
     if (own) {
       s.pr[tid] = make_float4(p.x, p.y, p.z, rbv);
-      s.v[0][tid] = v.x; s.v[1][tid] = v.y; s.v[2][tid] = v.z;
-      s.w[0][tid] = w.x; s.w[1][tid] = w.y; s.w[2][tid] = w.z;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) s.R[k][tid] = R.m[k];
+      s.vs[tid] = make_float4(v.x, v.y, v.z, a);
+      s.wt[tid] = make_float4(w.x, w.y, w.z, __int_as_float(ty));
+      s.R[0][tid] = make_float4(R.m[0], R.m[1], R.m[2], ex);
+      s.R[1][tid] = make_float4(R.m[3], R.m[4], R.m[5], ey);
+      s.R[2][tid] = make_float4(R.m[6], R.m[7], R.m[8], ez);
     }
-    for (int k = tid; k < T; k += N)
+    if (use_grid) {
+      for (int k = tid; k < T; k += N)
 #pragma unroll
-      for (int q = 0; q < NW; ++q) s.bucket[k][q] = 0ull;
+        for (int q = 0; q < NW; ++q) s.bucket[k][q] = 0ull;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      s.rowCand[tid][q] = 0ull;
-      s.rowC[tid][q] = 0ull;
-      s.colC[tid][q] = 0ull;
+      for (int q = 0; q < NW; ++q) s.row[tid][q] = 0ull;
     }
-    if (tid == 0) {
+    if (N > 64 && tid == 0) {
       s.kcnt = 0;
       s.ncc = 0;
-      s.ngc = 0;
     }
-    // 2. broadphase.  The candidate set is exactly {(i, j): i < j,
-    // |p_i - p_j|^2 <= (R_i + R_j)^2}; two ways produce it.  All-pairs: every
-    // lane tests every body, reading it with one broadcast LDS load (no
-    // divergence) -- the faster choice for one wave.  Grid: bodies hashed into
-    // bitset buckets by cell, each lane ORs its own and the 13 half-shell
-    // neighbour buckets and tests only the bodies found.  Cells far from the
-    // origin fall back to all-pairs.
+    // 2. broadphase: M, the neighbours of this lane's body -- the bodies j
+    // with |p_i - p_j|^2 <= (R_i + R_j)^2 (the test is symmetric in the two
+    // bodies, bit for bit).  Two ways give the same set.  All pairs: the
+    // lanes of an env of one wave share the work, `span` lanes to a slice of
+    // the bodies, each reading them with broadcast loads into a bitmask of
+    // its own (lane rotations that met in LDS through one atomic per found
+    // pair measured 2,050 cycles a substep at 32 bodies; a lane adding bits
+    // to its own mask needs no branch and no atomic).  Grid: bodies hashed
+    // into bitset buckets by cell, each lane ORs its own and the 13
+    // half-shell neighbour buckets and tests only the bodies found.  Cells
+    // far from the origin fall back to all pairs.
     int cx = 0, cy = 0, cz = 0, far_cell = 0;
     if (use_grid && own) {
-      const float fx = floorf(p.x * inv_c), fy = floorf(p.y * inv_c), fz = floorf(p.z * inv_c);
-      far_cell = !(fabsf(fx) < 1000.0f && fabsf(fy) < 1000.0f && fabsf(fz) < 1000.0f);
-      cx = (int)fx; cy = (int)fy; cz = (int)fz;
+      const float gx = floorf(p.x * inv_c), gy = floorf(p.y * inv_c), gz = floorf(p.z * inv_c);
+      far_cell = !(fabsf(gx) < 1000.0f && fabsf(gy) < 1000.0f && fabsf(gz) < 1000.0f);
+      cx = (int)gx; cy = (int)gy; cz = (int)gz;
     }
     // the barrier that publishes the substep state also ORs the far-cell
     // test over every wave of the env
     const bool grid = !env_any<N>(far_cell != 0) && use_grid;
+    uint64_t M[NW];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) M[q] = 0ull;
     if (!grid && N <= 64) {
       // Substeps after the first retest only the step's superset while every
       // body of the env is within a quarter of the margin of its step-start
@@ -726,13 +701,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       // its radii plus half the margin, and the other half covers rounding
       // (positions under 1000 m, where it is below 0.1 mm).  The retest is
       // the same expression, so the candidate set is the same bits.
-      // Only where a lane has more than one batch of eight rotations: below
-      // that the retest saves nothing.
-      const int groups = n <= N / 2 ? 2 : 1;
-      const int i = groups == 2 ? (tid & (N / 2 - 1)) : tid;
-      const int g = groups == 2 ? tid / (N / 2) : 0;
-      const int R = n / 2;
-      const bool use_sup = SUP && (R + groups - 1) / groups > 8;
+      const bool use_sup = SUP && n > 32;
       bool retest = false;
       if constexpr (SUP) {
         bool risky = true;
@@ -746,17 +715,10 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         }
         retest = half(__ballot(risky)) == 0;
       }
-      // one wave: lane l tests body i against body (i + r) mod n for its
-      // share of the rotations r = 1 .. n/2 (two groups of 32 lanes when
-      // n <= 32).  Every unordered pair is one rotation away from one of its
-      // bodies; at r = n/2 (n even) both see it and the lower one keeps it.
-      // The test is symmetric in the two bodies, bit for bit.
-      // Eight rotations per batch: their loads issue back to back.
-      const bool build = sub_i == 0 && use_sup;
-      if (i < n && retest) {
+      if (retest) {
         // eight members of the superset per batch: their loads issue together
-        const float4 me = s.pr[i];
-        uint64_t m = supM;
+        const float4 me = s.pr[tid];
+        uint64_t m = own ? supM : 0ull;
         while (m) {
           float4 o[8];
           int jj[8];
@@ -764,56 +726,73 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
           for (int u = 0; u < 8; ++u) {
             jj[u] = m ? __ffsll((unsigned long long)m) - 1 : -1;
             m &= m - 1ull;
-            o[u] = s.pr[jj[u] < 0 ? i : jj[u]];
+            o[u] = s.pr[jj[u] < 0 ? tid : jj[u]];
           }
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
-            const int j = jj[u];
             const f3 d = mk(me.x - o[u].x, me.y - o[u].y, me.z - o[u].z);
             const float rs = me.w + o[u].w;
-            if ((j >= 0) & (dot(d, d) <= rs * rs)) {
-              const int lo = i < j ? i : j, hi = i < j ? j : i;
-              atomicOr((unsigned long long*)&s.rowCand[lo][0], 1ull << hi);
-            }
+            if ((jj[u] >= 0) & (dot(d, d) <= rs * rs)) M[0] |= 1ull << jj[u];
           }
         }
-      } else if (i < n) {
-        const float4 me = s.pr[i];
-        if (build) supM = 0ull;
-        for (int r0 = 1 + g; r0 <= R; r0 += 8 * groups) {
-          float4 o[8];
-          int jj[8];
+      } else {
+        // COUNT bodies from j0 against body i, as a mask of their bits from
+        // bit 0 on (slots past n hold no body; their bits are cleared below)
+        const auto slice = [&](auto count, int i, int j0, bool build, uint32_t* sup) -> uint32_t {
+          constexpr int kCount = decltype(count)::value;
+          const float4 me = s.pr[i];
+          uint32_t bits = 0u;
+          float4 o[kCount];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int r = r0 + u * groups;
-            int j = i + r;
-            if (j >= n) j -= n;
-            jj[u] = r <= R ? j : i;
-            o[u] = s.pr[jj[u]];
-          }
+          for (int u = 0; u < kCount; ++u) o[u] = s.pr[j0 + u];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int r = r0 + u * groups, j = jj[u];
+          for (int u = 0; u < kCount; ++u) {
             const f3 d = mk(me.x - o[u].x, me.y - o[u].y, me.z - o[u].z);
             const float rs = me.w + o[u].w;
             const float d2 = dot(d, d);
-            const bool mine = (r <= R) & !((2 * r == n) & (i > j));
-            if (mine & (d2 <= rs * rs)) {
-              const int lo = i < j ? i : j, hi = i < j ? j : i;
-              atomicOr((unsigned long long*)&s.rowCand[lo][0], 1ull << hi);
-            }
+            bits |= d2 <= rs * rs ? 1u << u : 0u;
             if (build) {
               const float rm = rs + kSupMargin;
-              if (mine & (d2 <= rm * rm)) supM |= 1ull << j;
+              *sup |= d2 <= rm * rm ? 1u << u : 0u;
             }
           }
+          return bits;
+        };
+        using Eight = std::integral_constant<int, 8>;
+        using Four = std::integral_constant<int, 4>;
+        uint32_t none = 0u;
+        if (N == 64 && nn > 32) {
+          const bool build = SUP && use_sup && sub_i == 0;
+          if (build) supM = 0ull;
+          for (int j0 = 0; j0 < n; j0 += 8) {
+            uint32_t sup = 0u;
+            M[0] |= (uint64_t)slice(Eight{}, tid, j0, build, &sup) << j0;
+            if (build) supM |= (uint64_t)sup << j0;
+          }
+          if (build) supM &= below_mask(n) & ~(1ull << tid);
+        } else if (nn > 16) {
+          // 32 bodies: two groups of lanes take 16 bodies each (N = 64), or
+          // each lane all of them (N = 32)
+          const int i = tid & 31, g = N == 64 ? tid >> 5 : 0;
+          uint32_t m = 0u;
+#pragma unroll
+          for (int q = 0; q < (N == 64 ? 2 : 4); ++q)
+            m |= slice(Eight{}, i, 16 * g + 8 * q, false, &none) << (8 * q);
+          m <<= 16 * g;
+          if (N == 64) m |= __shfl_xor((int)m, 32, 64);
+          M[0] = m;
+        } else {
+          // 16 bodies: four groups of four bodies (N = 64), two of eight (N = 32)
+          const int i = tid & 15, g = tid >> 4;
+          uint32_t m = N == 64 ? slice(Four{}, i, 4 * g, false, &none) << (4 * g)
+                               : slice(Eight{}, i, 8 * g, false, &none) << (8 * g);
+          m |= __shfl_xor((int)m, 16, 64);
+          if (N == 64) m |= __shfl_xor((int)m, 32, 64);
+          M[0] = m;
         }
       }
     } else if (!grid) {
       if (own) {
-        uint64_t row[NW];
-#pragma unroll
-        for (int q = 0; q < NW; ++q) row[q] = 0ull;
         const float4 me = s.pr[tid];
         // j is the same in every lane: s.pr[j] is one broadcast load
 #pragma unroll 4
@@ -821,14 +800,12 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
           const float4 o = s.pr[j];
           const f3 d = mk(me.x - o.x, me.y - o.y, me.z - o.z);
           const float rs = me.w + o.w;
-          if (j > tid && dot(d, d) <= rs * rs) {
+          if (dot(d, d) <= rs * rs) {
 #pragma unroll
             for (int q = 0; q < NW; ++q)
-              if (q == (j >> 6)) row[q] |= 1ull << (j & 63);
+              if (q == (j >> 6)) M[q] |= 1ull << (j & 63);
           }
         }
-#pragma unroll
-        for (int q = 0; q < NW; ++q) s.rowCand[tid][q] = row[q];
       }
     } else {
       if (own) {
@@ -837,9 +814,9 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       }
       env_sync<N>();
       if (own) {
-        uint64_t M[NW];
+        uint64_t B[NW];
 #pragma unroll
-        for (int q = 0; q < NW; ++q) M[q] = 0ull;
+        for (int q = 0; q < NW; ++q) B[q] = 0ull;
         // own cell and the 13 neighbours of the half shell
 #pragma unroll
         for (int o = 0; o < 14; ++o) {
@@ -850,42 +827,75 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
           else { dx = 0; dy = 0; dz = 1; }
           const uint32_t h = grid_hash(cx + dx, cy + dy, cz + dz, hmask);
 #pragma unroll
-          for (int q = 0; q < NW; ++q) M[q] |= s.bucket[h][q];
+          for (int q = 0; q < NW; ++q) B[q] |= s.bucket[h][q];
         }
 #pragma unroll
         for (int q = 0; q < NW; ++q)
-          if (q == (tid >> 6)) M[q] &= ~(1ull << (tid & 63));
+          if (q == (tid >> 6)) B[q] &= ~(1ull << (tid & 63));
+        const float4 me = s.pr[tid];
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
-          uint64_t m = M[q];
+          uint64_t m = B[q];
           while (m) {
             const int j = 64 * q + __ffsll((unsigned long long)m) - 1;
             m &= m - 1ull;
-            const int lo = tid < j ? tid : j, hi = tid < j ? j : tid;
-            const float4 a4 = s.pr[lo], b4 = s.pr[hi];
-            const f3 d = mk(a4.x - b4.x, a4.y - b4.y, a4.z - b4.z);
-            const float rs = a4.w + b4.w;
-            if (dot(d, d) <= rs * rs)
-              atomicOr((unsigned long long*)&s.rowCand[lo][hi >> 6], 1ull << (hi & 63));
+            const float4 o = s.pr[j];
+            const f3 d = mk(me.x - o.x, me.y - o.y, me.z - o.z);
+            const float rs = me.w + o.w;
+            if (dot(d, d) <= rs * rs) {
+              atomicOr((unsigned long long*)&s.row[tid][j >> 6], 1ull << (j & 63));
+              atomicOr((unsigned long long*)&s.row[j][tid >> 6], 1ull << (tid & 63));
+            }
           }
         }
       }
-    }
-    env_sync<N>();
-    // 3. compaction of candidate rows into the sorted pair list
-    int ccount = 0;
-    if (own) {
+      env_sync<N>();
 #pragma unroll
-      for (int q = 0; q < NW; ++q) ccount += __popcll(s.rowCand[tid][q]);
+      for (int q = 0; q < NW; ++q) M[q] = s.row[tid][q];
     }
-    int ctotal;
-    const int cstart = block_excl_scan<N>(ccount, s.scan, &ctotal);
-    s.cstart[tid] = cstart;
-    if (own) {
+    // the body's candidates above it (its row) and below it (its column)
+    uint64_t row[NW], col[NW];
+    int ccount = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const uint64_t m = own ? M[q] & below_mask(n - 64 * q < 0 ? 0 : n - 64 * q) : 0ull;
+      const int t = tid - 64 * q;
+      const uint64_t up = t < 0 ? ~0ull : (t >= 63 ? 0ull : ~0ull << (t + 1));
+      row[q] = m & up;
+      col[q] = m & below_mask(t < 0 ? 0 : t);
+      ccount += __popcll(row[q]);
+    }
+    // a sphere touching the ground, and a cube with a corner below it (the
+    // same z of each corner as the corner test computes, p.z + row 2 of R
+    // times (+-e)): in contact, so the flags need no LDS
+    const bool gsph = own && ty == 0 && p.z < a;
+    bool gcube = false;
+    if (own && ty != 0 && p.z < rbv) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float wx = (k & 1) ? ex : -ex, wy = (k & 2) ? ey : -ey, wz = (k & 4) ? ez : -ez;
+        gcube |= p.z + ((R.m[6] * wx + R.m[7] * wy) + R.m[8] * wz) < 0.0f;
+      }
+    }
+    // 3. compaction: one scan places the candidate rows in a list sorted by
+    // (i, j) and both kinds of ground contact in theirs (candidates in the
+    // low 16 bits, at most N (N - 1) / 2; then 8 bits each)
+    int ctotal, ngs, ngc;
+    {
+      int total;
+      const int at = block_excl_scan<N>(ccount | (gsph ? 1 << 16 : 0) | (gcube ? 1 << 24 : 0), s.scan, &total);
+      const int cstart = at & 0xFFFF;
+      ctotal = total & 0xFFFF;
+      ngs = (total >> 16) & 0xFF;
+      ngc = (int)((uint32_t)total >> 24);
+      if (gsph) s.gsl[(at >> 16) & 0xFF] = (uint8_t)tid;
+      if (gcube) s.gcl[(uint32_t)at >> 24] = (uint8_t)tid;
+      s.cstart[tid] = cstart;
       int pos = cstart;
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
-        uint64_t m = s.rowCand[tid][q];
+        s.row[tid][q] = row[q];
+        uint64_t m = row[q];
         while (m) {
           const int j = 64 * q + __ffsll((unsigned long long)m) - 1;
           m &= m - 1ull;
@@ -896,269 +906,202 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     }
     if (ctotal > PhysLDS<N>::CAPC) bad = true;
     env_sync<N>();
-    // 4a. narrowphase of the pairs with a sphere, one candidate per lane;
-    // cube-cube pairs are queued.  A pair in contact takes the next free
-    // slot (handed out per wave) and its candidate remembers it, so the
-    // order of the slots affects no sum.
+    // 4a. the pairs with a sphere and the spheres on the ground, one per
+    // lane; box pairs are queued.  A pair in contact takes the next free
+    // slot and its candidate remembers it, so the order of the slots affects
+    // no sum.
     const int nc = ctotal < PhysLDS<N>::CAPC ? ctotal : PhysLDS<N>::CAPC;
-    const int ncw = wmax(nc);
-    for (int c0 = 0; c0 < ncw; c0 += N) {
+    const int items = wmax(nc + ngs);
+    int kcnt = 0, ncc = 0;
+    for (int c0 = 0; c0 < items; c0 += N) {
       const int k = c0 + tid;
-      bool contact = false, cc = false;
-      PairAcc acc;
+      const bool pair = k < nc, ground = !pair && k < nc + ngs;
+      bool hit = false, cc = false;
       int i = 0, j = 0;
-      if (k < nc) {
-        const uint32_t pr = s.cand[k];
-        i = (int)(pr & 0xFFFFu);
-        j = (int)(pr >> 16);
-        cc = (s.type[i] != 0) & (s.type[j] != 0);
-        if (!cc) {
-          acc = pair_forces<N, FR>(s, i, j, pc);
-          contact = acc.npts > 0;
+      PointTerms t;
+      if (pair || ground) {
+        if (pair) {
+          const uint32_t pr = s.cand[k];
+          i = (int)(pr & 0xFFFFu);
+          j = (int)(pr >> 16);
         } else {
+          i = j = s.gsl[k - nc];
+        }
+        const float4 wi = s.wt[i], wj = s.wt[j];
+        const float4 pi = s.pr[i], pj = s.pr[j], vi = s.vs[i], vj = s.vs[j];
+        const bool bi = __float_as_int(wi.w) != 0, bj = __float_as_int(wj.w) != 0;
+        if (bi & bj) {
           // box pairs apart along a face axis have no point: not queued
-          cc = !face_separated(ldsP(s, i), ldsR(s, i), ldsE(s, i), ldsP(s, j), ldsR(s, j), ldsE(s, j));
+          f3 ei, ej;
+          const M3 Ri = ldsRE(s, i, &ei), Rj = ldsRE(s, j, &ej);
+          cc = !face_separated(xyz(pi), Ri, ei, xyz(pj), Rj, ej);
+        } else {
+          Point pt;
+          hit = sphere_point(s, i, j, bi | bj, ground, pi, pj, vi.w, vj.w, !bi, &pt);
+          if (hit)
+            t = point_terms<FR>(pt, !bi, xyz(pi), xyz(vi), xyz(wi), xyz(pj), xyz(vj), xyz(wj), ground, pc);
         }
       }
-      const uint64_t cm = __ballot(contact), qm = __ballot(cc);
-      int kb = 0, qb = 0;
-      if (lane == lbase) {
-        if (half(cm)) kb = atomicAdd(&s.kcnt, __popcll(half(cm)));
-        if (half(qm)) qb = atomicAdd(&s.ncc, __popcll(half(qm)));
+      const bool contact = hit && pair;
+      const int slot = take(__ballot(contact), kcnt, &s.kcnt);
+      const int at = take(__ballot(cc), ncc, &s.ncc);
+      if (pair) s.kslot[k] = contact ? (uint16_t)slot : kNoSlot;
+      if (contact && slot < PhysLDS<N>::CAPK) {
+        s.kres[0][slot] = t.Fi.x; s.kres[1][slot] = t.Fi.y; s.kres[2][slot] = t.Fi.z;
+        s.kres[3][slot] = t.ti.x; s.kres[4][slot] = t.ti.y; s.kres[5][slot] = t.ti.z;
+        s.kres[6][slot] = t.tj.x; s.kres[7][slot] = t.tj.y; s.kres[8][slot] = t.tj.z;
       }
-      kb = __shfl(kb, lbase, 64);
-      qb = __shfl(qb, lbase, 64);
-      if (contact) {
-        const int slot = kb + below(cm);
-        s.kslot[k] = (uint16_t)slot;
-        if (slot < PhysLDS<N>::CAPK) {
-          s.kres[0][slot] = acc.SF.x; s.kres[1][slot] = acc.SF.y; s.kres[2][slot] = acc.SF.z;
-          s.kres[3][slot] = acc.Ti.x; s.kres[4][slot] = acc.Ti.y; s.kres[5][slot] = acc.Ti.z;
-          s.kres[6][slot] = acc.Tj.x; s.kres[7][slot] = acc.Tj.y; s.kres[8][slot] = acc.Tj.z;
-        }
-        atomicOr((unsigned long long*)&s.rowC[i][j >> 6], 1ull << (j & 63));
-        atomicOr((unsigned long long*)&s.colC[j][i >> 6], 1ull << (i & 63));
+      if (ground) {
+        s.gres[0][i] = t.Fi.x; s.gres[1][i] = t.Fi.y; s.gres[2][i] = t.Fi.z;
+        s.gres[3][i] = t.ti.x; s.gres[4][i] = t.ti.y; s.gres[5][i] = t.ti.z;
       }
-      if (cc) s.ccl[qb + below(qm)] = (uint32_t)k | ((uint32_t)i << 10) | ((uint32_t)j << 21);
-    }
-    // ground: a sphere's single point on its own lane; cubes are queued
-    bool gsph = false;
-    PairAcc gs;
-    if (own && p.z < rbv && ty == 0) {
-      const f3 z3 = mk(0.0f, 0.0f, 0.0f);
-      Point pt;
-      gs.SF = z3;
-      gs.Ti = z3;
-      gs.Tj = z3;
-      gs.npts = 0;
-      if (p.z < a) {
-        pt.n = mk(0.0f, 0.0f, 1.0f);
-        pt.delta = a - p.z;
-        pt.xc = mk(p.x, p.y, p.z - a);
-        add_point<FR>(gs, pt, true, p, v, w, z3, z3, z3, true, pc);
-        gsph = true;
-      }
-    }
-    {
-      // a cube is queued for the 8-lane corner terms only if one of its
-      // corners is below the ground: the same z of each corner as the
-      // corner test computes, p.z + row 2 of R times (+-e)
-      bool gq = false;
-      if (own && p.z < rbv && ty != 0) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const float wx = (k & 1) ? ex : -ex, wy = (k & 2) ? ey : -ey, wz = (k & 4) ? ez : -ez;
-          gq |= p.z + ((R.m[6] * wx + R.m[7] * wy) + R.m[8] * wz) < 0.0f;
-        }
-      }
-      const uint64_t gm = __ballot(gq);
-      int gb = 0;
-      if (lane == lbase && half(gm)) gb = atomicAdd(&s.ngc, __popcll(half(gm)));
-      gb = __shfl(gb, lbase, 64);
-      if (gq) s.gcl[gb + below(gm)] = tid;
-      s.gflag[tid] = gsph ? 1 : 0;
-      if (gsph) {
-        s.gres[0][tid] = gs.SF.x; s.gres[1][tid] = gs.SF.y; s.gres[2][tid] = gs.SF.z;
-        s.gres[3][tid] = gs.Ti.x; s.gres[4][tid] = gs.Ti.y; s.gres[5][tid] = gs.Ti.z;
-      }
+      if (cc) s.ccl[at] = (uint32_t)k | ((uint32_t)i << 10) | ((uint32_t)j << 21);
     }
     env_sync<N>();
-    // 4b. cube-cube pairs, 16 lanes each: lane r of a group tests corner
-    // r & 7 of cube i inside cube j (r < 8), then of j inside i -- the
-    // oracle's point order -- and lanes 0..8 of the group then sum one
-    // component each over the points found, in that order.
-    const int ncc = s.ncc;
-    const int nccw = wmax(ncc);
-    for (int t0 = 0; t0 < 16 * nccw; t0 += N) {
+    if (N > 64) ncc = s.ncc;
+    // 4b. box pairs, 16 lanes each, then cubes on the ground, 8 lanes each, in
+    // one list of lanes.  Lane r of a pair tests corner r & 7 of box i inside
+    // box j (r < 8), then of j inside i -- the oracle's point order; lane r
+    // of a ground cube tests corner r.  The first 9 (6) lanes then sum one
+    // component each over the points, in that order.
+    const int lanes = wmax(16 * ncc + 8 * ngc);
+    for (int t0 = 0; t0 < lanes; t0 += N) {
       const int t = t0 + tid;
-      const int r = lane & 15;
+      const bool pair = t < 16 * ncc, ground = !pair && t < 16 * ncc + 8 * ngc;
+      const int r = pair ? (lane & 15) : (lane & 7);
       bool hit = false;
       int k = 0, i = 0, j = 0;
-      if (t < 16 * ncc) {
-        const uint32_t e = s.ccl[t >> 4];
-        k = (int)(e & 0x3FFu);
-        i = (int)((e >> 10) & 0x7FFu);
-        j = (int)(e >> 21);
-        const int A = r < 8 ? i : j, B = r < 8 ? j : i;
-        const f3 pA = ldsP(s, A), pB = ldsP(s, B);
-        const M3 RA = ldsR(s, A), RB = ldsR(s, B);
-        const f3 aA = ldsE(s, A), aB = ldsE(s, B);
-        const f3 vi = ldsV(s, i), wi = ldsW(s, i), vj = ldsV(s, j), wj = ldsW(s, j);
-        Point pt;
-        hit = corner_in_box(pA, RA, aA, r & 7, pB, RB, aB, &pt);
-        if (hit) {
-          const f3 pi = r < 8 ? pA : pB, pj = r < 8 ? pB : pA;
-          const PointTerms pq = point_terms<FR>(pt, r < 8, pi, vi, wi, pj, vj, wj, false, pc);
-          s.stage[0][tid] = pq.Fi.x; s.stage[1][tid] = pq.Fi.y; s.stage[2][tid] = pq.Fi.z;
-          s.stage[3][tid] = pq.ti.x; s.stage[4][tid] = pq.ti.y; s.stage[5][tid] = pq.ti.z;
-          s.stage[6][tid] = pq.tj.x; s.stage[7][tid] = pq.tj.y; s.stage[8][tid] = pq.tj.z;
+      PointTerms pq;
+      pq.Fi = pq.ti = pq.tj = mk(0.0f, 0.0f, 0.0f);
+      if (pair || ground) {
+        if (pair) {
+          const uint32_t e = s.ccl[t >> 4];
+          k = (int)(e & 0x3FFu);
+          i = (int)((e >> 10) & 0x7FFu);
+          j = (int)(e >> 21);
+        } else {
+          i = j = s.gcl[(t - 16 * ncc) >> 3];
         }
+        // the corner's body A and the body B it may lie in
+        const bool first = r < 8;
+        const int A = first ? i : j, B = first ? j : i;
+        const f3 pA = ldsP(s, A), vA = ldsV(s, A), wA = ldsW(s, A);
+        f3 aA, aB;
+        const M3 RA = ldsRE(s, A, &aA);
+        Point pt;
+        pt.n = mk(0.0f, 0.0f, 1.0f);
+        pt.xc = corner_vertex(pA, RA, aA, r & 7);
+        f3 pB = pA, vB = vA, wB = wA;
+        if (ground) {
+          pt.delta = -pt.xc.z;
+          hit = pt.xc.z < 0.0f;
+        } else {
+          pB = ldsP(s, B);
+          vB = ldsV(s, B);
+          wB = ldsW(s, B);
+          const M3 RB = ldsRE(s, B, &aB);
+          hit = corner_in_box(pB, RB, aB, &pt);
+        }
+        if (hit)
+          pq = point_terms<FR>(pt, first, first ? pA : pB, first ? vA : vB, first ? wA : wB, first ? pB : pA,
+                               first ? vB : vA, first ? wB : wA, ground, pc);
       }
+      s.stage[0][tid] = pq.Fi.x; s.stage[1][tid] = pq.Fi.y; s.stage[2][tid] = pq.Fi.z;
+      s.stage[3][tid] = pq.ti.x; s.stage[4][tid] = pq.ti.y; s.stage[5][tid] = pq.ti.z;
+      s.stage[6][tid] = pq.tj.x; s.stage[7][tid] = pq.tj.y; s.stage[8][tid] = pq.tj.z;
       // edge-edge point (after the 16 vertex points in the pair's order)
       bool ehit = false;
-      if constexpr (EE) ehit = edge_point<N, FR>(s, t < 16 * ncc, r, lane, i, j, pc);
-      const uint64_t hm = __ballot(hit);
+      if constexpr (EE) ehit = edge_point<N, FR>(s, pair, lane & 15, lane, i, j, pc);
+      const uint64_t hm = __ballot(hit && pair);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const int g0 = lane & 48;  // the group's first lane in the wave
-      const uint32_t gm = (uint32_t)(hm >> g0) & 0xFFFFu;
+      const int g0 = lane & 48;  // the pair's first lane in the wave
+      const bool any = pair && ((uint32_t)(hm >> g0) & 0xFFFFu || ehit);
       float sum = 0.0f;
-      if (r < 9) sum = ordered_sum<16, N>(s, r, tid - r, gm);
+      if (r < 9) sum = ordered_sum<N>(s, r, tid - r, pair ? 16 : 8);
       if constexpr (EE) {
         if (ehit && r < 9) sum = sum + s.estage[r][tid >> 4];
       }
-      const bool any = gm != 0 || ehit;
-      const uint64_t lead = __ballot(r == 0 && any);
-      int kb = 0;
-      if (lane == lbase && half(lead)) kb = atomicAdd(&s.kcnt, __popcll(half(lead)));
-      kb = __shfl(kb, lbase, 64);
+      const uint64_t lead = __ballot(any && r == 0);
+      const int mine = take(lead, kcnt, &s.kcnt);  // the slot of the pair's first lane
+      const int slot = __shfl(mine, g0, 64);
       if (any) {
-        const int slot = kb + __popcll(half(lead) & ((1ull << (g0 - lbase)) - 1ull));
         if (r < 9 && slot < PhysLDS<N>::CAPK) s.kres[r][slot] = sum;
-        if (r == 0) {
-          s.kslot[k] = (uint16_t)slot;
-          atomicOr((unsigned long long*)&s.rowC[i][j >> 6], 1ull << (j & 63));
-          atomicOr((unsigned long long*)&s.colC[j][i >> 6], 1ull << (i & 63));
-        }
+        if (r == 0) s.kslot[k] = (uint16_t)slot;
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-    // 4c. cubes near the ground, 8 lanes each: lane r tests corner r, and
-    // lanes 0..5 sum the force and torque components in corner order
-    const int ngc = s.ngc;
-    const int ngcw = wmax(ngc);
-    for (int t0 = 0; t0 < 8 * ngcw; t0 += N) {
-      const int t = t0 + tid;
-      const int r = lane & 7;
-      bool hit = false;
-      int b = 0;
-      if (t < 8 * ngc) {
-        b = s.gcl[t >> 3];
-        const f3 pb = ldsP(s, b), vb = ldsV(s, b), wb = ldsW(s, b);
-        const f3 vtx = corner_vertex(pb, ldsR(s, b), ldsE(s, b), r);
-        if (vtx.z < 0.0f) {
-          hit = true;
-          const f3 z3 = mk(0.0f, 0.0f, 0.0f);
-          Point pt;
-          pt.n = mk(0.0f, 0.0f, 1.0f);
-          pt.delta = -vtx.z;
-          pt.xc = vtx;
-          const PointTerms pq = point_terms<FR>(pt, true, pb, vb, wb, z3, z3, z3, true, pc);
-          s.stage[0][tid] = pq.Fi.x; s.stage[1][tid] = pq.Fi.y; s.stage[2][tid] = pq.Fi.z;
-          s.stage[3][tid] = pq.ti.x; s.stage[4][tid] = pq.ti.y; s.stage[5][tid] = pq.ti.z;
-        }
-      }
-      const uint64_t hm = __ballot(hit);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const uint32_t gm = (uint32_t)(hm >> (lane & 56)) & 0xFFu;
-      if (gm != 0 && r < 6) {
-        s.gres[r][b] = ordered_sum<8, N>(s, r, tid - r, gm);
-        if (r == 0) s.gflag[b] = 1;
-      }
+      if (ground && r < 6) s.gres[r][i] = sum;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     env_sync<N>();
-    if (s.kcnt > PhysLDS<N>::CAPK) bad = true;
+    if (N > 64) kcnt = s.kcnt;
+    if (kcnt > PhysLDS<N>::CAPK) bad = true;
     // 5. gather in sorted pair order, then the ground, then integrate.
-    // Contacts are taken four at a time so that each level of lookups
+    // Candidates are taken four at a time so that each level of lookups
     // (candidate index, slot, sums) issues its loads together.
     if (own) {
       f3 F = mk(0.0f, 0.0f, 0.0f), Tq = F;
+      if (kcnt > 0) {
 #pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        // pairs (i, tid), i ascending: the candidate index of (i, tid) is
-        // the start of row i plus the rank of tid in that row
-        uint64_t m = s.colC[tid][q];
-        while (m) {
-          int ii[4], idx[4];
+        for (int q = 0; q < NW; ++q) {
+          // pairs (i, tid), i ascending: the candidate index of (i, tid) is
+          // the start of row i plus the rank of tid in that row
+          uint64_t m = col[q];
+          while (m) {
+            int ii[4], idx[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            ii[u] = m ? 64 * q + __ffsll((unsigned long long)m) - 1 : -1;
-            m &= m - 1ull;
+            for (int u = 0; u < 4; ++u) {
+              ii[u] = m ? 64 * q + __ffsll((unsigned long long)m) - 1 : -1;
+              m &= m - 1ull;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int i = ii[u] < 0 ? 0 : ii[u];
+              const int c = s.cstart[i] + popc_below<NW>(s.row[i], tid);
+              idx[u] = s.kslot[c < PhysLDS<N>::CAPC ? c : 0];
+              if (ii[u] < 0 || c >= PhysLDS<N>::CAPC || idx[u] >= PhysLDS<N>::CAPK) idx[u] = -1;
+            }
+            float kv[4][6];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int x = idx[u] < 0 ? 0 : idx[u];
+              kv[u][0] = s.kres[0][x]; kv[u][1] = s.kres[1][x]; kv[u][2] = s.kres[2][x];
+              kv[u][3] = s.kres[6][x]; kv[u][4] = s.kres[7][x]; kv[u][5] = s.kres[8][x];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              if (idx[u] >= 0) {
+                F = sub(F, mk(kv[u][0], kv[u][1], kv[u][2]));
+                Tq = add(Tq, mk(kv[u][3], kv[u][4], kv[u][5]));
+              }
+            }
           }
+        }
+        // pairs (tid, j), j ascending: the candidates of row tid in turn
+        const int c1 = s.cstart[tid] + ccount;
+        for (int c = s.cstart[tid]; c < c1; c += 4) {
+          int idx[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const int i = ii[u] < 0 ? 0 : ii[u];
-            idx[u] = s.kslot[s.cstart[i] + popc_below<NW>(s.rowCand[i], tid)];
-            if (ii[u] < 0 || idx[u] >= PhysLDS<N>::CAPK) idx[u] = -1;
+            const bool ok = c + u < c1 && c + u < PhysLDS<N>::CAPC;
+            idx[u] = s.kslot[ok ? c + u : 0];
+            if (!ok || idx[u] >= PhysLDS<N>::CAPK) idx[u] = -1;
           }
           float kv[4][6];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int x = idx[u] < 0 ? 0 : idx[u];
             kv[u][0] = s.kres[0][x]; kv[u][1] = s.kres[1][x]; kv[u][2] = s.kres[2][x];
-            kv[u][3] = s.kres[6][x]; kv[u][4] = s.kres[7][x]; kv[u][5] = s.kres[8][x];
+            kv[u][3] = s.kres[3][x]; kv[u][4] = s.kres[4][x]; kv[u][5] = s.kres[5][x];
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             if (idx[u] >= 0) {
-              F = sub(F, mk(kv[u][0], kv[u][1], kv[u][2]));
+              F = add(F, mk(kv[u][0], kv[u][1], kv[u][2]));
               Tq = add(Tq, mk(kv[u][3], kv[u][4], kv[u][5]));
             }
           }
         }
       }
-      {
-        // pairs (tid, j), j ascending: candidates of row tid in contact
-        int c = cstart;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-          uint64_t m = s.rowCand[tid][q];
-          const uint64_t mc = s.rowC[tid][q];
-          uint64_t mk_ = mc;
-          while (mk_) {
-            // candidate index of each of the next four contacts: the row
-            // start plus its rank among the row's candidates
-            int idx[4];
-            bool ok[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              ok[u] = mk_ != 0ull;
-              const int j = ok[u] ? __ffsll((unsigned long long)mk_) - 1 : 0;
-              mk_ &= mk_ - 1ull;
-              idx[u] = s.kslot[c + __popcll(m & below_mask(j))];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (!ok[u] || idx[u] >= PhysLDS<N>::CAPK) idx[u] = -1;
-            float kv[4][6];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int x = idx[u] < 0 ? 0 : idx[u];
-              kv[u][0] = s.kres[0][x]; kv[u][1] = s.kres[1][x]; kv[u][2] = s.kres[2][x];
-              kv[u][3] = s.kres[3][x]; kv[u][4] = s.kres[4][x]; kv[u][5] = s.kres[5][x];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              if (idx[u] >= 0) {
-                F = add(F, mk(kv[u][0], kv[u][1], kv[u][2]));
-                Tq = add(Tq, mk(kv[u][3], kv[u][4], kv[u][5]));
-              }
-            }
-          }
-          c += __popcll(m);
-        }
-      }
-      if (s.gflag[tid]) {
+      if (gsph || gcube) {
         F = add(F, mk(s.gres[0][tid], s.gres[1][tid], s.gres[2][tid]));
         Tq = add(Tq, mk(s.gres[3][tid], s.gres[4][tid], s.gres[5][tid]));
       }
@@ -1171,12 +1114,11 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         // a box: Euler's equations in the body frame with the gyroscopic
         // term, R of the substep start: w_b = R^T w,
         // dw_b = (R^T T - w_b x (I w_b)) / I, w = R (w_b + h dw_b)
-        const M3 Rs = ldsR(s, tid);
         const f3 I = mk(s.inert[0][tid], s.inert[1][tid], s.inert[2][tid]);
-        const f3 wb = rotT(Rs, w), tb = rotT(Rs, Tq);
+        const f3 wb = rotT(R, w), tb = rotT(R, Tq);
         const f3 gy = cross(wb, mk(I.x * wb.x, I.y * wb.y, I.z * wb.z));
         const f3 dwb = mk((tb.x - gy.x) / I.x, (tb.y - gy.y) / I.y, (tb.z - gy.z) / I.z);
-        w = rot(Rs, add(wb, mul(dwb, pc.h)));
+        w = rot(R, add(wb, mul(dwb, pc.h)));
       } else {
         w = add(w, mul(mul(Tq, inv_I), pc.h));
       }
@@ -1192,37 +1134,34 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       const float inv = 1.0f / sqrtf(n2);
       qw = qw * inv; qx = qx * inv; qy = qy * inv; qz = qz * inv;
     }
-    env_sync<N>();
     if (W.contacts) {
-      // pairs of row tid in ascending j, then (tid, ground)
-      int cnt = 0;
-      bool gc = false;
-      if (own) {
-        gc = s.gflag[tid] != 0;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) cnt += __popcll(s.rowC[tid][q]);
-        cnt += gc ? 1 : 0;
-      }
+      // pairs of row tid in contact, in ascending j, then (tid, ground)
+      const bool gc = gsph || gcube;
+      int cnt = gc ? 1 : 0;
+      const int c0 = s.cstart[tid];
+      for (int c = c0; c < c0 + ccount; ++c) cnt += (c < PhysLDS<N>::CAPC && s.kslot[c] != kNoSlot) ? 1 : 0;
       int tot;
       const int off = block_excl_scan<N>(cnt, s.scan, &tot);
       int32_t* dst = W.contacts + ((int64_t)(env < 0 ? 0 : env) * pc.substeps + sub_i) * (1 + 2 * W.pair_cap);
       if (tid == 0 && env >= 0) dst[0] = tot;
       if (own) {
-        int pos = off;
+        int pos = off, c = c0;
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
-          uint64_t m = s.rowC[tid][q];
+          uint64_t m = row[q];
           while (m) {
             const int j = 64 * q + __ffsll((unsigned long long)m) - 1;
             m &= m - 1ull;
-            if (pos < W.pair_cap) { dst[1 + 2 * pos] = tid; dst[2 + 2 * pos] = j; }
-            ++pos;
+            if (c < PhysLDS<N>::CAPC && s.kslot[c] != kNoSlot) {
+              if (pos < W.pair_cap) { dst[1 + 2 * pos] = tid; dst[2 + 2 * pos] = j; }
+              ++pos;
+            }
+            ++c;
           }
         }
         if (gc && pos < W.pair_cap) { dst[1 + 2 * pos] = tid; dst[2 + 2 * pos] = kGroundPair; }
       }
     }
-    env_sync<N>();
     if (++sub_i == pc.substeps) {
       // the end of a step
       sub_i = 0;
@@ -1232,6 +1171,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
             isfinite(v.z) && isfinite(w.x) && isfinite(w.y) && isfinite(w.z) && isfinite(qw) && isfinite(qx) &&
             isfinite(qy) && isfinite(qz);
     }
+    env_sync<N>();  // the next substep clears what a wave still gathering reads
   }
   if (own) {
     out[PX * cap + gb] = p.x; out[PY * cap + gb] = p.y; out[PZ * cap + gb] = p.z;
