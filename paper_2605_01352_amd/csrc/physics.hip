@@ -111,7 +111,6 @@ struct PhysLDS {
   float gres[6][N];       // ground force and torque of each body
   int32_t scan[NW + 1];
   float red[NW];
-  int32_t work;
   int32_t kcnt, ncc;
 };
 constexpr uint16_t kNoSlot = 0xFFFF;
@@ -1186,14 +1185,19 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
 // FR: friction; EE: edge-edge points of box pairs; SUP: the step's candidate
 // superset on the all-pairs path (compiled in only for launches whose envs
 // exceed 32 bodies, where it pays).  N lanes per env: a workgroup of 64
-// threads holds two envs at N = 32, one at N = 64; two waves hold one env at
-// N = 128.  Work item w takes envs P w .. P w + P - 1 of the list (P envs per
-// workgroup).
+// threads holds two envs at N = 32, one at N = 64.  At N = 128 a workgroup of
+// two waves holds one env of more than 64 bodies (the list's first n_big, which
+// the list's order puts in front) or two smaller ones, a wave each: with two
+// waves for every env, 1,500 envs of 4 to 128 bodies took 107 us a step.
 template <int N, bool FR, bool EE, bool SUP>
 __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, PhysConsts pc, PhysLaunch L) {
-  constexpr int P = N < 64 ? 64 / N : 1;
-  __shared__ PhysLDS<N> sh[P];
-  const int sub = (int)threadIdx.x / N;
+  constexpr int P = N == 64 ? 1 : 2;  // envs per workgroup (N = 128: beyond the first n_big)
+  constexpr int kSmall = N == 128 ? 64 : N;
+  __shared__ union LDS {
+    PhysLDS<N> big;
+    PhysLDS<kSmall> small[P];
+  } sh;
+  __shared__ int32_t next;
   // The step is latency-bound; a higher issue priority shortens it when it
   // shares CUs with the render phase.
   switch (L.prio) {
@@ -1202,23 +1206,30 @@ __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, Ph
     case 3: __builtin_amdgcn_s_setprio(3); break;
     default: break;
   }
-  if (L.persistent == 0) {
-    const int wi = blockIdx.x;
-    if (P * wi >= L.n_work) return;
-    const int item = P * wi + sub;
-    step_env<N, FR, EE, SUP>(sh[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity, L.nsteps,
-                             L.broadphase);
-    return;
-  }
+  const int big = N == 128 ? L.n_big : 0;
+  const int items = big + (L.n_work - big + P - 1) / P;
+  // one copy of the step for both launch forms: it is 17 KB of code, and the
+  // instruction cache is shared with the render's kernels
+  int wi = blockIdx.x;
   for (;;) {
-    if (threadIdx.x == 0) sh[0].work = atomicAdd(L.queue, 1);
-    __syncthreads();
-    const int wi = sh[0].work;
-    __syncthreads();
-    if (P * wi >= L.n_work) return;
-    const int item = P * wi + sub;
-    step_env<N, FR, EE, SUP>(sh[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity, L.nsteps,
-                             L.broadphase);
+    if (L.persistent) {
+      if (threadIdx.x == 0) next = atomicAdd(L.queue, 1);
+      __syncthreads();
+      wi = next;
+      __syncthreads();
+    }
+    if (wi >= items) return;
+    if (N == 128 && wi < big) {
+      step_env<N, FR, EE, SUP>(sh.big, W, pc, uniform_ld(L.work + wi), L.parity, L.nsteps, L.broadphase);
+    } else {
+      int sub = P == 1 ? 0 : (int)threadIdx.x / kSmall;
+      if (N == 128) sub = __builtin_amdgcn_readfirstlane(sub);
+      const int item = big + P * (wi - big) + sub;
+      step_env<kSmall, FR, EE, SUP>(sh.small[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity,
+                                    L.nsteps, L.broadphase);
+    }
+    if (!L.persistent) return;
+    __syncthreads();  // the next env reuses the LDS
   }
 }
 
@@ -1293,16 +1304,17 @@ hipError_t launch_physics(const WorldDev& w, const PhysConsts& pc, const PhysLau
                           hipStream_t s, LaunchEvents* ev) {
   if (l.n_work <= 0) return hipSuccess;
   // lanes per env: two envs of at most 32 bodies share a wave when packing
-  // is on; one wave for up to 64 bodies; two for up to 128
+  // is on; one wave for up to 64 bodies; two for up to 128 (beside smaller
+  // envs of one wave each)
   const int N = (l.max_bodies <= 32 && l.pack == 2) ? 32 : (l.max_bodies <= 64 ? 64 : 128);
-  const int P = N < 64 ? 64 / N : 1;
-  const int items = (l.n_work + P - 1) / P;
+  const int big = N == 128 ? l.n_big : 0, P = N == 64 ? 1 : 2;
+  const int items = big + (l.n_work - big + P - 1) / P;
   const bool fr = pc.mu > 0.0f, ee = pc.edge != 0;
   int grid = items;
   if (l.persistent != 0) {
     const void* fn = N == 32 ? physics_fn<32, false>(fr, ee)
                      : N == 64 ? (l.max_bodies > 32 ? physics_fn<64, true>(fr, ee) : physics_fn<64, false>(fr, ee))
-                               : physics_fn<128, false>(fr, ee);
+                               : physics_fn<128, true>(fr, ee);
     const hipError_t e = persistent_grid(l.persistent, items, fn, N < 64 ? 64 : N, 0, &grid);
     if (e != hipSuccess) return e;
   }
@@ -1315,7 +1327,7 @@ hipError_t launch_physics(const WorldDev& w, const PhysConsts& pc, const PhysLau
   if (N == 32) launch_n<32, false>(fr, ee, ev, dim3(grid), s, w, pc, lt);
   else if (N == 64 && l.max_bodies > 32) launch_n<64, true>(fr, ee, ev, dim3(grid), s, w, pc, lt);
   else if (N == 64) launch_n<64, false>(fr, ee, ev, dim3(grid), s, w, pc, lt);
-  else launch_n<128, false>(fr, ee, ev, dim3(grid), s, w, pc, lt);
+  else launch_n<128, true>(fr, ee, ev, dim3(grid), s, w, pc, lt);
   return hipGetLastError();
 }
 

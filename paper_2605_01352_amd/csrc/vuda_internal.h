@@ -209,8 +209,9 @@ __device__ __forceinline__ void raise_flag(const WorldDev& w, int32_t env, uint3
 
 // Host-side launchers (implemented next to the kernels).
 struct PhysLaunch {
-  const int32_t* work;     // env ids, LPT order
+  const int32_t* work;     // env ids, LPT order (more bodies first)
   int32_t n_work;
+  int32_t n_big;           // the listed envs of more than 64 bodies: the first ones
   int32_t max_bodies;      // over the listed envs
   int32_t parity;          // buffer read; writes 1 - parity
   int32_t nsteps;

@@ -74,6 +74,7 @@ struct WorkList {
   bool dirty = true;   // rebuild before the next use
   int32_t n = 0;
   int32_t max_bodies = 0;
+  int32_t n_big = 0;   // step: envs of more than 64 bodies, first in the list
   int32_t max_verts = 0;
   int32_t max_tris = 0;
   int32_t max_tiles = 0;

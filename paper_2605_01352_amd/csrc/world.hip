@@ -860,7 +860,7 @@ int vuda_world::get_list(int phase, int32_t lo, int32_t hi, const WorkList** out
   for (int k = 0; k < B.nfence; ++k) HIPCHK(hipEventSynchronize(B.fence[k]));
   B.nfence = 0;
   L.n = 0;
-  L.max_bodies = L.max_verts = L.max_tris = L.max_tiles = 0;
+  L.max_bodies = L.n_big = L.max_verts = L.max_tris = L.max_tiles = 0;
   std::vector<std::pair<int64_t, int32_t>> items;
   for (int32_t e = lo; e < hi; ++e) {
     if (!env_active[e]) continue;
@@ -869,6 +869,7 @@ int vuda_world::get_list(int phase, int32_t lo, int32_t hi, const WorkList** out
       if (d.n_bodies == 0) continue;
       items.push_back({(int64_t)d.n_bodies * d.n_bodies + 8 * d.n_bodies, e});
       L.max_bodies = std::max(L.max_bodies, d.n_bodies);
+      L.n_big += d.n_bodies > 64;
     } else {
       for (int32_t c = d.cam_off; c < d.cam_off + d.n_cams; ++c) {
         const CamDev& cd = cam_host[c];
@@ -964,6 +965,7 @@ int vuda_world::enqueue_physics(const WorkList& L, int parity, int nsteps, hipSt
   PhysLaunch pl;
   pl.work = L.dptr;
   pl.n_work = L.n;
+  pl.n_big = L.n_big;
   pl.max_bodies = L.max_bodies;
   pl.parity = parity;
   pl.nsteps = nsteps;

@@ -53,3 +53,21 @@ def test_steps_in_one_call_under_launch_modes(key, value):
                 b.step()
             sa, sb = a.state(), b.state()
             assert all(np.array_equal(sa[c].view(np.uint32), sb[c].view(np.uint32)) for c in sa)
+
+
+# workgroups of two waves: one env of more than 64 bodies or two smaller ones
+# (an odd one left over, none at all, an empty env among them)
+@pytest.mark.parametrize("sizes", [[128, 65, 64, 1, 33], [66], [65, 64], [3, 100, 0, 17, 70, 64, 32]])
+@pytest.mark.parametrize("options", [{}, dict(mu=0.5, edge_contacts=True)])
+@pytest.mark.parametrize("persistent", [0, 1, 3])
+def test_envs_of_one_and_two_waves_together(sizes, options, persistent):
+    import dataclasses
+
+    from tests.gpu_util import compare_step
+    scene = dataclasses.replace(sg.with_boxes(scene_of(sizes)), **options)
+    with vuda.World(scene, debug=True) as w:
+        w.set_tuning(vuda.TUNE_PHYS_PERSISTENT, persistent)
+        w.step(nsteps=60)
+        for _ in range(2):
+            r = compare_step(w, scene)
+            assert r["bitexact"], r
