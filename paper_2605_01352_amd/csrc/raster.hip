@@ -12,22 +12,24 @@
 //      crosses the near plane is cut along it into one or two pieces (the
 //      polygon in front, split as a fan), each culled the same way;
 //      survivors are compacted into lists;
-//   4. each survivor gets a setup record in the image's raster scratch
-//      (snapped vertices in edge order, depths, 1/area, primitive and flat Lambert
-//      colour) and the tiles of its box are counted with LDS atomics;
-//   5. a workgroup prefix scan of the counts places each 16x16 tile's bin; a
-//      scatter pass appends each triangle's record id to the bins of the
-//      tiles of its box, after an exact corner test of the edge functions
-//      where its box in the tile is large, flagged when the triangle covers
-//      the whole tile.
+//   4. the tiles of each survivor's box are counted with LDS atomics;
+//   5. a workgroup prefix scan of the counts places each 16x16 tile's bin;
+//      then each survivor gets a setup record in the image's raster scratch
+//      (snapped vertices in edge order, depths, 1/area, primitive and flat
+//      Lambert colour), and its pairs with the tiles of its box, a lane each,
+//      append its record id to their bins, after an exact corner test of the
+//      edge functions where its box in the tile is large, flagged when the
+//      triangle covers the whole tile.
+//   Each wave keeps the survivors it finds to itself from step 3 on.
 // raster_tile_kernel, one wave per tile and one, two or four tiles of a row
 //   per workgroup; a lane owns four horizontally adjacent pixels.  The bin is read in batches of 64
-//   records.  Small triangles (at most 64 pixels of their box in the tile)
-//   are expanded into fragments, one pixel per lane across several
+//   records.  Small triangles (at most kSmallMax pixels of their box in the
+//   tile) are expanded into fragments, one pixel per lane across several
 //   triangles, whose keys meet in an LDS z-buffer through atomic minimum;
 //   large ones are tested by every lane on its own four pixels, keeping the
-//   minimum in registers.  Edge functions are exact (integer values carried
-//   in fp64); a pixel centre is covered if every edge value is > 0, or == 0
+//   minimum in registers.  Edge functions are exact (32-bit integers for
+//   triangles of up to 120 pixels, else integer values carried in fp64); a
+//   pixel centre is covered if every edge value is > 0, or == 0
 //   on a top-left edge.  Depth is interpolated in fp32 and quantised to 24
 //   bits, and the minimum key (depth << 40 | primitive << 24 | RGB8) wins,
 //   so the result depends neither on bin order nor on which lane tests which
@@ -48,60 +50,103 @@ namespace vuda {
 namespace {
 
 constexpr int kMaxLdsTiles = 4096;  // tile table held in the setup kernel's LDS
-constexpr int kSmallMax = 64;       // box pixels in the tile of a fragment-packed triangle
+// Box pixels in the tile of a fragment-packed triangle: a window of 64
+// fragments takes 70 vector instructions (1.1 a pixel), a large triangle 110
+// to 130 a tile, so they meet near 104.  (64, when a large one took 199: at two
+// 256x256 cameras of 64 bodies 1,902 us a launch against 1,873.)
+constexpr int kSmallMax = 104;
 constexpr int kWide = 8;            // triangles over more tiles are binned by their whole wave
-constexpr int kTplBytes = (int)((sizeof(Templates) + 15) & ~(size_t)15);
-
 __host__ __device__ inline int align16(int x) { return (x + 15) & ~15; }
 
 struct SetupLayout {
   // byte offsets into the setup (or fused) kernel's dynamic LDS
-  int tpl, body, verts, vis, cvis, pmap, vmap, tiles, misc, lrec, lbin, total;
-  int nmax, vmax, tw, rec_cap, bin_cap;
+  int tpl, body, vis, cvis, own, pmap, vxy, vz, tiles, misc, lrec, lbin, total;
+  int nmax, vmax, tw, rec_cap, bin_cap, vis_cap;
 };
 
 // The regions the setup alone uses (templates, poses, survivor lists, maps)
 // come first, and at least zone0 bytes are reserved for them: the fused
 // kernel's tile pass keeps its z-buffers there once the setup is done.  Then
 // the vertex cache, the tile table and counters, and (fused kernel) rec_cap
-// compact records and bin_cap bin entries.
+// compact records and bin_cap bin entries.  threads: the workgroup's size
+// (its waves keep their survivors in lists of their own).
 __host__ __device__ inline SetupLayout setup_layout(int max_bodies, int max_verts, int max_tiles,
-                                                    int max_tris, bool near_clip, int zone0 = 0,
-                                                    int rec_cap = 0, int bin_cap = 0) {
+                                                    int max_tris, bool near_clip, int threads, int tpl_words,
+                                                    int zone0 = 0, int rec_cap = 0, int bin_cap = 0) {
   SetupLayout L;
   L.nmax = max_bodies + 1;
   L.vmax = max_verts;
   L.tw = max_tiles < kMaxLdsTiles ? max_tiles : kMaxLdsTiles;
   L.rec_cap = rec_cap;
   L.bin_cap = bin_cap;
+  L.vis_cap = (max_tris + threads - 1) / threads * 64;  // survivors of one wave
   int o = 0;
-  L.tpl = o;    o += kTplBytes;
-  L.body = o;   o += align16(4 * 20 * L.nmax);
-  L.vis = o;    o += align16(2 * max_tris);
+  L.tpl = o;    o += 4 * tpl_words;
+  L.body = o;   o += 80 * L.nmax;
+  L.vis = o;    o += align16(2 * L.vis_cap * (threads / 64));
   L.cvis = o;   o += near_clip ? align16(40 * kClipRecs) : 0;  // near-plane pieces: X[3] Y[3] z[3], primitive
+  L.own = o;    o += 4 * threads;
   L.pmap = o;   o += align16(max_tris);   // primitive -> body map of the env
-  L.vmap = o;   o += align16(L.vmax);     // vertex -> body map of the env
   if (o < zone0) o = align16(zone0);
-  L.verts = o;  o += 16 * L.vmax;         // (X, Y, z, 0) per vertex
+  L.vxy = o;    o += align16(8 * L.vmax);  // (X, Y) per vertex
+  L.vz = o;     o += align16(4 * L.vmax);  // depth per vertex
   L.tiles = o;  o += align16(4 * (3 * L.tw + 1));
-  L.misc = o;   o += 128;  // [2] record count, [3] near-plane pieces, [4] queue slot,
+  L.misc = o;   o += 192;  // [2] record count, [3] near-plane pieces, [4] queue slot,
                            // [5] a vertex behind the near plane, [6] fused: bit 0 records
-                           // and bins in LDS, bit 1 binned; [8, 24) scan totals
+                           // and bins in LDS, bit 1 binned; [8, 24) scan totals; [24, 40)
+                           // survivors of each wave
   L.lrec = o;   o += 16 * rec_cap;
   L.lbin = o;   o += align16(2 * bin_cap);
   L.total = o;
   return L;
 }
 
+// A body in LDS: five quads, so that a lane takes what it needs of one in a
+// few loads (arrays by component took 17 per vertex).
 struct BodyLDS {
-  float* p;       // [3][nmax]
-  float* R;       // [9][nmax]
-  float4* e;      // [nmax] half-extents along the body axes (x, y, z, 0); a radius thrice for a sphere
-  int32_t* type;  // [nmax]
-  int32_t* vb;    // [nmax] vertex base (env-local)
-  int32_t* pb;    // [nmax] primitive base
-  int32_t* alb;   // [nmax]
+  float4* R;     // [3][nmax] rows of R(q), each with that component of the position
+  float4* e;     // [nmax] half-extents along the body axes (x, y, z, 0); a radius thrice for a sphere
+  int4* id;      // [nmax] vertex base and primitive base (env-local), albedo, type
 };
+
+// The mesh templates in LDS and the descriptor's constants.
+struct Tpl {
+  const uint32_t* w;
+  int cv, gv, sn, cn, sf, cf, gf;  // word offsets (Templates::at_*)
+  float near_w, guard, ground_albedo, ground_uv_scale, light[3];
+  __device__ __forceinline__ float3 vec(int at, int i) const {
+    const float* p = (const float*)w + at + 3 * i;
+    return make_float3(p[0], p[1], p[2]);
+  }
+  __device__ __forceinline__ float3 vertex(bool cube, int i) const { return vec(cube ? cv : kTplSphereV, i); }
+  __device__ __forceinline__ float3 normal(bool cube, int i) const { return vec(cube ? cn : sn, i); }
+  __device__ __forceinline__ float3 albedo(int i) const { return vec(0, i); }
+};
+
+__device__ __forceinline__ Tpl tpl_view(const Templates* g, const uint32_t* lds) {
+  Tpl t;
+  t.w = lds;
+  t.cv = uniform_ld(&g->at_cube_v);
+  t.gv = uniform_ld(&g->at_ground_v);
+  t.sn = uniform_ld(&g->at_sphere_n);
+  t.cn = uniform_ld(&g->at_cube_n);
+  t.sf = uniform_ld(&g->at_sphere_f);
+  t.cf = uniform_ld(&g->at_cube_f);
+  t.gf = uniform_ld(&g->at_ground_f);
+  t.near_w = uniform_ld(&g->near_w);
+  t.guard = uniform_ld(&g->guard);
+  t.ground_albedo = uniform_ld(&g->ground_albedo);
+  t.ground_uv_scale = uniform_ld(&g->ground_uv_scale);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) t.light[k] = uniform_ld(&g->light[k]);
+  return t;
+}
+
+// v turned by the rows r0, r1, r2
+__device__ __forceinline__ float3 turned(float4 r0, float4 r1, float4 r2, float3 v) {
+  return make_float3((r0.x * v.x + r0.y * v.y) + r0.z * v.z, (r1.x * v.x + r1.y * v.y) + r1.z * v.z,
+                     (r2.x * v.x + r2.y * v.y) + r2.z * v.z);
+}
 
 // Rotation matrix of a unit quaternion, row-major, element k at m[k * stride]
 __device__ __forceinline__ void quat_rot(float w, float x, float y, float z, float* m, int stride) {
@@ -131,31 +176,33 @@ struct Tri {
 
 // vertex indices (env-local) of primitive `prim` whose body (from the map) is
 // b; *body = -1 for the ground
-__device__ __forceinline__ void prim_vertices(const Templates* T, const BodyLDS& B, int b, int prim,
-                                              int* body, int vid[3]) {
-  if (b == kGroundBody) {
-    *body = -1;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) vid[k] = T->ground_f[prim][k];
-    return;
+__device__ __forceinline__ void prim_vertices(const Tpl& T, const BodyLDS& B, int b, int prim, int* body, int vid[3]) {
+  int at = T.gf + prim, vb = 0;
+  *body = -1;
+  if (b != kGroundBody) {
+    const int4 id = B.id[b];
+    at = (id.w ? T.cf : T.sf) + (prim - id.y);
+    vb = id.x;
+    *body = b;
   }
-  const int f = prim - B.pb[b];
-  *body = b;
-  const uint8_t* fi = B.type[b] ? T->cube_f[f] : T->sphere_f[f];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) vid[k] = B.vb[b] + fi[k];
+  const uint32_t f = T.w[at];
+  vid[0] = vb + (int)(f & 0xFFu);
+  vid[1] = vb + (int)((f >> 8) & 0xFFu);
+  vid[2] = vb + (int)(f >> 16);
 }
 
-__device__ __forceinline__ Tri load_tri(const int4* V, const int vid[3]) {
+// Snapped corners in edge order (vertices 0, 2, 1 of the face) from the vertex
+// cache; ok: all in front of the near plane and inside the guard band.
+__device__ __forceinline__ Tri load_tri(const int2* V, const int vid[3]) {
   Tri t;
   const int ord[3] = {0, 2, 1};
   t.ok = true;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const int4 q = V[vid[ord[k]]];
+    const int2 q = V[vid[ord[k]]];
     t.X[k] = q.x;
     t.Y[k] = q.y;
-    t.z[k] = __int_as_float(q.z);
+    t.z[k] = 0.0f;
     if (t.X[k] <= kBehind) t.ok = false;  // kInvalid or kBehind
   }
   return t;
@@ -181,19 +228,19 @@ __device__ __forceinline__ bool tri_pixels(const int32_t* X, const int32_t* Y, i
 
 // Viewport transform and 24.8 snap of clip coordinates c: X = kBehind when
 // near_test and c.w < near, kInvalid outside the guard band.
-__device__ __forceinline__ void snap_clip(float4 c, float fW, float fH, const Templates* T, bool near_test,
+__device__ __forceinline__ void snap_clip(float4 c, float fW, float fH, const Tpl& T, bool near_test,
                                           int32_t* X, int32_t* Y, float* z) {
   *X = kInvalid;
   *Y = kInvalid;
   *z = 0.0f;
-  if (near_test && c.w < T->near_w) {
+  if (near_test && c.w < T.near_w) {
     *X = *Y = kBehind;
     return;
   }
   const float nx = c.x / c.w, ny = c.y / c.w, nz = c.z / c.w;
   const float px = (nx * 0.5f + 0.5f) * fW;
   const float py = (0.5f - ny * 0.5f) * fH;
-  if (!(fabsf(px) > T->guard || fabsf(py) > T->guard)) {
+  if (!(fabsf(px) > T.guard || fabsf(py) > T.guard)) {
     *X = (int32_t)rintf(px * 256.0f);
     *Y = (int32_t)rintf(py * 256.0f);
     *z = nz;
@@ -214,8 +261,7 @@ __device__ __forceinline__ float4 near_cut(float4 a, float4 b, float near_w) {
 // order, split as a fan from its first vertex; the piece in edge order.
 // Returns false if there is no piece s; t->ok is false if a cut point falls
 // outside the guard band.
-__device__ __forceinline__ bool near_piece(const float4 c[3], int s, float fW, float fH, const Templates* T,
-                                           Tri* t) {
+__device__ __forceinline__ bool near_piece(const float4 c[3], int s, float fW, float fH, const Tpl& T, Tri* t) {
   // the polygon's candidate points in cycle order: vertex k (if in front),
   // then the cut of edge k -> k+1 (if it crosses); selected with static
   // indices only, so that everything stays in registers
@@ -224,11 +270,11 @@ __device__ __forceinline__ bool near_piece(const float4 c[3], int s, float fW, f
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const int k1 = k == 2 ? 0 : k + 1;
-    const bool ik = !(c[k].w < T->near_w), ik1 = !(c[k1].w < T->near_w);
+    const bool ik = !(c[k].w < T.near_w), ik1 = !(c[k1].w < T.near_w);
     val[2 * k] = c[k];
     has[2 * k] = ik;
     cut[2 * k] = false;
-    val[2 * k + 1] = ik ? near_cut(c[k], c[k1], T->near_w) : near_cut(c[k1], c[k], T->near_w);
+    val[2 * k + 1] = ik ? near_cut(c[k], c[k1], T.near_w) : near_cut(c[k1], c[k], T.near_w);
     has[2 * k + 1] = ik != ik1;
     cut[2 * k + 1] = true;
   }
@@ -264,51 +310,43 @@ __device__ __forceinline__ bool top_left(int32_t dx, int32_t dy) {
 // Classify the pixel centres of the block [x0..x1] x [y0..y1] against the
 // edges of a snapped triangle (edge order): 0 none can be covered, 1 some may
 // be, 2 all are.  Edge values are affine in the pixel centre, so their
-// extremes over the block are at its corners; all values are exact in fp64.
-__device__ __forceinline__ int tile_class(const int32_t* X, const int32_t* Y, int x0, int x1, int y0,
-                                          int y1) {
-  const double Px = (double)(256 * x0 + 128), Py = (double)(256 * y0 + 128);
-  const double wx = (double)(256 * (x1 - x0)), wy = (double)(256 * (y1 - y0));
-  bool all = true;
+// extremes over the block are at its corners.  V: the type that holds them
+// exactly: int32_t for a narrow triangle and a block inside its box, else
+// double.
+template <class V>
+__device__ __forceinline__ int tile_class(const int32_t* X, const int32_t* Y, int x0, int x1, int y0, int y1) {
+  const int32_t Px = 256 * x0 + 128, Py = 256 * y0 + 128;
+  const V wx = (V)(256 * (x1 - x0)), wy = (V)(256 * (y1 - y0));
+  bool all = true, none = false;
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     const int a = (e + 1) % 3, b = (e + 2) % 3;
     const int32_t dx = X[b] - X[a], dy = Y[b] - Y[a];
-    const double E = (double)dx * (Py - (double)Y[a]) - (double)dy * (Px - (double)X[a]);
-    const double ax = -(double)dy * wx, ay = (double)dx * wy;
-    const double emin = E + fmin(0.0, ax) + fmin(0.0, ay);
-    const double emax = E + fmax(0.0, ax) + fmax(0.0, ay);
-    const bool tl = top_left(dx, dy);
-    if (emax < 0.0 || (emax == 0.0 && !tl)) return 0;
-    if (!(emin > 0.0 || (emin == 0.0 && tl))) all = false;
+    const V E = (V)dx * (V)(Py - Y[a]) - (V)dy * (V)(Px - X[a]);
+    const V ax = -(V)dy * wx, ay = (V)dx * wy, zero = 0;
+    const V emin = E + (ax < zero ? ax : zero) + (ay < zero ? ay : zero);
+    const V emax = E + (ax < zero ? zero : ax) + (ay < zero ? zero : ay);
+    const V thr = top_left(dx, dy) ? 0 : 1;  // covered from this value on
+    none |= emax < thr;
+    all &= emin >= thr;
   }
-  return all ? 2 : 1;
+  return none ? 0 : (all ? 2 : 1);
 }
 
 // Flat Lambert colour of face `face` of body `body` (-1: ground), RGB8 packed.
-__device__ __forceinline__ uint32_t face_color(const Templates* tp, const BodyLDS& B, int nmax,
-                                               int body, int face) {
-  float nx, ny, nz, al[3];
-  if (body < 0) {
-    nx = 0.0f; ny = 0.0f; nz = 1.0f;
-    al[0] = al[1] = al[2] = tp->ground_albedo;
-  } else {
-    const float* nf = B.type[body] ? tp->cube_n[face] : tp->sphere_n[face];
-    const float* R = B.R + body;
-    const int S = nmax;
-    nx = (R[0] * nf[0] + R[S] * nf[1]) + R[2 * S] * nf[2];
-    ny = (R[3 * S] * nf[0] + R[4 * S] * nf[1]) + R[5 * S] * nf[2];
-    nz = (R[6 * S] * nf[0] + R[7 * S] * nf[1]) + R[8 * S] * nf[2];
-    const int ai = B.alb[body];
-    al[0] = tp->palette[ai][0];
-    al[1] = tp->palette[ai][1];
-    al[2] = tp->palette[ai][2];
+__device__ __forceinline__ uint32_t face_color(const Tpl& T, const BodyLDS& B, int nmax, int body, int face) {
+  float3 n = make_float3(0.0f, 0.0f, 1.0f), al = make_float3(T.ground_albedo, T.ground_albedo, T.ground_albedo);
+  if (body >= 0) {
+    const int4 id = B.id[body];
+    n = turned(B.R[body], B.R[nmax + body], B.R[2 * nmax + body], T.normal(id.w != 0, face));
+    al = T.albedo(id.z);
   }
-  const float l = fmaxf(0.0f, (nx * tp->light[0] + ny * tp->light[1]) + nz * tp->light[2]);
+  const float l = fmaxf(0.0f, (n.x * T.light[0] + n.y * T.light[1]) + n.z * T.light[2]);
+  const float a[3] = {al.x, al.y, al.z};
   uint32_t rgb = 0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const float col = al[c] * (0.2f + 0.8f * l);
+    const float col = a[c] * (0.2f + 0.8f * l);
     rgb |= (uint32_t)fminf(255.0f, rintf(col * 255.0f)) << (8 * c);
   }
   return rgb;
@@ -326,14 +364,16 @@ __device__ __forceinline__ int wave_incl_add(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return x;
 }
-__device__ __forceinline__ int wave_incl_max(int x) {
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
-  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
-  return x;
+// (unsigned: 0 is then the maximum's identity, and each step one instruction)
+__device__ __forceinline__ int wave_incl_max(int v) {
+  uint32_t x = (uint32_t)v;
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+  return (int)x;
 }
 
 // Exclusive prefix sum over the workgroup of one value per thread.
@@ -397,8 +437,7 @@ __device__ __forceinline__ int rec_flags(const Tri& t) {
 // every tile it is binned to needs, so that the tile kernel recomputes none
 // of it.  Word 2 of the last quad holds the flags.
 __device__ __forceinline__ void store_rec(int4* recs, int r, const Tri& t, int prim, float invA,
-                                          uint32_t rgb, int x0, int x1, int y0, int y1) {
-  const int flags = rec_flags(t);
+                                          uint32_t rgb, int flags, int x0, int x1, int y0, int y1) {
   int4* p = recs + 4 * r;
   p[0] = make_int4(t.X[0], t.Y[0], t.X[1], t.Y[1]);
   p[1] = make_int4(t.X[2], t.Y[2], prim, __float_as_int(t.z[0]));
@@ -406,52 +445,29 @@ __device__ __forceinline__ void store_rec(int4* recs, int r, const Tri& t, int p
   p[3] = make_int4(x0 | (x1 << 16), y0 | (y1 << 16), flags, 0);
 }
 
-// Append record r to the bin of tile (tx, ty) unless its edges miss the tile;
-// flag the entry when the triangle covers every pixel of the tile.  Only a
-// box of more than kSmallMax pixels in the tile is classified (the tile
-// kernel rasterizes it pixel by pixel over the whole tile, where the flag and
-// the rejection pay); a smaller one is expanded into its box's pixels there
-// anyway.
-__device__ __forceinline__ void bin_tile(const Tri& t, int r, int tx, int ty, int x0, int x1, int y0,
-                                         int y1, bool classify, int Wd, int Ht, int ntx, int TS,
-                                         const int32_t* toff, int32_t* tfill, uint16_t* bins) {
-  const int bx0 = max(x0, tx * TS), bx1 = min(x1, tx * TS + TS - 1);
-  const int by0 = max(y0, ty * TS), by1 = min(y1, ty * TS + TS - 1);
-  const bool large = (bx1 - bx0 + 1) * (by1 - by0 + 1) > kSmallMax;
-  const int cls = (classify && large) ? tile_class(t.X, t.Y, bx0, bx1, by0, by1) : 1;
-  if (cls == 0) return;
-  const bool whole = bx0 == tx * TS && by0 == ty * TS &&
-                     bx1 == min(Wd - 1, tx * TS + TS - 1) &&
-                     by1 == min(Ht - 1, ty * TS + TS - 1);
-  const int ti = ty * ntx + tx;
-  bins[toff[ti] + atomicAdd(&tfill[ti], 1)] = (uint16_t)(r | ((cls == 2 && whole) ? 0x8000 : 0));
-}
-
 // ---------------------------------------------------------------------------
 // setup kernel
 // ---------------------------------------------------------------------------
 
-// Clip coordinates of env-local vertex vi: the body's pose applied to the
-// scaled template vertex (the ground's vertices as they are), then the
-// camera's view-projection (row dot products summed left to right, then the
-// translation).
-__device__ __forceinline__ float4 vertex_clip(const Templates* T, const BodyLDS& B, int S, const uint8_t* gvmap,
-                                              int vi, const float* vp) {
+// Clip coordinates of env-local vertex vi of body b (from the map): the
+// body's pose applied to the scaled template vertex (the ground's vertices as
+// they are), then the camera's view-projection (row dot products summed left
+// to right, then the translation).
+__device__ __forceinline__ float4 vertex_clip(const Tpl& T, const BodyLDS& B, int S, int b, int vi, const float* vp) {
   float wx, wy, wz;
-  const int b = gvmap[vi];
   if (b == kGroundBody) {
-    wx = T->ground_v[vi][0];
-    wy = T->ground_v[vi][1];
-    wz = T->ground_v[vi][2];
+    const float3 g = T.vec(T.gv, vi);
+    wx = g.x;
+    wy = g.y;
+    wz = g.z;
   } else {
-    const int lv = vi - B.vb[b];
-    const float* tv = B.type[b] ? T->cube_v[lv] : T->sphere_v[lv];
-    const float4 e = B.e[b];
-    const float sx = e.x * tv[0], sy = e.y * tv[1], sz = e.z * tv[2];
-    const float* R = B.R + b;
-    wx = B.p[b] + ((R[0] * sx + R[S] * sy) + R[2 * S] * sz);
-    wy = B.p[S + b] + ((R[3 * S] * sx + R[4 * S] * sy) + R[5 * S] * sz);
-    wz = B.p[2 * S + b] + ((R[6 * S] * sx + R[7 * S] * sy) + R[8 * S] * sz);
+    const int4 id = B.id[b];
+    const float3 tv = T.vertex(id.w != 0, vi - id.x);
+    const float4 e = B.e[b], r0 = B.R[b], r1 = B.R[S + b], r2 = B.R[2 * S + b];
+    const float3 t = turned(r0, r1, r2, make_float3(e.x * tv.x, e.y * tv.y, e.z * tv.z));
+    wx = r0.w + t.x;
+    wy = r1.w + t.y;
+    wz = r2.w + t.z;
   }
   return make_float4(((vp[0] * wx + vp[1] * wy) + vp[2] * wz) + vp[3], ((vp[4] * wx + vp[5] * wy) + vp[6] * wz) + vp[7],
                      ((vp[8] * wx + vp[9] * wy) + vp[10] * wz) + vp[11],
@@ -463,40 +479,27 @@ __device__ __forceinline__ float4 vertex_clip(const Templates* T, const BodyLDS&
 // and the reciprocal clip w of each vertex in edge order (face vertices 0, 2,
 // 1), and the albedo.  A sphere's vertex normal is its unit template vertex
 // turned by R, a cube's or box's the face normal, the ground's +z.
-__device__ __forceinline__ void store_attr(float4* ga, float4* gt, int r, const Templates* T, const BodyLDS& B,
-                                           int S, const uint8_t* gvmap, int body, int face, const int vid[3],
-                                           const float* vp) {
+__device__ __forceinline__ void store_attr(float4* ga, float4* gt, int r, const Tpl& T, const BodyLDS& B,
+                                           int S, int body, int face, const int vid[3], const float* vp) {
   const int ord[3] = {0, 2, 1};
-  float n[3][3], iw[3], al[3];
+  float iw[3];
+  float3 n[3], al = make_float3(T.ground_albedo, T.ground_albedo, T.ground_albedo);
+  const int4 id = B.id[body < 0 ? 0 : body];
+  const bool cube = id.w != 0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const int v = vid[ord[k]];
-    iw[k] = 1.0f / vertex_clip(T, B, S, gvmap, v, vp).w;
-    if (body < 0) {
-      n[k][0] = 0.0f;
-      n[k][1] = 0.0f;
-      n[k][2] = 1.0f;
-    } else {
-      const float* nb = B.type[body] ? T->cube_n[face] : T->sphere_v[v - B.vb[body]];
-      const float* R = B.R + body;
-      n[k][0] = (R[0] * nb[0] + R[S] * nb[1]) + R[2 * S] * nb[2];
-      n[k][1] = (R[3 * S] * nb[0] + R[4 * S] * nb[1]) + R[5 * S] * nb[2];
-      n[k][2] = (R[6 * S] * nb[0] + R[7 * S] * nb[1]) + R[8 * S] * nb[2];
-    }
+    iw[k] = 1.0f / vertex_clip(T, B, S, body < 0 ? (int)kGroundBody : body, v, vp).w;
+    n[k] = make_float3(0.0f, 0.0f, 1.0f);
+    if (body >= 0)
+      n[k] = turned(B.R[body], B.R[S + body], B.R[2 * S + body], cube ? T.normal(true, face) : T.vertex(false, v - id.x));
   }
-  if (body < 0) {
-    al[0] = al[1] = al[2] = T->ground_albedo;
-  } else {
-    const int ai = B.alb[body];
-    al[0] = T->palette[ai][0];
-    al[1] = T->palette[ai][1];
-    al[2] = T->palette[ai][2];
-  }
+  if (body >= 0) al = T.albedo(id.z);
   float4* p = ga + 4 * r;
-  p[0] = make_float4(n[0][0], n[0][1], n[0][2], n[1][0]);
-  p[1] = make_float4(n[1][1], n[1][2], n[2][0], n[2][1]);
-  p[2] = make_float4(n[2][2], iw[0], iw[1], iw[2]);
-  p[3] = make_float4(al[0], al[1], al[2], 0.0f);
+  p[0] = make_float4(n[0].x, n[0].y, n[0].z, n[1].x);
+  p[1] = make_float4(n[1].y, n[1].z, n[2].x, n[2].y);
+  p[2] = make_float4(n[2].z, iw[0], iw[1], iw[2]);
+  p[3] = make_float4(al.x, al.y, al.z, 0.0f);
   if (!gt) return;
   // textured worlds: the texture coordinates of the vertices in edge order
   // (the ground: world x, y scaled; a cube or box face: the unit square over
@@ -507,20 +510,19 @@ __device__ __forceinline__ void store_attr(float4* ga, float4* gt, int r, const 
     textured = 1.0f;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const int v = vid[ord[k]];
-      uv[k][0] = T->ground_v[v][0] * T->ground_uv_scale;
-      uv[k][1] = T->ground_v[v][1] * T->ground_uv_scale;
+      const float3 g = T.vec(T.gv, vid[ord[k]]);
+      uv[k][0] = g.x * T.ground_uv_scale;
+      uv[k][1] = g.y * T.ground_uv_scale;
     }
-  } else if (B.type[body]) {
+  } else if (cube) {
     textured = 1.0f;
-    const float* fn = T->cube_n[face];
-    const int a = fabsf(fn[0]) > 0.5f ? 0 : (fabsf(fn[1]) > 0.5f ? 1 : 2);
-    const int t0 = a == 0 ? 1 : 0, t1 = a == 2 ? 1 : 2;
+    const float3 fn = T.normal(true, face);
+    const int a = fabsf(fn.x) > 0.5f ? 0 : (fabsf(fn.y) > 0.5f ? 1 : 2);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const float* tv = T->cube_v[vid[ord[k]] - B.vb[body]];
-      uv[k][0] = (tv[t0] + 1.0f) * 0.5f;
-      uv[k][1] = (tv[t1] + 1.0f) * 0.5f;
+      const float3 tv = T.vertex(true, vid[ord[k]] - id.x);
+      uv[k][0] = ((a == 0 ? tv.y : tv.x) + 1.0f) * 0.5f;
+      uv[k][1] = ((a == 2 ? tv.y : tv.z) + 1.0f) * 0.5f;
     }
   }
   float4* q = gt + 2 * r;
@@ -540,16 +542,17 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   const int tid = threadIdx.x;
   const int nthr = blockDim.x;
   const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
   const CamDev cam = uniform_copy(W.cams + cam_id);
   const EnvDev ed = uniform_copy(W.envs + cam.env);
   const int n = ed.n_bodies;
   const int ntris = ed.n_tris;
   const int64_t cap = W.cap_bodies;
   const float* st = W.state[L.parity];
-  // the env's primitive and vertex maps (16-byte aligned and padded), read
-  // once into LDS: every phase below looks them up per triangle or vertex
+  // the env's primitive map (16-byte aligned and padded), read once into LDS:
+  // the phases below look it up per triangle
   const uint8_t* gpmap = (const uint8_t*)(lds + Lo.pmap);
-  const uint8_t* gvmap = (const uint8_t*)(lds + Lo.vmap);
+  const uint8_t* gvmap = W.vert_body + ed.vert_map;
   const int Wd = cam.w, Ht = cam.h;
   const int tsh = L.tile_shift, TS = 1 << tsh;  // tile edge in pixels
   const int ntx = (Wd + TS - 1) >> tsh;
@@ -558,57 +561,51 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   // for the smallest tiles)
   unsigned char* rs = W.rscratch + cam.rs_off + (int64_t)L.parity * cam.rs_total;  // one scratch per state buffer
   int32_t* hdr = (int32_t*)rs;
-  int32_t* ttab = (int32_t*)(rs + 64);
+  int2* ttab = (int2*)(rs + 64);
   int4* grec = (int4*)(rs + cam.rs_recs);
   uint16_t* bins = (uint16_t*)(rs + cam.rs_bins);
   const int rs_bin_cap = kBinsPerTri * (cam.n_tris + kClipRecs);
   const int bin_cap = (L.bin_limit > 0 && L.bin_limit < rs_bin_cap) ? L.bin_limit : rs_bin_cap;
 
-  Templates* T = (Templates*)(lds + Lo.tpl);
+  const int S = Lo.nmax;
   BodyLDS B;
-  float* bf = (float*)(lds + Lo.body);
-  B.p = bf;
-  B.R = bf + 3 * Lo.nmax;
-  B.e = (float4*)(bf + 12 * Lo.nmax);
-  B.type = (int32_t*)(bf + 16 * Lo.nmax);
-  B.vb = (int32_t*)(bf + 17 * Lo.nmax);
-  B.pb = (int32_t*)(bf + 18 * Lo.nmax);
-  B.alb = (int32_t*)(bf + 19 * Lo.nmax);
-  int4* V = (int4*)(lds + Lo.verts);
-  uint16_t* vis = (uint16_t*)(lds + Lo.vis);
+  B.R = (float4*)(lds + Lo.body);
+  B.e = B.R + 3 * S;
+  B.id = (int4*)(B.R + 4 * S);
+  int2* V = (int2*)(lds + Lo.vxy);
+  float* Vz = (float*)(lds + Lo.vz);
+  uint16_t* vis = (uint16_t*)(lds + Lo.vis) + wave * Lo.vis_cap;  // this wave's survivors
   int32_t* cvis = (int32_t*)(lds + Lo.cvis);  // 10 words per piece
+  int32_t* own = (int32_t*)(lds + Lo.own) + 64 * wave;  // this wave's owner marks
   int32_t* tcount = (int32_t*)(lds + Lo.tiles);
   int32_t* toff = tcount + Lo.tw;
-  int32_t* tfill = toff + Lo.tw + 1;
+  int32_t* tend = toff + Lo.tw + 1;
   int32_t* misc = (int32_t*)(lds + Lo.misc);
+  const Tpl T = tpl_view(W.tpl, (const uint32_t*)(lds + Lo.tpl));
 
-  // 1. templates, maps and bodies
+  // 1. templates, primitive map and bodies
+  for (int b = tid; b < n; b += nthr) {
+    const int g = ed.body_off + b;
+    float R[9];
+    quat_rot(st[QW * cap + g], st[QX * cap + g], st[QY * cap + g], st[QZ * cap + g], R, 1);
+    B.R[b] = make_float4(R[0], R[1], R[2], st[PX * cap + g]);
+    B.R[S + b] = make_float4(R[3], R[4], R[5], st[PY * cap + g]);
+    B.R[2 * S + b] = make_float4(R[6], R[7], R[8], st[PZ * cap + g]);
+    const float* bx = W.box + 6 * (int64_t)g;
+    B.e[b] = make_float4(bx[0], bx[1], bx[2], 0.0f);
+    B.id[b] = make_int4(W.vert_base[g], W.prim_base[g], W.albedo[g], W.type[g]);
+  }
   {
-    const int4* src = (const int4*)W.tpl;
-    int4* dst = (int4*)T;
-    for (int i = tid; i < kTplBytes / 16; i += nthr) dst[i] = src[i];
+    const int4* src = (const int4*)W.tpl->data;
+    int4* dst = (int4*)(lds + Lo.tpl);
+    for (int i = tid; i < L.tpl_words / 4; i += nthr) dst[i] = src[i];
     const int4* ps = (const int4*)(W.prim_body + ed.prim_map);
     int4* pd = (int4*)(lds + Lo.pmap);
     for (int i = tid; i < (ntris + 15) / 16; i += nthr) pd[i] = ps[i];
-    const int4* vs = (const int4*)(W.vert_body + ed.vert_map);
-    int4* vd = (int4*)(lds + Lo.vmap);
-    for (int i = tid; i < (ed.n_verts + 15) / 16; i += nthr) vd[i] = vs[i];
   }
-  for (int b = tid; b < n; b += nthr) {
-    const int g = ed.body_off + b;
-    B.p[b] = st[PX * cap + g];
-    B.p[Lo.nmax + b] = st[PY * cap + g];
-    B.p[2 * Lo.nmax + b] = st[PZ * cap + g];
-    quat_rot(st[QW * cap + g], st[QX * cap + g], st[QY * cap + g], st[QZ * cap + g], B.R + b, Lo.nmax);
-    const float* bx = W.box + 6 * (int64_t)g;
-    B.e[b] = make_float4(bx[0], bx[1], bx[2], 0.0f);
-    B.type[b] = W.type[g];
-    B.vb[b] = W.vert_base[g];
-    B.pb[b] = W.prim_base[g];
-    B.alb[b] = W.albedo[g];
-  }
+  int body_next = gvmap[min(tid, ed.n_verts - 1)];
   const bool tiled = ntiles <= Lo.tw;
-  if (tid == 0) misc[2] = misc[3] = misc[5] = 0;
+  if (tid == 0) misc[3] = misc[5] = 0;
   if (tiled)
     for (int t = tid; t < ntiles; t += nthr) tcount[t] = 0;
   __syncthreads();
@@ -616,25 +613,30 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   // 2. vertices
   const float* vp = cam.vp;
   const float fW = (float)Wd, fH = (float)Ht;
+  // (the body of a lane's next vertex is on its way while this one is transformed)
   for (int vi = tid; vi < ed.n_verts; vi += nthr) {
+    const int b = body_next;
+    body_next = gvmap[min(vi + nthr, ed.n_verts - 1)];
     int32_t X, Y;
     float z;
-    snap_clip(vertex_clip(T, B, Lo.nmax, gvmap, vi, vp), fW, fH, T, true, &X, &Y, &z);
+    snap_clip(vertex_clip(T, B, S, b, vi, vp), fW, fH, T, true, &X, &Y, &z);
     if (CLIP && X == kBehind) misc[5] = 1;  // some vertex of the image is behind the near plane
-    V[vi] = make_int4(X, Y, __float_as_int(z), 0);
+    V[vi] = make_int2(X, Y);
+    Vz[vi] = z;
   }
   __syncthreads();
 
   // 3. visibility.  A triangle survives if every vertex is in front of the
   // near plane and inside the guard band, its integer area is > 0 (front
-  // facing, not degenerate) and its box holds a pixel centre.  Survivors are
-  // compacted into vis (a wave ballot and one atomic per wave), so that the
-  // costlier steps below run on full waves.  A triangle that crosses the
-  // near plane (and has no vertex in front outside the guard band) is cut
+  // facing, not degenerate) and its box holds a pixel centre.  Each wave
+  // compacts its survivors into a list of its own (a ballot, no atomic), so
+  // that the costlier steps below run on full waves.  A triangle that crosses
+  // the near plane (and has no vertex in front outside the guard band) is cut
   // along it: its surviving pieces go to cvis, and become the records after
   // the whole triangles.
   // (two versions of the pass: images with no vertex behind the near plane,
   // nearly all of them, run the one without the cut)
+  int nmine = 0;  // this wave's survivors
   const auto visibility = [&](auto cut_tag) {
   for (int base = 0; base < ntris; base += nthr) {
     const int pr = base + tid;
@@ -655,7 +657,7 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
       if (behind > 0 && behind < 3 && outside == 0) {
         float4 c[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) c[k] = vertex_clip(T, B, Lo.nmax, gvmap, vid[k], vp);
+        for (int k = 0; k < 3; ++k) c[k] = vertex_clip(T, B, S, body < 0 ? (int)kGroundBody : body, vid[k], vp);
         for (int sp = 0; sp < 2; ++sp) {
           Tri q;
           q.ok = false;
@@ -680,11 +682,9 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
       }
     }
     const uint64_t m = __ballot(keep);
-    int wbase = 0;
-    if (lane == 0 && m) wbase = atomicAdd(&misc[2], __popcll(m));
-    wbase = __builtin_amdgcn_readfirstlane(wbase);
     const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-    if (keep) vis[wbase + below] = (uint16_t)pr;
+    if (keep) vis[nmine + below] = (uint16_t)pr;
+    nmine += __popcll(m);
   }
   };
   if constexpr (CLIP) {
@@ -693,23 +693,26 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   } else {
     visibility(std::false_type{});
   }
-  __syncthreads();
-  const int nwhole = misc[2];
-  const int npieces = min(misc[3], kClipRecs);
-  const int nrec = nwhole + npieces;
-  if (tid == 0 && misc[3] > kClipRecs) raise_flag(W, cam.env, kFlagClipOverflow);
-  // record r: whole triangle vis[r], or piece cvis[r - nwhole]; vid its
-  // face's vertices in face order
-  const auto record_tri = [&](int r, int* pr, int* body, int vid[3], Tri* t) {
-    if (!CLIP || r < nwhole) {
-      *pr = vis[r];
-      prim_vertices(T, B, gpmap[*pr], *pr, body, vid);
+  if (lane == 0) misc[24 + wave] = nmine;
+  int npieces = 0;
+  if constexpr (CLIP) {
+    // the pieces are the first wave's, after its whole triangles
+    __syncthreads();
+    npieces = min(misc[3], kClipRecs);
+    if (tid == 0 && misc[3] > kClipRecs) raise_flag(W, cam.env, kFlagClipOverflow);
+  }
+  const int mine = nmine + (wave == 0 ? npieces : 0);  // records this wave makes
+  // the wave's record i: whole triangle vis[i], or piece cvis[i - nmine]; vid
+  // its face's vertices in face order
+  const auto record_tri = [&](int i, int* pr, int* body, int vid[3], Tri* t) {
+    const int32_t* o = cvis + 10 * (i - nmine);
+    const bool whole = !CLIP || i < nmine;
+    *pr = whole ? (int)vis[i] : o[9];
+    prim_vertices(T, B, gpmap[*pr], *pr, body, vid);
+    if (whole) {
       *t = load_tri(V, vid);
       return;
     }
-    const int32_t* o = cvis + 10 * (r - nwhole);
-    *pr = o[9];
-    prim_vertices(T, B, gpmap[*pr], *pr, body, vid);
     t->ok = true;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -718,43 +721,59 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
       t->z[k] = __int_as_float(o[6 + k]);
     }
   };
+  // the tiles [tx0, tx0 + nx) x [ty0, ty0 + ny) of a triangle's box
+  struct Box {
+    int x0, x1, y0, y1, tx0, ty0, nx, ny;
+  };
+  const auto box_of = [&](const Tri& t) -> Box {
+    Box q;
+    tri_pixels(t.X, t.Y, Wd, Ht, &q.x0, &q.x1, &q.y0, &q.y1);
+    q.tx0 = q.x0 >> tsh;
+    q.ty0 = q.y0 >> tsh;
+    q.nx = (q.x1 >> tsh) - q.tx0 + 1;
+    q.ny = (q.y1 >> tsh) - q.ty0 + 1;
+    return q;
+  };
 
   // 4. tile counts, one surviving triangle per lane.  A triangle whose box
   // spans more than kWide tiles is counted by its whole wave, one tile per
   // lane, so that one lane never walks a long tile list alone.
   if (tiled) {
-    for (int base = 0; base < nrec; base += nthr) {
-      const int r = base + tid;
-      int tx0 = 0, ty0 = 0, nx = 0, ny = 0;
-      if (r < nrec) {
+    for (int base = 0; base < mine; base += 64) {
+      const int i = base + lane;
+      Box q{};
+      if (i < mine) {
         int pr, body, vid[3];
         Tri t;
-        record_tri(r, &pr, &body, vid, &t);
-        int x0, x1, y0, y1;
-        tri_pixels(t.X, t.Y, Wd, Ht, &x0, &x1, &y0, &y1);
-        tx0 = x0 >> tsh;
-        ty0 = y0 >> tsh;
-        nx = (x1 >> tsh) - tx0 + 1;
-        ny = (y1 >> tsh) - ty0 + 1;
+        record_tri(i, &pr, &body, vid, &t);
+        q = box_of(t);
       }
-      const bool wide = nx * ny > kWide;
+      const bool wide = q.nx * q.ny > kWide;
       if (!wide)
-        for (int qy = 0; qy < ny; ++qy)
-          for (int qx = 0; qx < nx; ++qx) atomicAdd(&tcount[(ty0 + qy) * ntx + tx0 + qx], 1);
+        for (int qy = 0; qy < q.ny; ++qy)
+          for (int qx = 0; qx < q.nx; ++qx) atomicAdd(&tcount[(q.ty0 + qy) * ntx + q.tx0 + qx], 1);
       uint64_t m = __ballot(wide);
       while (m) {
         const int j = __ffsll((unsigned long long)m) - 1;
         m &= m - 1ull;
-        const int jx0 = __shfl(tx0, j, 64), jy0 = __shfl(ty0, j, 64);
-        const int jnx = __shfl(nx, j, 64), jn = jnx * __shfl(ny, j, 64);
-        for (int q = lane; q < jn; q += 64) {
-          const int qy = q / jnx;
-          atomicAdd(&tcount[(jy0 + qy) * ntx + jx0 + (q - qy * jnx)], 1);
+        const int jx0 = __builtin_amdgcn_readlane(q.tx0, j), jy0 = __builtin_amdgcn_readlane(q.ty0, j);
+        const int jnx = __builtin_amdgcn_readlane(q.nx, j), jn = jnx * __builtin_amdgcn_readlane(q.ny, j);
+        for (int k = lane; k < jn; k += 64) {
+          const int qy = k / jnx;
+          atomicAdd(&tcount[(jy0 + qy) * ntx + jx0 + (k - qy * jnx)], 1);
         }
       }
     }
   }
   __syncthreads();
+  // records are numbered wave by wave
+  int first = 0, nrec = npieces;
+  for (int k = 0; k < nwaves; ++k) {
+    const int c = misc[24 + k];
+    first += k < wave ? c : 0;
+    nrec += c;
+  }
+  if (wave > 0) first += npieces;
   // bin entries hold 15-bit record ids
   bool binned = tiled && nrec <= 32768;
   int total = 0;
@@ -765,102 +784,140 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   int4* lrec = (int4*)(lds + Lo.lrec);
   uint16_t* bout = local ? (uint16_t*)(lds + Lo.lbin) : bins;
   if (binned) {
-    for (int t = tid; t < ntiles; t += nthr) tfill[t] = 0;
+    for (int t = tid; t < ntiles; t += nthr) tend[t] = toff[t];
     __syncthreads();
   }
 
   // 5. a setup record (with the face colour) per surviving triangle, and its
-  // record id scattered into the bins, from the vertex cache.  Record slots
-  // differ from run to run; they appear in no key, which orders by depth,
-  // then primitive.
-  for (int base = 0; base < nrec; base += nthr) {
-    const int r = base + tid;
-    int x0 = 0, x1 = 0, y0 = 0, y1 = 0, nx = 0, ny = 0;
+  // record id scattered into the bins.  Record slots are in no key, which
+  // orders by depth, then primitive.
+  for (int base = 0; base < mine; base += 64) {
+    const int i = base + lane, r = first + i;
+    Box q{};
     Tri t{};
-    if (r < nrec) {
+    int flags = 0;
+    if (i < mine) {
       int pr, body, vid[3];
-      record_tri(r, &pr, &body, vid, &t);
-      tri_pixels(t.X, t.Y, Wd, Ht, &x0, &x1, &y0, &y1);
+      record_tri(i, &pr, &body, vid, &t);
+      q = box_of(t);
       const int64_t A = tri_area(t.X, t.Y);
-      const int face = body < 0 ? pr : pr - B.pb[body];
+      const int face = body < 0 ? pr : pr - B.id[body].y;
       uint32_t rgb;
       if (L.smooth) {
         // the key carries the record instead of a colour; the pixel's colour
         // comes from the record's attributes in the tile kernel
         rgb = (uint32_t)r;
-        store_attr((float4*)(rs + cam.rs_attr), W.texture ? (float4*)(rs + cam.rs_tuv) : nullptr, r, T, B,
-                   Lo.nmax, gvmap, body, face, vid, vp);
+        store_attr((float4*)(rs + cam.rs_attr), W.texture ? (float4*)(rs + cam.rs_tuv) : nullptr, r, T, B, S, body,
+                   face, vid, vp);
       } else {
-        rgb = face_color(T, B, Lo.nmax, body, face);
+        rgb = face_color(T, B, S, body, face);
       }
       const float invA = 1.0f / (float)(double)A;
-      if (FUSED && local)
+      flags = rec_flags(t);
+      if (FUSED && local) {
         lrec[r] = make_int4((int32_t)((uint32_t)vid[0] | ((uint32_t)vid[2] << 16)),
                             (int32_t)((uint32_t)vid[1] | ((uint32_t)pr << 16)), __float_as_int(invA),
-                            (int32_t)(rgb | ((uint32_t)rec_flags(t) << 24)));
-      else
-        store_rec(grec, r, t, pr, invA, rgb, x0, x1, y0, y1);
-      nx = (x1 >> tsh) - (x0 >> tsh) + 1;
-      ny = (y1 >> tsh) - (y0 >> tsh) + 1;
+                            (int32_t)(rgb | ((uint32_t)flags << 24)));
+      } else {
+        if (!CLIP || i < nmine) {
+          t.z[0] = Vz[vid[0]];
+          t.z[1] = Vz[vid[2]];
+          t.z[2] = Vz[vid[1]];
+        }
+        store_rec(grec, r, t, pr, invA, rgb, flags, q.x0, q.x1, q.y0, q.y1);
+      }
     }
     if (!binned) continue;
-    const bool wide = nx * ny > kWide;
-    if (!wide)
-      for (int qy = 0; qy < ny; ++qy)
-        for (int qx = 0; qx < nx; ++qx)
-          bin_tile(t, r, (x0 >> tsh) + qx, (y0 >> tsh) + qy, x0, x1, y0, y1, nx * ny > 1, Wd, Ht, ntx, TS,
-                   toff, tfill, bout);
-    // a wide triangle is binned by the whole wave, one tile per lane; its
-    // snapped vertices and pixel box come from its lane's registers
-    uint64_t m = __ballot(wide);
-    while (m) {
-      const int j = __ffsll((unsigned long long)m) - 1;
-      m &= m - 1ull;
-      const int jr = __builtin_amdgcn_readlane(r, j);
-      Tri J{};
+    // Every (triangle, tile of its box) pair takes a lane: pair f belongs to
+    // the lane j with off_j <= f < off_j + n_j, found by marking where each
+    // range starts and spreading the marks with a max-scan.  A lane walking
+    // its triangle's tiles one after the other left the others waiting for
+    // the longest: the pass took 28,000 of 70,000 cycles at 540 triangles.
+    // A pair's entry is rejected if the triangle's edges miss the tile, and
+    // flagged if they cover it, where its box in the tile holds more than
+    // kSmallMax pixels (the tile kernel goes over the whole tile then; a
+    // smaller one is expanded into its box's pixels there anyway).
+    const int cnt = q.nx * q.ny;
+    const int incl = wave_incl_add(cnt);
+    const int pairs = __builtin_amdgcn_readlane(incl, 63);
+    const int off = incl - cnt;
+    const float rnx = __builtin_amdgcn_rcpf((float)q.nx);
+    const int bxx = q.x0 | (q.x1 << 16), byy = q.y0 | (q.y1 << 16);
+    int carry = 0;  // owner + 1 of the pair before the window
+    for (int f0 = 0; f0 < pairs; f0 += 64) {
+      own[lane] = 0;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      if (cnt > 0 && off >= f0 && off < f0 + 64) own[off - f0] = lane + 1;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      int o = own[lane];
+      if (lane == 0) o = max(o, carry);
+      o = wave_incl_max(o);
+      carry = __builtin_amdgcn_readlane(o, 63);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int f = f0 + lane;
+      const int j = (o - 1) & 63;
+      const int k = f - __shfl(off, j, 64);
+      const int jnx = __shfl(q.nx, j, 64);
+      // k / jnx exactly: k < 2^18 tiles and jnx <= 512, so the quotient's
+      // fraction is at least 1/1024 away from an integer and its rounding
+      // error below 2^-12
+      const int qy = (int)(((float)k + 0.5f) * __int_as_float(__shfl(__float_as_int(rnx), j, 64)));
+      const int tx = __shfl(q.tx0, j, 64) + k - qy * jnx, ty = __shfl(q.ty0, j, 64) + qy;
+      const int xx = __shfl(bxx, j, 64), yy = __shfl(byy, j, 64);
+      const int px = tx << tsh, py = ty << tsh;
+      const int bx0 = max(xx & 0xFFFF, px), bx1 = min(xx >> 16, px + TS - 1);
+      const int by0 = max(yy & 0xFFFF, py), by1 = min(yy >> 16, py + TS - 1);
+      const bool live = f < pairs;
+      const bool large = live && (bx1 - bx0 + 1) * (by1 - by0 + 1) > kSmallMax;
+      int cls = 1;
+      if (__ballot(large)) {
+        int32_t JX[3], JY[3];
 #pragma unroll
-      for (int v = 0; v < 3; ++v) {
-        J.X[v] = __builtin_amdgcn_readlane(t.X[v], j);
-        J.Y[v] = __builtin_amdgcn_readlane(t.Y[v], j);
+        for (int v = 0; v < 3; ++v) {
+          JX[v] = __shfl(t.X[v], j, 64);
+          JY[v] = __shfl(t.Y[v], j, 64);
+        }
+        const bool narrow = (__shfl(flags, j, 64) & 8) != 0;
+        const bool alone = jnx == 1 && __shfl(q.ny, j, 64) == 1;  // a single tile is never missed
+        if (large && !alone) {
+          if (narrow) cls = tile_class<int32_t>(JX, JY, bx0, bx1, by0, by1);
+          else cls = tile_class<double>(JX, JY, bx0, bx1, by0, by1);
+        }
       }
-      const int jx0 = __builtin_amdgcn_readlane(x0, j), jx1 = __builtin_amdgcn_readlane(x1, j);
-      const int jy0 = __builtin_amdgcn_readlane(y0, j), jy1 = __builtin_amdgcn_readlane(y1, j);
-      const int jnx = (jx1 >> tsh) - (jx0 >> tsh) + 1;
-      const int jn = jnx * ((jy1 >> tsh) - (jy0 >> tsh) + 1);
-      for (int q = lane; q < jn; q += 64) {
-        const int qy = q / jnx;
-        bin_tile(J, jr, (jx0 >> tsh) + (q - qy * jnx), (jy0 >> tsh) + qy, jx0, jx1, jy0, jy1, true, Wd, Ht,
-                 ntx, TS, toff, tfill, bout);
+      if (live && cls != 0) {
+        const bool whole = cls == 2 && bx0 == px && by0 == py && bx1 == min(Wd - 1, px + TS - 1) &&
+                           by1 == min(Ht - 1, py + TS - 1);
+        const int jr = first + base + j;
+        bout[atomicAdd(&tend[ty * ntx + tx], 1)] = (uint16_t)(jr | (whole ? 0x8000 : 0));
       }
     }
   }
   if constexpr (FUSED) {
     // the tile pass reads the table from LDS after the caller's barrier
-    if (tid == 0) misc[6] = (local ? 1 : 0) | (binned ? 2 : 0);
+    if (tid == 0) {
+      misc[2] = nrec;
+      misc[6] = (local ? 1 : 0) | (binned ? 2 : 0);
+    }
     return;
   }
   __syncthreads();
   if (binned)
-    for (int t = tid; t < ntiles; t += nthr) {
-      ttab[2 * t] = toff[t];
-      ttab[2 * t + 1] = tfill[t];
-    }
+    for (int t = tid; t < ntiles; t += nthr) ttab[t] = make_int2(toff[t], tend[t] - toff[t]);
   if (tid == 0) {
     hdr[0] = nrec;
     hdr[1] = binned ? 1 : 0;
   }
 }
 
-// Held to 80 VGPRs (six waves per SIMD; left alone the compiler takes 134,
-// mostly fp64 edge terms of the tile classification hoisted out of the
-// binning loops, and is capped at 128).  The spills this costs (about 50
-// VGPRs to scratch) slow the kernel by about 1.5% when it runs alone, but
-// its waves then fit beside the tile and physics waves that hold the rest of
-// a SIMD's register file when the render overlaps the next step: about 4%
-// more steps per second co-scheduled, at 1024 envs of 32 bodies and at 4096
-// envs of 64 (7 and 8 waves per SIMD, 72 and 64 VGPRs, spill more and lose).
+// Held to 72 VGPRs (seven waves per SIMD), as many as a tile wave takes, so
+// that a slot a tile wave leaves can take one of its waves when the render
+// overlaps the next step.  Bound by latency: at 1,024 images of 540 visible
+// triangles (128 threads each) it takes 37.9 us alone against 37.1 at 80 VGPRs,
+// but the co-scheduled iteration 85.8 us against 90.5 (at 4,096 envs of two
+// 256x256 cameras 2,230 against 2,221; at 2,048 envs of mixed sizes 275 against
+// 270).
 template <bool CLIP>
-__global__ void __attribute__((amdgpu_waves_per_eu(6))) raster_setup_kernel(WorldDev W, RasterLaunch L) {
+__global__ void __attribute__((amdgpu_waves_per_eu(7))) raster_setup_kernel(WorldDev W, RasterLaunch L) {
   extern __shared__ __align__(16) unsigned char lds[];
   // At the end of a step this kernel shares CUs with the render's tile
   // waves; a higher issue priority keeps its chains of dependent steps moving.
@@ -870,20 +927,21 @@ __global__ void __attribute__((amdgpu_waves_per_eu(6))) raster_setup_kernel(Worl
     case 3: __builtin_amdgcn_s_setprio(3); break;
     default: break;
   }
-  const SetupLayout Lo = setup_layout(L.max_bodies, L.max_verts, L.max_tiles, L.max_tris, CLIP);
-  if (L.persistent == 0) {
-    if ((int)blockIdx.x >= L.n_work) return;
-    setup_image<CLIP, false>(lds, Lo, W, L, uniform_ld(L.work + blockIdx.x));
-    return;
-  }
+  const SetupLayout Lo = setup_layout(L.max_bodies, L.max_verts, L.max_tiles, L.max_tris, CLIP, (int)blockDim.x, L.tpl_words);
+  // one copy of the setup for both launch forms (14 KB of code; the instruction
+  // cache is shared with the step's and the tiles' kernels)
   int32_t* slot = (int32_t*)(lds + Lo.misc) + 4;
+  int wi = (int)blockIdx.x;
   for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) *slot = atomicAdd(L.queue, 1);
-    __syncthreads();
-    const int wi = *slot;
+    if (L.persistent) {
+      __syncthreads();
+      if (threadIdx.x == 0) *slot = atomicAdd(L.queue, 1);
+      __syncthreads();
+      wi = *slot;
+    }
     if (wi >= L.n_work) return;
     setup_image<CLIP, false>(lds, Lo, W, L, uniform_ld(L.work + wi));
+    if (!L.persistent) return;
   }
 }
 
@@ -993,6 +1051,7 @@ __device__ __forceinline__ uint32_t smooth_color(const int4* grec, const float4*
 // vertex cache and the pixel box recomputed, so that fetch() returns the
 // four quads of the 64-byte record.
 struct GlobalRecs {
+  static constexpr bool kUniform = true;  // a wave can read one record with scalar loads
   const int4* rec;
   const uint16_t* bins;
   __device__ __forceinline__ int bin(int k) const { return bins[k]; }
@@ -1005,17 +1064,20 @@ struct GlobalRecs {
 };
 
 struct LdsRecs {
+  static constexpr bool kUniform = false;
   const int4* rec;
-  const int4* V;
+  const int2* V;
+  const float* z;
   const uint16_t* bins;
   int w, h;
   __device__ __forceinline__ int bin(int k) const { return bins[k]; }
   __device__ __forceinline__ void fetch(int r, int4& a, int4& b, int4& c, int4& d) const {
     const int4 q = rec[r];
-    const int4 v0 = V[q.x & 0xFFFF], v1 = V[(uint32_t)q.x >> 16], v2 = V[q.y & 0xFFFF];
+    const int i0 = q.x & 0xFFFF, i1 = (int)((uint32_t)q.x >> 16), i2 = q.y & 0xFFFF;
+    const int2 v0 = V[i0], v1 = V[i1], v2 = V[i2];
     a = make_int4(v0.x, v0.y, v1.x, v1.y);
-    b = make_int4(v2.x, v2.y, (int32_t)((uint32_t)q.y >> 16), v0.z);
-    c = make_int4(v1.z, v2.z, q.z, q.w & 0xFFFFFF);
+    b = make_int4(v2.x, v2.y, (int32_t)((uint32_t)q.y >> 16), __float_as_int(z[i0]));
+    c = make_int4(__float_as_int(z[i1]), __float_as_int(z[i2]), q.z, q.w & 0xFFFFFF);
     const int32_t X[3] = {v0.x, v1.x, v2.x}, Y[3] = {v0.y, v1.y, v2.y};
     int x0, x1, y0, y1;
     tri_pixels(X, Y, w, h, &x0, &x1, &y0, &y1);
@@ -1023,9 +1085,28 @@ struct LdsRecs {
   }
 };
 
+// A register of no particular value (no instruction): for lanes that hold no
+// record.
+__device__ __forceinline__ int4 no_value() {
+  int4 v;
+  asm("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
+  return v;
+}
+
+// The key of a pixel no triangle covers, above every other (primitives stay
+// below 0xFFFF); its colour bits are the background's.
+constexpr uint64_t kNoKey = 0xFFFFFFFFFF000000ull;
+
 // One tile of an image: records k0 .. k1 of the tile's bin (binned), or
 // every record k0 .. k1 of the image.  rs: the image's raster scratch (smooth
 // shading reads its attribute records there).
+//
+// Bound by VALU issue, so it is the instructions per tile that count: empty
+// tiles leave at once, lanes past the bin hold no values, a large triangle's
+// record comes by scalar loads and its edge values from integers where they
+// fit.  At 8,192 images of 256x256 (64 bodies) 1,985 -> 1,873 us a launch, at
+// 1,024 of 128x128 (32 bodies) 65.8 -> 62.9; and 76 -> 66 VGPRs, seven waves
+// per SIMD instead of six (1,982 us with six).
 template <bool DBG, bool SMOOTH, int TS, class Src>
 __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam, const Src& src, bool binned,
                                             int k0, int k1, int tx, int ty, TileWaveLDS<TS>& S, int32_t* cov,
@@ -1041,11 +1122,31 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
   const int bx = lane % G::LPR, by = lane / G::LPR;
   const int px0 = tx0 + BW * bx, py0 = ty0 + BH * by;
   const auto zidx = [&](int i, int j) { return (BH * by + j) * TS + BW * bx + i; };
+  // the image's outputs: a uniform base and 32-bit pixel offsets (4096^2 at most)
+  uint32_t* const depth = W.depth + cam.pix_off;
+  uint8_t* const image = W.rgb + 3 * cam.pix_off;
+  const uint32_t row0 = (uint32_t)(py0 * Wd + px0);
+  const bool aligned = ((cam.pix_off + (int64_t)Wd * py0) & 3) == 0;
   uint64_t* zb = S.zb;
+  if (!DBG && BW == 4 && BH == 1 && k0 >= k1) {
+    // an empty bin (a third of the tiles of a settled scene): the background
+    if (py0 <= ty1 && px0 + 3 <= tx1 && aligned) {
+      *(uint4*)((char*)depth + 4 * row0) = make_uint4(~0u, ~0u, ~0u, ~0u);
+      uint32_t* c = (uint32_t*)(image + 3 * row0);
+      c[0] = c[1] = c[2] = 0u;
+      return;
+    }
+    if (py0 <= ty1)
+      for (int i = 0; i < 4 && px0 + i <= tx1; ++i) {
+        depth[row0 + i] = ~0u;
+        for (int q = 0; q < 3; ++q) image[3 * (row0 + i) + q] = 0;
+      }
+    return;
+  }
   // The LDS z-buffer is only for small triangles' fragments: it is cleared
   // before the first fragment window and read back only if it was.  A tile
-  // whose bin is empty (a third of them in a settled scene) or holds large
-  // triangles alone, such as the open ground, never touches it.
+  // that holds large triangles alone, such as the open ground, never touches
+  // it.
   bool zused = false;
   if (DBG) {
 #pragma unroll
@@ -1057,7 +1158,7 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
   int creg[NPX];
 #pragma unroll
   for (int q = 0; q < NPX; ++q) {
-    kreg[q] = ~0ull;
+    kreg[q] = kNoKey;
     creg[q] = 0;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1065,62 +1166,90 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
   for (int kb = k0; kb < k1; kb += 64) {
     // One record per lane, kept in registers: a small triangle's fragments
     // fetch their owner's values with cross-lane reads (ds_bpermute, which
-    // needs no LDS of its own), a large triangle's record is read uniformly
-    // with readlane.  So the tile keeps little LDS, and the step's waves
-    // find room beside it on the CU.
+    // needs no LDS of its own), a large triangle's record is read uniformly.
+    // So the tile keeps little LDS, and the step's waves find room beside it
+    // on the CU.  Lanes past the bin hold no values (and no instructions
+    // clear them): their area is 0.
     const int k = kb + lane;
-    int full = 0, area = 0, fx0 = 0, fy0 = 0, bw = 1;
-    bool big = false;
-    int4 ra = make_int4(0, 0, 0, 0), rb = ra, rc = ra;
-    int E0[3] = {0, 0, 0}, sr[3] = {0, 0, 0}, sc[3] = {0, 0, 0}, thr = 0;
+    int ent = 0;  // record, bit 31 set when its triangle covers the tile
+    int4 ra = no_value(), rb = no_value(), rc = no_value(), rd = no_value();
     if (k < k1) {
-      int rec = k;
+      ent = k;
       if (binned) {
         const int e = src.bin(k);
-        rec = e & 0x7FFF;
-        full = e >> 15;
+        ent = (e & 0x7FFF) | ((e >> 15) << 31);
       }
-      int4 rd;
-      src.fetch(rec, ra, rb, rc, rd);
-      const int32_t X[3] = {ra.x, ra.z, rb.x}, Y[3] = {ra.y, ra.w, rb.y};
-      // the triangle's pixel box (never empty) clipped to the tile
-      fx0 = max(rd.x & 0xFFFF, tx0);
-      fy0 = max(rd.y & 0xFFFF, ty0);
-      bw = min(rd.x >> 16, tx1) - fx0 + 1;
-      const int bh = min(rd.y >> 16, ty1) - fy0 + 1;
-      area = ((bw > 0) & (bh > 0)) ? bw * bh : 0;
-      if (bw < 1) bw = 1;
-      const bool narrow = (rd.z & 8) != 0;
-      big = area > kSmallMax || (area > 0 && !narrow);
-      if (!big && area > 0) {
-        // edge values at the centre of pixel (fx0, fy0), steps per row and
-        // column; (E > 0 or E == 0 on a top-left edge) == (E >= thr bit)
-        const int Px = 256 * fx0 + 128, Py = 256 * fy0 + 128;
+      src.fetch(ent & 0x7FFFFFFF, ra, rb, rc, rd);
+    }
+    const int32_t X[3] = {ra.x, ra.z, rb.x}, Y[3] = {ra.y, ra.w, rb.y};
+    // the triangle's pixel box (never empty) clipped to the tile
+    const int fx0 = max(rd.x & 0xFFFF, tx0), fy0 = max(rd.y & 0xFFFF, ty0);
+    const int bw = min(rd.x >> 16, tx1) - fx0 + 1, bh = min(rd.y >> 16, ty1) - fy0 + 1;
+    const int area = ((k < k1) & (bw > 0) & (bh > 0)) ? bw * bh : 0;
+    const bool narrow = (rd.z & 8) != 0;
+    const bool big = area > kSmallMax || (area > 0 && !narrow);
+    // small triangles: edge values at the centre of pixel (fx0, fy0), steps
+    // per row and column; (E > 0 or E == 0 on a top-left edge) == (E >= thr
+    // bit).  Other lanes' values are unused.
+    int E0[3], sr[3], sc[3];
+    {
+      const int Px = 256 * fx0 + 128, Py = 256 * fy0 + 128;
 #pragma unroll
-        for (int e = 0; e < 3; ++e) {
-          const int a0 = (e + 1) % 3, b0 = (e + 2) % 3;
-          const int32_t dx = X[b0] - X[a0], dy = Y[b0] - Y[a0];
-          E0[e] = __mul24(dx, Py - Y[a0]) - __mul24(dy, Px - X[a0]);
-          sr[e] = 256 * dx;
-          sc[e] = -256 * dy;
-        }
-        thr = rd.z & 7;
+      for (int e = 0; e < 3; ++e) {
+        const int a0 = (e + 1) % 3, b0 = (e + 2) % 3;
+        const int32_t dx = X[b0] - X[a0], dy = Y[b0] - Y[a0];
+        E0[e] = __mul24(dx, Py - Y[a0]) - __mul24(dy, Px - X[a0]);
+        sr[e] = 256 * dx;
+        sc[e] = -256 * dy;
       }
     }
-    // small triangles: fragments packed over lanes.  Fragment f belongs to
-    // the lane j with off_j <= f < off_j + a_j; per window of 64 fragments
-    // each owner marks where its range starts and a max-scan spreads it.
+    const int thr = rd.z;
+    // fragments packed over lanes: fragment f belongs to the lane j with
+    // off_j <= f < off_j + a_j; per window of 64 fragments each owner marks
+    // where its range starts and a max-scan spreads it.
     const int a = big ? 0 : area;
     const int incl = wave_incl_add(a);
     const int F = __builtin_amdgcn_readlane(incl, 63);
     const int off = incl - a;
     const int mxy = fx0 | (fy0 << 16), mob = off | (bw << 16);
+    const float rbw = __builtin_amdgcn_rcpf((float)bw);
     int carry = 0;  // owner + 1 of the fragment before the window
+    // The record of the first large triangle of the mask m.  Where records
+    // are in memory these are scalar loads: no vector instruction, and
+    // neighbouring tiles' waves find the record in the scalar cache; the first
+    // one is asked for here, ahead of the fragments, the others one triangle
+    // ahead.
+    struct LargeRec {
+      int4 a, b, c;
+      int flags, ent;
+    };
+    const auto large_rec = [&](uint64_t m) -> LargeRec {
+      const int j = __ffsll((unsigned long long)m) - 1;
+      LargeRec q;
+      q.ent = __builtin_amdgcn_readlane(ent, j);
+      if constexpr (Src::kUniform) {
+        const int4* p = src.rec + 4 * (int64_t)(q.ent & 0x7FFFFFFF);
+        q.a = uniform_copy(p);
+        q.b = uniform_copy(p + 1);
+        q.c = uniform_copy(p + 2);
+        q.flags = uniform_ld((const int32_t*)(p + 3) + 2);
+      } else {
+        const auto rl = [&](int v) { return __builtin_amdgcn_readlane(v, j); };
+        q.a = make_int4(rl(ra.x), rl(ra.y), rl(ra.z), rl(ra.w));
+        q.b = make_int4(rl(rb.x), rl(rb.y), rl(rb.z), rl(rb.w));
+        q.c = make_int4(rl(rc.x), rl(rc.y), rl(rc.z), rl(rc.w));
+        q.flags = rl(rd.z);
+      }
+      return q;
+    };
+    uint64_t m = __ballot(big);
+    LargeRec next{};
+    if (m) next = large_rec(m);
     if (F > 0 && !zused) {
 #pragma unroll
       for (int j = 0; j < BH; ++j)
 #pragma unroll
-        for (int i = 0; i < BW; ++i) zb[zidx(i, j)] = ~0ull;
+        for (int i = 0; i < BW; ++i) zb[zidx(i, j)] = kNoKey;
       zused = true;
     }
     for (int f0 = 0; f0 < F; f0 += 64) {
@@ -1137,11 +1266,11 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
       const int j = (o - 1) & 63;
       const int jxy = __shfl(mxy, j, 64), job = __shfl(mob, j, 64);
       const int rr = f - (job & 0xFFFF), jbw = job >> 16;
-      // rr / jbw exactly: rr < 64 and jbw <= 32 (a box in a tile of at
-      // most 32 pixels) keep the quotient's fraction at least 1/64 away
-      // from an integer, far above the reciprocal's rounding
-      const int qy = (int)(((float)rr + 0.5f) * __builtin_amdgcn_rcpf((float)jbw));
-      const int qx = rr - qy * jbw;
+      // rr / jbw exactly: rr < kSmallMax <= 128 and jbw <= 32 (a box in a
+      // tile of at most 32 pixels) keep the quotient's fraction at least
+      // 1/64 away from an integer, far above the reciprocal's rounding
+      const int qy = (int)(((float)rr + 0.5f) * __int_as_float(__shfl(__float_as_int(rbw), j, 64)));
+      const int qx = rr - __mul24(qy, jbw);
       const int e0 = __shfl(E0[0], j, 64) + __mul24(__shfl(sr[0], j, 64), qy) + __mul24(__shfl(sc[0], j, 64), qx);
       const int e1 = __shfl(E0[1], j, 64) + __mul24(__shfl(sr[1], j, 64), qy) + __mul24(__shfl(sc[1], j, 64), qx);
       const int e2 = __shfl(E0[2], j, 64) + __mul24(__shfl(sr[2], j, 64), qy) + __mul24(__shfl(sc[2], j, 64), qx);
@@ -1149,7 +1278,7 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
       const float z0 = __int_as_float(__shfl(rb.w, j, 64)), z1 = __int_as_float(__shfl(rc.x, j, 64));
       const float z2 = __int_as_float(__shfl(rc.y, j, 64)), invA = __int_as_float(__shfl(rc.z, j, 64));
       const int jprim = __shfl(rb.z, j, 64), jrgb = __shfl(rc.w, j, 64);
-      if ((f < F) & (e0 >= (jthr & 1)) & (e1 >= ((jthr >> 1) & 1)) & (e2 >= (jthr >> 2))) {
+      if ((f < F) & (e0 >= (jthr & 1)) & (e1 >= ((jthr >> 1) & 1)) & (e2 >= ((jthr >> 2) & 1))) {
         const uint64_t kk = depth_key((float)e0, (float)e1, (float)e2, z0, z1, z2, invA,
                                       prim_key(jprim, (uint32_t)jrgb));
         const int p = (jxy >> 16) + qy - ty0;  // row in the tile
@@ -1159,61 +1288,74 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     }
-    // large triangles: every lane on its four pixels, the record uniform
-    uint64_t m = __ballot(big);
+    // large triangles: every lane on its own pixels, the record uniform
     while (m) {
-      const int j = __ffsll((unsigned long long)m) - 1;
+      const LargeRec q = next;
       m &= m - 1ull;
-      const bool jfull = __builtin_amdgcn_readlane(full, j) != 0;  // uniform
-      const int32_t X[3] = {__builtin_amdgcn_readlane(ra.x, j), __builtin_amdgcn_readlane(ra.z, j),
-                            __builtin_amdgcn_readlane(rb.x, j)};
-      const int32_t Y[3] = {__builtin_amdgcn_readlane(ra.y, j), __builtin_amdgcn_readlane(ra.w, j),
-                            __builtin_amdgcn_readlane(rb.y, j)};
-      const float z0 = __int_as_float(__builtin_amdgcn_readlane(rb.w, j));
-      const float z1 = __int_as_float(__builtin_amdgcn_readlane(rc.x, j));
-      const float z2 = __int_as_float(__builtin_amdgcn_readlane(rc.y, j));
-      const float invA = __int_as_float(__builtin_amdgcn_readlane(rc.z, j));
-      const uint64_t key = prim_key(__builtin_amdgcn_readlane(rb.z, j), (uint32_t)__builtin_amdgcn_readlane(rc.w, j));
-      // edge values at the lane's first pixel, one pixel right, one row
-      // down: exact integers in fp64, so stepping is exact
-      double Er[3], step[3], down[3], thr[3];
+      if (m) next = large_rec(m);  // on its way while this one is rasterized
+      const bool jfull = q.ent < 0;  // uniform
+      const int4 qa = q.a, qb = q.b, qc = q.c;
+      const int jflags = q.flags;
+      const int32_t JX[3] = {qa.x, qa.z, qb.x}, JY[3] = {qa.y, qa.w, qb.y};
+      const float z0 = __int_as_float(qb.w), z1 = __int_as_float(qc.x), z2 = __int_as_float(qc.y);
+      const float invA = __int_as_float(qc.z);
+      const uint64_t key = prim_key(qb.z, (uint32_t)qc.w);
+      // one row of the lane's pixels from the edge values E at its first,
+      // step per pixel; a pixel is covered if every value reaches thr (0, or
+      // 1 on an edge that is not top-left)
+      const auto row = [&](auto full, int j, auto E0, auto E1, auto E2, auto s0, auto s1, auto s2) {
 #pragma unroll
-      for (int e = 0; e < 3; ++e) {
-        const int a0 = (e + 1) % 3, b0 = (e + 2) % 3;
-        const int32_t dx = X[b0] - X[a0], dy = Y[b0] - Y[a0];
-        Er[e] = fma(-(double)dy, (double)(256 * px0 + 128 - X[a0]), (double)dx * (double)(256 * py0 + 128 - Y[a0]));
-        step[e] = -(double)dy * 256.0;
-        down[e] = (double)dx * 256.0;
-        thr[e] = top_left(dx, dy) ? 0.0 : 1.0;
-      }
-#pragma unroll
-      for (int j = 0; j < BH; ++j) {
-        double E[3] = {Er[0], Er[1], Er[2]};
-        if (jfull) {
-          // every pixel of the tile is covered
-#pragma unroll
-          for (int i = 0; i < BW; ++i) {
-            const int q = j * BW + i;
-            const uint64_t kk = depth_key((float)E[0], (float)E[1], (float)E[2], z0, z1, z2, invA, key);
+        for (int i = 0; i < BW; ++i) {
+          const int q = j * BW + i;
+          const uint64_t kk = depth_key((float)E0, (float)E1, (float)E2, z0, z1, z2, invA, key);
+          if constexpr (decltype(full)::value) {
             kreg[q] = kk < kreg[q] ? kk : kreg[q];
             if (DBG) creg[q] += 1;
-#pragma unroll
-            for (int e = 0; e < 3; ++e) E[e] += step[e];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < BW; ++i) {
-            const int q = j * BW + i;
-            const bool in = (E[0] >= thr[0]) & (E[1] >= thr[1]) & (E[2] >= thr[2]);
-            const uint64_t kk = depth_key((float)E[0], (float)E[1], (float)E[2], z0, z1, z2, invA, key);
+          } else {
+            const bool in = (E0 >= (jflags & 1)) & (E1 >= ((jflags >> 1) & 1)) & (E2 >= ((jflags >> 2) & 1));
             kreg[q] = (in & (kk < kreg[q])) ? kk : kreg[q];
             if (DBG) creg[q] += in ? 1 : 0;
-#pragma unroll
-            for (int e = 0; e < 3; ++e) E[e] += step[e];
           }
+          E0 += s0;
+          E1 += s1;
+          E2 += s2;
+        }
+      };
+      if (TS <= 16 && (jflags & 8)) {
+        // A narrow triangle's edge values stay below 2^31 over the whole of a
+        // tile of at most 16 pixels that its box touches: 2 kNarrow (kNarrow
+        // + 16 * 256).  The value at the tile's corner and the steps are
+        // scalar work, so a lane starts with a multiply-add per axis.
+        int E[3], step[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const int a0 = (e + 1) % 3, b0 = (e + 2) % 3;
+          const int32_t dx = JX[b0] - JX[a0], dy = JY[b0] - JY[a0];
+          const int32_t corner = dx * (256 * ty0 + 128 - JY[a0]) - dy * (256 * tx0 + 128 - JX[a0]);
+          step[e] = -256 * dy;
+          E[e] = corner + __mul24(by, 256 * dx) + __mul24(BW * bx, step[e]);
+        }
+        if (jfull) row(std::true_type{}, 0, E[0], E[1], E[2], step[0], step[1], step[2]);
+        else row(std::false_type{}, 0, E[0], E[1], E[2], step[0], step[1], step[2]);
+      } else {
+        // edge values at the lane's first pixel, one pixel right, one row
+        // down: exact integers in fp64, so stepping is exact
+        double Er[3], step[3], down[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const int a0 = (e + 1) % 3, b0 = (e + 2) % 3;
+          const int32_t dx = JX[b0] - JX[a0], dy = JY[b0] - JY[a0];
+          Er[e] = fma(-(double)dy, (double)(256 * px0 + 128 - JX[a0]), (double)dx * (double)(256 * py0 + 128 - JY[a0]));
+          step[e] = -(double)dy * 256.0;
+          down[e] = (double)dx * 256.0;
         }
 #pragma unroll
-        for (int e = 0; e < 3; ++e) Er[e] += down[e];
+        for (int r = 0; r < BH; ++r) {
+          if (jfull) row(std::true_type{}, r, Er[0], Er[1], Er[2], step[0], step[1], step[2]);
+          else row(std::false_type{}, r, Er[0], Er[1], Er[2], step[0], step[1], step[2]);
+#pragma unroll
+          for (int e = 0; e < 3; ++e) Er[e] += down[e];
+        }
       }
     }
   }
@@ -1221,6 +1363,16 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
 
   // resolve: the fragment z-buffer against the registers, then the winners'
   // colours and the stores, one row of the lane's block at a time
+  if (zused) {
+#pragma unroll
+    for (int j = 0; j < BH; ++j)
+#pragma unroll
+      for (int i = 0; i < BW; ++i) {
+        const uint64_t zk = zb[zidx(i, j)];
+        const int q = j * BW + i;
+        kreg[q] = zk < kreg[q] ? zk : kreg[q];
+      }
+  }
 #pragma unroll
   for (int j = 0; j < BH; ++j) {
     const int py = py0 + j;
@@ -1228,12 +1380,10 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
     int32_t win[BW];
 #pragma unroll
     for (int i = 0; i < BW; ++i) {
-      const int q = j * BW + i;
-      const uint64_t zk = zused ? zb[zidx(i, j)] : ~0ull;
-      const uint64_t key = zk < kreg[q] ? zk : kreg[q];
-      const bool hit = key != ~0ull;
+      const uint64_t key = kreg[j * BW + i];
+      const bool hit = key != kNoKey;
       D[i] = hit ? (uint32_t)(key >> 40) : 0xFFFFFFFFu;
-      rgb[i] = hit ? (uint32_t)key & 0xFFFFFFu : 0u;  // the winner's colour travels in its key
+      rgb[i] = (uint32_t)key & 0xFFFFFFu;  // the winner's colour travels in its key
       win[i] = hit ? (int32_t)((key >> 24) & 0xFFFFu) : -1;
       if constexpr (SMOOTH) {
         // the key's low bits name the winning record
@@ -1244,11 +1394,11 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
       }
     }
     if (py > ty1) continue;
-    const int64_t pix = cam.pix_off + (int64_t)py * Wd + px0;
+    const uint32_t pix = row0 + (uint32_t)(j * Wd);
     if constexpr (BW == 4) {
-      if (px0 + 3 <= tx1 && (pix & 3) == 0) {
-        *(uint4*)(W.depth + pix) = make_uint4(D[0], D[1], D[2], D[3]);
-        uint32_t* c = (uint32_t*)(W.rgb + 3 * pix);  // 3 pix is a multiple of 12
+      if (px0 + 3 <= tx1 && ((cam.pix_off + (int64_t)Wd * py) & 3) == 0) {
+        *(uint4*)((char*)depth + 4 * pix) = make_uint4(D[0], D[1], D[2], D[3]);
+        uint32_t* c = (uint32_t*)(image + 3 * pix);  // 3 pixels of the arena is a multiple of 12
         c[0] = rgb[0] | (rgb[1] << 24);
         c[1] = (rgb[1] >> 8) | (rgb[2] << 16);
         c[2] = (rgb[2] >> 16) | (rgb[3] << 8);
@@ -1256,26 +1406,26 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
 #pragma unroll
         for (int i = 0; i < BW; ++i) {
           if (px0 + i > tx1) continue;
-          W.depth[pix + i] = D[i];
-          W.rgb[3 * (pix + i)] = (uint8_t)(rgb[i] & 0xFF);
-          W.rgb[3 * (pix + i) + 1] = (uint8_t)((rgb[i] >> 8) & 0xFF);
-          W.rgb[3 * (pix + i) + 2] = (uint8_t)((rgb[i] >> 16) & 0xFF);
+          depth[pix + i] = D[i];
+          image[3 * (pix + i)] = (uint8_t)(rgb[i] & 0xFF);
+          image[3 * (pix + i) + 1] = (uint8_t)((rgb[i] >> 8) & 0xFF);
+          image[3 * (pix + i) + 2] = (uint8_t)((rgb[i] >> 16) & 0xFF);
         }
       }
     } else {
       if (px0 <= tx1) {
-        W.depth[pix] = D[0];
-        W.rgb[3 * pix] = (uint8_t)(rgb[0] & 0xFF);
-        W.rgb[3 * pix + 1] = (uint8_t)((rgb[0] >> 8) & 0xFF);
-        W.rgb[3 * pix + 2] = (uint8_t)((rgb[0] >> 16) & 0xFF);
+        depth[pix] = D[0];
+        image[3 * pix] = (uint8_t)(rgb[0] & 0xFF);
+        image[3 * pix + 1] = (uint8_t)((rgb[0] >> 8) & 0xFF);
+        image[3 * pix + 2] = (uint8_t)((rgb[0] >> 16) & 0xFF);
       }
     }
     if (DBG) {
 #pragma unroll
       for (int i = 0; i < BW; ++i) {
         if (px0 + i > tx1) continue;
-        W.winners[pix + i] = win[i];
-        W.coverage[pix + i] = cov[zidx(i, j)] + creg[j * BW + i];
+        W.winners[cam.pix_off + pix + i] = win[i];
+        W.coverage[cam.pix_off + pix + i] = cov[zidx(i, j)] + creg[j * BW + i];
       }
     }
   }
@@ -1329,11 +1479,11 @@ __global__ void __launch_bounds__(64 * TW) raster_tile_kernel(WorldDev W, Raster
 // records and bins in src.
 template <bool DBG, int TS, class Src>
 __device__ __forceinline__ void fused_tiles(const WorldDev& W, const CamDev& cam, const Src& src, bool binned,
-                                            int nrec, const int32_t* toff, const int32_t* tfill, int wave,
+                                            int nrec, const int32_t* toff, const int32_t* tend, int wave,
                                             int nw, TileWaveLDS<TS>* S, int32_t* C, const unsigned char* rs) {
   const int ntx = (cam.w + TS - 1) / TS, ntiles = ntx * ((cam.h + TS - 1) / TS);
   for (int t = wave; t < ntiles; t += nw) {
-    const int k0 = binned ? toff[t] : 0, k1 = binned ? k0 + tfill[t] : nrec;
+    const int k0 = binned ? toff[t] : 0, k1 = binned ? tend[t] : nrec;
     raster_tile<DBG, false, TS>(W, cam, src, binned, k0, k1, t % ntx, t / ntx, S[wave],
                                 DBG ? C + wave * TS * TS : nullptr, rs);
   }
@@ -1347,15 +1497,15 @@ __device__ __forceinline__ void fused_tiles(const WorldDev& W, const CamDev& cam
 template <bool DBG, int TS>
 __global__ void __launch_bounds__(1024) raster_fused_kernel(WorldDev W, RasterLaunch L) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const SetupLayout Lo = setup_layout(L.max_bodies, L.max_verts, L.max_tiles, L.max_tris, false, L.lds_zone0,
-                                      L.lrec_cap, L.lbin_cap);
+  const SetupLayout Lo = setup_layout(L.max_bodies, L.max_verts, L.max_tiles, L.max_tris, false, (int)blockDim.x,
+                                      L.tpl_words, L.lds_zone0, L.lrec_cap, L.lbin_cap);
   const int nw = (int)(blockDim.x >> 6);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   TileWaveLDS<TS>* S = (TileWaveLDS<TS>*)lds;
   int32_t* C = (int32_t*)(lds + nw * sizeof(TileWaveLDS<TS>));  // debug coverage, TS * TS per wave
   int32_t* misc = (int32_t*)(lds + Lo.misc);
   const int32_t* toff = (const int32_t*)(lds + Lo.tiles) + Lo.tw;
-  const int32_t* tfill = toff + Lo.tw + 1;
+  const int32_t* tend = toff + Lo.tw + 1;
   int wi = (int)blockIdx.x;
   for (;;) {
     if (L.persistent > 0) {
@@ -1373,12 +1523,12 @@ __global__ void __launch_bounds__(1024) raster_fused_kernel(WorldDev W, RasterLa
     const bool binned = (mode & 2) != 0;
     const unsigned char* rs = W.rscratch + cam.rs_off + (int64_t)L.parity * cam.rs_total;
     if (mode & 1) {
-      const LdsRecs src{(const int4*)(lds + Lo.lrec), (const int4*)(lds + Lo.verts),
+      const LdsRecs src{(const int4*)(lds + Lo.lrec), (const int2*)(lds + Lo.vxy), (const float*)(lds + Lo.vz),
                         (const uint16_t*)(lds + Lo.lbin), cam.w, cam.h};
-      fused_tiles<DBG, TS>(W, cam, src, binned, nrec, toff, tfill, wave, nw, S, C, rs);
+      fused_tiles<DBG, TS>(W, cam, src, binned, nrec, toff, tend, wave, nw, S, C, rs);
     } else {
       const GlobalRecs src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
-      fused_tiles<DBG, TS>(W, cam, src, binned, nrec, toff, tfill, wave, nw, S, C, rs);
+      fused_tiles<DBG, TS>(W, cam, src, binned, nrec, toff, tend, wave, nw, S, C, rs);
     }
     if (L.persistent == 0) return;
     __syncthreads();  // the next image's setup reuses the LDS
@@ -1388,7 +1538,9 @@ __global__ void __launch_bounds__(1024) raster_fused_kernel(WorldDev W, RasterLa
 }  // namespace
 
 size_t raster_lds_bytes(const RasterLaunch& l) {
-  return (size_t)setup_layout(l.max_bodies, l.max_verts, l.max_tiles, l.max_tris, l.near_clip != 0).total;
+  return (size_t)setup_layout(l.max_bodies, l.max_verts, l.max_tiles, l.max_tris, l.near_clip != 0, l.threads,
+                              l.tpl_words)
+      .total;
 }
 
 // The fused kernel's LDS for workgroups of l.threads: the tile pass's
@@ -1406,8 +1558,8 @@ size_t raster_fused_plan(RasterLaunch* l, bool debug, int max_recs) {
   int cap = (l->max_tris + 1) / 2 + 64;
   if (max_recs > 0 && max_recs < cap) cap = max_recs;
   for (const int least = cap < 64 ? cap : 64; cap >= least; cap /= 2) {
-    const SetupLayout Lo = setup_layout(l->max_bodies, l->max_verts, l->max_tiles, l->max_tris, false,
-                                        l->lds_zone0, cap, 4 * cap);
+    const SetupLayout Lo = setup_layout(l->max_bodies, l->max_verts, l->max_tiles, l->max_tris, false, l->threads,
+                                        l->tpl_words, l->lds_zone0, cap, 4 * cap);
     if (Lo.total <= kFusedLdsMax) {
       l->lrec_cap = cap;
       l->lbin_cap = 4 * cap;

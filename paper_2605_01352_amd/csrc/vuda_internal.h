@@ -127,19 +127,20 @@ __host__ __device__ inline int32_t tiles_of(int32_t w, int32_t h, int shift = 4)
   return ((w + t - 1) >> shift) * ((h + t - 1) >> shift);
 }
 
-// Mesh templates and shading constants (device copy of the descriptor).
+// Mesh templates and shading constants (device copy of the descriptor).  The
+// arrays are packed one after the other in `data`, so that the setup kernel
+// keeps in LDS what the templates use, not what they may: palette [8][3],
+// sphere vertices [nv][3] (from kTplSphereV), cube and ground vertices, face
+// normals of sphere and cube [nf][3], then per face one word of three vertex
+// indices, a byte each.  at_*: word offsets.
+constexpr int kTplSphereV = 24;
+constexpr int kTplWordsMax =
+    kTplSphereV + 3 * (2 * kMaxTplVerts + kMaxGroundVerts) + 3 * 2 * kMaxTplFaces + 2 * kMaxTplFaces + kMaxGroundFaces;
 struct alignas(16) Templates {
-  float sphere_v[kMaxTplVerts][3];
-  float cube_v[kMaxTplVerts][3];
-  float ground_v[kMaxGroundVerts][3];
-  uint8_t sphere_f[kMaxTplFaces][3];
-  uint8_t cube_f[kMaxTplFaces][3];
-  uint8_t ground_f[kMaxGroundFaces][3];
-  float sphere_n[kMaxTplFaces][3];
-  float cube_n[kMaxTplFaces][3];
   int32_t sphere_nv, sphere_nf, cube_nv, cube_nf, ground_nv, ground_nf;
+  int32_t at_cube_v, at_ground_v, at_sphere_n, at_cube_n, at_sphere_f, at_cube_f, at_ground_f;
+  int32_t words;  // of data in use, a multiple of 4
   float light[3];
-  float palette[8][3];
   float ground_albedo;
   float near_w;
   float guard;
@@ -147,6 +148,7 @@ struct alignas(16) Templates {
   // repeats per metre
   int32_t tex_w, tex_h;
   float ground_uv_scale;
+  alignas(16) uint32_t data[kTplWordsMax];
 };
 
 struct PhysConsts {
@@ -245,6 +247,7 @@ struct RasterLaunch {
   int32_t* queue;
   int32_t prio;            // setup and tile kernels: wave issue priority 0..3 (s_setprio)
   int32_t near_clip;       // setup kernel: cut triangles crossing the near plane
+  int32_t tpl_words;       // Templates::words
   int32_t smooth;          // per-pixel shading of interpolated vertex normals
   int32_t tile_shift;      // raster tiles of edge 1 << tile_shift (8, 16 or 32 pixels)
   int32_t tile_waves;      // tile kernel: tiles (one per wave) per workgroup, 1, 2 or 4

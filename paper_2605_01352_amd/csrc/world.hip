@@ -183,30 +183,33 @@ static int validate_render(const vuda_render_desc& r) {
 
 static void fill_templates(Templates& t, const vuda_render_desc& r) {
   memset(&t, 0, sizeof(t));
-  for (int i = 0; i < r.sphere_nv; ++i)
-    for (int k = 0; k < 3; ++k) t.sphere_v[i][k] = r.sphere_v[3 * i + k];
-  for (int i = 0; i < r.cube_nv; ++i)
-    for (int k = 0; k < 3; ++k) t.cube_v[i][k] = r.cube_v[3 * i + k];
-  for (int i = 0; i < r.ground_nv; ++i)
-    for (int k = 0; k < 3; ++k) t.ground_v[i][k] = r.ground_v[3 * i + k];
-  for (int i = 0; i < r.sphere_nf; ++i)
-    for (int k = 0; k < 3; ++k) {
-      t.sphere_f[i][k] = (uint8_t)r.sphere_f[3 * i + k];
-      t.sphere_n[i][k] = r.sphere_n[3 * i + k];
-    }
-  for (int i = 0; i < r.cube_nf; ++i)
-    for (int k = 0; k < 3; ++k) {
-      t.cube_f[i][k] = (uint8_t)r.cube_f[3 * i + k];
-      t.cube_n[i][k] = r.cube_n[3 * i + k];
-    }
-  for (int i = 0; i < r.ground_nf; ++i)
-    for (int k = 0; k < 3; ++k) t.ground_f[i][k] = (uint8_t)r.ground_f[3 * i + k];
+  int32_t at = 0;
+  const auto floats = [&](const float* p, int n) {
+    const int32_t first = at;
+    memcpy(t.data + at, p, 4 * (size_t)n);
+    at += n;
+    return first;
+  };
+  const auto faces = [&](const int32_t* f, int n) {
+    const int32_t first = at;
+    for (int i = 0; i < n; ++i)
+      t.data[at++] = (uint32_t)f[3 * i] | ((uint32_t)f[3 * i + 1] << 8) | ((uint32_t)f[3 * i + 2] << 16);
+    return first;
+  };
+  floats(r.palette, 24);
+  floats(r.sphere_v, 3 * r.sphere_nv);
+  t.at_cube_v = floats(r.cube_v, 3 * r.cube_nv);
+  t.at_ground_v = floats(r.ground_v, 3 * r.ground_nv);
+  t.at_sphere_n = floats(r.sphere_n, 3 * r.sphere_nf);
+  t.at_cube_n = floats(r.cube_n, 3 * r.cube_nf);
+  t.at_sphere_f = faces(r.sphere_f, r.sphere_nf);
+  t.at_cube_f = faces(r.cube_f, r.cube_nf);
+  t.at_ground_f = faces(r.ground_f, r.ground_nf);
+  t.words = (at + 3) & ~3;
   t.sphere_nv = r.sphere_nv; t.sphere_nf = r.sphere_nf;
   t.cube_nv = r.cube_nv; t.cube_nf = r.cube_nf;
   t.ground_nv = r.ground_nv; t.ground_nf = r.ground_nf;
   for (int k = 0; k < 3; ++k) t.light[k] = r.light[k];
-  for (int i = 0; i < 8; ++i)
-    for (int k = 0; k < 3; ++k) t.palette[i][k] = r.palette[3 * i + k];
   t.ground_albedo = r.ground_albedo;
   t.near_w = r.near_w;
   t.guard = r.guard;
@@ -247,9 +250,9 @@ int vuda_world::alloc_arena(const vuda_allocator* a) {
   off_.rgb = take(3 * P + 16);
   off_.depth = take(4 * P);
   off_.flags = take(4 * E + 4);
-  off_.tpl = take(sizeof(Templates));
+  off_.tpl = take(sizeof(Templates) + 64);  // and the persistent launches' queues
+  off_.queues = off_.tpl + sizeof(Templates);
   off_.texture = take(textured ? 3 * (size_t)tpl.tex_w * (size_t)tpl.tex_h : 0);
-  off_.queues = take(64);
   off_.rs = take(256 * (size_t)std::max<int64_t>(cap_rs, 1));
   if (debug) {
     off_.winners = take(4 * P);
@@ -995,6 +998,7 @@ int vuda_world::raster_launch_of(const WorkList& L, int parity, int32_t* queue, 
   rl.queue = queue;
   rl.prio = 0;
   rl.near_clip = near_clip ? 1 : 0;
+  rl.tpl_words = tpl.words;
   rl.smooth = smooth ? 1 : 0;
   rl.tile_shift = tune.tile_shift;
   rl.tile_waves = tune.tile_waves;
