@@ -34,8 +34,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRows = 64;      // envs per layer-1 workgroup
 constexpr int kCols = 256;     // hidden units per layer-1 workgroup (64 per wave)
-constexpr int kKStep = 32;     // k per MFMA step
-constexpr int kLdsRow = 40;    // bfloat16 per staged row (32 + 8 padding against bank conflicts)
+constexpr int kKStep = 32;     // k per MFMA
+constexpr int kLdsPad = 8;     // bfloat16 between staged rows (the 16 rows of a fragment read then meet every bank)
 
 constexpr int kXcds = 8;        // accelerator complex dies, each with its own L2
 
@@ -62,48 +62,73 @@ __device__ __forceinline__ uint2 bytes_to_bf16(uint32_t w) {
   return make_uint2(__builtin_amdgcn_perm(f1, f0, 0x07060302u), __builtin_amdgcn_perm(f3, f2, 0x07060302u));
 }
 
-// The bytes behind 8 observation values x[k .. k+7] of one frame (k a
-// multiple of 8): 8 RGB bytes while k is in the RGB part (which ends at
-// 3 W H, a multiple of 32, so a whole 32-k step is on one side), else 8
-// depth words; only the members of that kind are loaded and read.  They are
-// loaded a step ahead and converted only after that step's MFMAs, so that
+// One thread's share of the kStage (64 or 32) observation values that a stage
+// takes of a frame: kStage / 4 of them, a run (RGB part: bytes in a row) or
+// fours (depth part: words 16 i + 4 q, so that the threads of a row read whole
+// sectors).  The RGB part ends at 3 W H, a multiple of kStage, so a stage is on
+// one side; only the members of that side are loaded and read.  They are
+// loaded a stage ahead and converted only after that stage's MFMAs, so that
 // the wait for them does not come before the MFMAs.
-struct ObsRaw {
-  uint2 c;       // RGB bytes
-  uint4 d0, d1;  // depth words
+struct __attribute__((packed, aligned(8))) Bytes16 {  // a frame starts on a multiple of 8 bytes
+  uint32_t w[4];
+};
+template <int kStage>
+union ObsRaw {
+  Bytes16 c;                // kStage 64
+  uint2 c2;                 // kStage 32
+  uint4 d[kStage / 16];
 };
 
-// kRgb: the bytes at rgb[k ..]; else the words at depth[kd ..]
-template <bool kRgb>
-__device__ __forceinline__ void obs_load(ObsRaw& r, const uint8_t* rgb, const uint32_t* depth, int k, int kd) {
+// q of 4: the thread's place in its row of kStage values at k
+template <bool kRgb, int kStage>
+__device__ __forceinline__ void obs_load(ObsRaw<kStage>& r, const uint8_t* rgb, const uint32_t* depth, int k, int q,
+                                         int krgb) {
   if constexpr (kRgb) {
-    r.c = *(const uint2*)(rgb + k);
+    if constexpr (kStage == 64) r.c = *(const Bytes16*)(rgb + k + 16 * q);
+    else r.c2 = *(const uint2*)(rgb + k + 8 * q);
   } else {
-    r.d0 = *(const uint4*)(depth + kd);
-    r.d1 = *(const uint4*)(depth + kd + 4);
+    // (a load for a stage still in the RGB part reads depth words 0 on)
+    const uint32_t* p = depth + max(k - krgb, 0) + 4 * q;
+#pragma unroll
+    for (int i = 0; i < kStage / 16; ++i) r.d[i] = *(const uint4*)(p + 16 * i);
   }
 }
 
-// the 8 values as bfloat16
-template <bool kRgb>
-__device__ __forceinline__ uint4 obs_convert(const ObsRaw& r) {
-  uint32_t w0, w1;
+// the values as bfloat16 into the staged row
+template <bool kRgb, int kStage>
+__device__ __forceinline__ void obs_stage(const ObsRaw<kStage>& r, uint16_t* row, int q) {
   if constexpr (kRgb) {
-    w0 = r.c.x;
-    w1 = r.c.y;
+    const uint32_t w[4] = {kStage == 64 ? r.c.w[0] : r.c2.x, kStage == 64 ? r.c.w[1] : r.c2.y,
+                           kStage == 64 ? r.c.w[2] : 0u, kStage == 64 ? r.c.w[3] : 0u};
+#pragma unroll
+    for (int i = 0; i < kStage / 32; ++i) {
+      const uint2 lo = bytes_to_bf16(w[2 * i]), hi = bytes_to_bf16(w[2 * i + 1]);
+      *(uint4*)(row + kStage / 4 * q + 8 * i) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
   } else {
-    // byte 2 of each depth word: its top byte (background 0xFFFFFFFF gives 255)
-    w0 = __builtin_amdgcn_perm(r.d0.y, r.d0.x, 0x0c0c0602u) | (__builtin_amdgcn_perm(r.d0.w, r.d0.z, 0x0c0c0602u) << 16);
-    w1 = __builtin_amdgcn_perm(r.d1.y, r.d1.x, 0x0c0c0602u) | (__builtin_amdgcn_perm(r.d1.w, r.d1.z, 0x0c0c0602u) << 16);
+#pragma unroll
+    for (int i = 0; i < kStage / 16; ++i) {
+      // byte 2 of each depth word: its top byte (background 0xFFFFFFFF gives 255)
+      const uint32_t w = __builtin_amdgcn_perm(r.d[i].y, r.d[i].x, 0x0c0c0602u) |
+                         (__builtin_amdgcn_perm(r.d[i].w, r.d[i].z, 0x0c0c0602u) << 16);
+      *(uint2*)(row + 16 * i + 4 * q) = bytes_to_bf16(w);
+    }
   }
-  const uint2 lo = bytes_to_bf16(w0), hi = bytes_to_bf16(w1);
-  return make_uint4(lo.x, lo.y, hi.x, hi.y);
 }
 
 // Layer 1: partial sums over k in [s Kc, (s+1) Kc) for kRows envs and kCols
-// hidden units.  Wave w owns units n0 + 64 w .. + 63, all kRows envs: 4 x 4
-// blocks of 16 x 16, one MFMA each per k step.
-__global__ __launch_bounds__(256) void policy_l1_kernel(WorldDev W, PolicyLaunch L) {
+// hidden units.  Wave w owns units n0 + 64 w .. + 63 of all kRows envs: 4 x 4
+// blocks of 16 x 16, one MFMA each per 32 k.  kStage k are staged between two
+// barriers.  At 1,024 envs of 128x128 the reads of W1 bound it (each tile of 64
+// envs reads its columns' weights from L2, 8.6 GB at hidden 4096): 707 us at
+// hidden 4096 (778 TFLOP/s), which took 887 in stages of 32 with a branch
+// around each load.  Tiles of 128 envs in the same splits were slower (one wave
+// per SIMD: 1,101 us for the launch against 1,006), and so were fragments a
+// stage ahead (two waves per SIMD in place of three: 1,077).
+template <int kStage>
+__global__ __launch_bounds__(256, 2) void policy_l1_kernel(WorldDev W, PolicyLaunch L) {
+  constexpr int kRb = kRows / 16;
+  constexpr int kLdsRow = kStage + kLdsPad;
   __shared__ __align__(16) uint16_t sA[2][kRows * kLdsRow];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -112,88 +137,88 @@ __global__ __launch_bounds__(256) void policy_l1_kernel(WorldDev W, PolicyLaunch
   const int n0 = tile.y * kCols + 64 * wave;
   const int s = tile.z;
   const int krgb = L.krgb, Kc = L.kchunk;
-  const int kbeg = s * Kc;
-  const int nsteps = Kc / kKStep;
-  // staging role: row r = tid / 4, k offset 8 (tid % 4) of each step
-  const int r = tid >> 2, kq = 8 * (tid & 3);
-  // rows past M (a ragged last tile) read row m0's frame: a row of A only
+  const int kbeg = s * Kc, kend = kbeg + Kc;
+  const int nstages = Kc / kStage;
+  // staging role: row r, place q4 of each stage
+  const int r = tid >> 2, q4 = tid & 3;
+  // rows past M (a ragged last tile) read row M - 1's frame: a row of A only
   // reaches the same row of the product, and those rows are not stored
-  const CamDev cam = W.cams[W.envs[L.envs[min(m0 + r, L.M - 1)]].cam_off];
-  const uint8_t* rgb = W.rgb + 3 * cam.pix_off;
-  const uint32_t* dep = W.depth + cam.pix_off;
+  const int64_t off = W.cams[W.envs[L.envs[min(m0 + r, L.M - 1)]].cam_off].pix_off;
+  const uint8_t* rgb = W.rgb + 3 * off;
+  const uint32_t* dep = W.depth + off;
   // B fragments: lane (column n0 + 16 cb + lane % 16, k + 8 (lane / 16) .. + 7),
   // in the panel of step k at (k / 32) 32 H
-  const uint16_t* bcol[4];
-#pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    const int n = min(n0 + 16 * cb + (lane & 15), L.H - 1);
-    bcol[cb] = L.w1t + (int64_t)n * kKStep + 8 * (lane >> 4);
-  }
   const int64_t panel = (int64_t)kKStep * L.H;
-  f32x4 acc[4][4];
+  const uint16_t* bpan = L.w1t + (kbeg / kKStep) * panel;  // uniform: the panel in bn
+  uint32_t bcol[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int cb = 0; cb < 4; ++cb)
+    bcol[cb] = (uint32_t)(min(n0 + 16 * cb + (lane & 15), L.H - 1) * kKStep + 8 * (lane >> 4));
+  f32x4 acc[kRb][4];
+#pragma unroll
+  for (int i = 0; i < kRb; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  const int kend = kbeg + Kc;
-  {
-    ObsRaw raw;
-    uint4 v;
-    if (kbeg < krgb) {
-      obs_load<true>(raw, rgb, dep, kbeg + kq, 0);
-      v = obs_convert<true>(raw);
-    } else {
-      obs_load<false>(raw, rgb, dep, 0, kbeg + kq - krgb);
-      v = obs_convert<false>(raw);
-    }
-    *(uint4*)&sA[0][r * kLdsRow + kq] = v;
-  }
-  // W1 fragments run one step ahead of the MFMAs that use them
+  ObsRaw<kStage> raw;
+  // W1 fragments run one step of 32 k ahead of the MFMAs that use them (those
+  // loaded by the last step of a chunk are the next chunk's, or the padding
+  // panel's, and unused)
   uint4 bn[4];
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) bn[cb] = *(const uint4*)(bcol[cb] + (kbeg / kKStep) * panel);
+  for (int cb = 0; cb < 4; ++cb) bn[cb] = *(const uint4*)(bpan + bcol[cb]);
+  if (kbeg < krgb) {
+    obs_load<true, kStage>(raw, rgb, dep, kbeg, q4, krgb);
+    obs_stage<true, kStage>(raw, &sA[0][r * kLdsRow], q4);
+  } else {
+    obs_load<false, kStage>(raw, rgb, dep, kbeg, q4, krgb);
+    obs_stage<false, kStage>(raw, &sA[0][r * kLdsRow], q4);
+  }
   __syncthreads();
-  // One step: the next step's W1 fragments and observation bytes (of the
-  // kind the template argument names) go out, this step's MFMAs run, then
-  // the bytes are converted and staged.  No branch surrounds a load, so no
-  // register copy of a loaded value (and no wait for it) lands before the
-  // MFMAs.  The last step reloads itself (in bounds, unused).
-  auto step = [&](auto next_rgb, int t) {
-    constexpr bool kNextRgb = decltype(next_rgb)::value;
-    const int k = kbeg + t * kKStep;
-    const int knext = min(k + kKStep, kend - kKStep);
+  // One stage: the next stage's observation bytes (of the kind the template
+  // argument names) go out, this stage's MFMAs run, then the bytes are
+  // converted and staged.  No branch surrounds a load, so no register copy of
+  // a loaded value (and no wait for it) lands before the MFMAs.  The last
+  // stage reloads itself (in bounds, unused).
+  const auto step = [&](auto next, int t) {
+    constexpr bool kNextRgb = decltype(next)::value;
     const int buf = t & 1;
-    bf16x8 b[4];
+    const int knext = min(kbeg + (t + 1) * kStage, kend - kStage);
+    obs_load<kNextRgb, kStage>(raw, rgb, dep, knext, q4, krgb);
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) b[cb] = __builtin_bit_cast(bf16x8, bn[cb]);
+    for (int q = 0; q < kStage / kKStep; ++q) {
+      uint4 b[4];
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) bn[cb] = *(const uint4*)(bcol[cb] + (knext / kKStep) * panel);
-    ObsRaw raw;
-    // (a depth load for a step still in the RGB part reads depth word 0 on)
-    obs_load<kNextRgb>(raw, rgb, dep, knext + kq, max(knext + kq - krgb, 0));
-    // the loads go out before the MFMAs
-    __builtin_amdgcn_sched_barrier(0);
+      for (int cb = 0; cb < 4; ++cb) b[cb] = bn[cb];
+      bpan += panel;
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, *(const uint4*)&sA[buf][(16 * rb + (lane & 15)) * kLdsRow + 8 * (lane >> 4)]);
+      for (int cb = 0; cb < 4; ++cb) bn[cb] = *(const uint4*)(bpan + bcol[cb]);
+      // the loads go out before the MFMAs
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[cb], acc[rb][cb], 0, 0, 0);
+      for (int rb = 0; rb < kRb; ++rb) {
+        const bf16x8 a = __builtin_bit_cast(
+            bf16x8, *(const uint4*)&sA[buf][(16 * rb + (lane & 15)) * kLdsRow + kKStep * q + 8 * (lane >> 4)]);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+          acc[rb][cb] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, b[cb]), acc[rb][cb], 0, 0, 0);
+      }
+      // nothing below moves above the MFMAs
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // nothing below moves above the MFMAs
-    __builtin_amdgcn_sched_barrier(0);
-    *(uint4*)&sA[buf ^ 1][r * kLdsRow + kq] = obs_convert<kNextRgb>(raw);
+    obs_stage<kNextRgb, kStage>(raw, &sA[buf ^ 1][r * kLdsRow], q4);
     __syncthreads();
   };
-  // steps whose successor is in the RGB part, then the rest
-  const int t_rgb = min(max((krgb - kbeg) / kKStep, 0), nsteps);  // steps in the RGB part
+  // stages whose successor is in the RGB part, then the rest
+  const int t_rgb = min(max((krgb - kbeg) / kStage, 0), nstages);  // stages in the RGB part
   int t = 0;
   for (; t < t_rgb - 1; ++t) step(std::true_type{}, t);
-  for (; t < nsteps; ++t) step(std::false_type{}, t);
+  for (; t < nstages; ++t) step(std::false_type{}, t);
   // D layout: lane holds rows 4 (lane / 16) + i of a block, column lane % 16
   float* P = L.partial + (int64_t)s * L.M * L.H;
 #pragma unroll
-  for (int rb = 0; rb < 4; ++rb)
+  for (int rb = 0; rb < kRb; ++rb)
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
       const int n = n0 + 16 * cb + (lane & 15);
@@ -222,18 +247,29 @@ __device__ __forceinline__ float ordered_strided_sum(const float* p, int64_t str
   return acc;
 }
 
-// sum_{i < n} x[i] w[i * stride] in i order (x in LDS), loads kBatch at a time
+// sum_{i < n} x[i] w[i * stride] in i order (x in LDS, on 16 bytes), loads
+// kBatch at a time
 template <int kBatch>
 __device__ __forceinline__ float ordered_dot(const float* x, const float* w, int64_t stride, int n) {
   float acc = 0.0f;
   int i = 0;
+  // (one copy of the batch: the kernel runs each line a few times per launch,
+  // and unrolled further it waits for its instructions)
+#pragma unroll 1
   for (; i + kBatch <= n; i += kBatch) {
     float v[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) v[u] = w[(i + u) * stride];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) acc = acc + x[i + u] * v[u];
+    for (int u = 0; u < kBatch; u += 4) {
+      const float4 q = *(const float4*)(x + i + u);
+      acc = acc + q.x * v[u];
+      acc = acc + q.y * v[u + 1];
+      acc = acc + q.z * v[u + 2];
+      acc = acc + q.w * v[u + 3];
+    }
   }
+#pragma unroll 1
   for (; i < n; ++i) acc = acc + x[i] * w[i * stride];
   return acc;
 }
@@ -247,17 +283,21 @@ __device__ __forceinline__ float action_of(float y, float a_max) {
 
 // Layers 2 and 3, one workgroup per env (blockDim = H rounded up to 64,
 // at most 1024): the split-K partials added in split order, then every unit
-// on its own lane, its dot product in index order.  (Splitting each sum over
-// more lanes, to put more loads in flight, was slower: the weight reads from
-// L2 bound this kernel, not their latency.)
+// on its own lane, its dot product in index order.  The reads bound it: W2
+// from L2 by each workgroup (268 MB at 1,024 envs of H = 256), the partials
+// (33 MB at 250 envs in 128 splits) from memory.  Layer 1 and head take 69.5
+// and 31.6 us there, 74 and 31.9 with h read a word at a time; with batches of
+// 64 or of two in flight, or four envs per workgroup, the head alone took 20 to
+// 32 us where it takes 16 to 24.  (Splitting each sum over more lanes was
+// slower too, and would reorder it.)
 __global__ __launch_bounds__(1024) void policy_head_kernel(WorldDev W, PolicyLaunch L) {
-  extern __shared__ float sh[];  // h1 [H], h2 [H]
+  extern __shared__ __align__(16) float sh[];  // h1 [H], h2 [H], each from a multiple of 4
   const int m = blockIdx.x;
   if (m >= L.M) return;
   const int env = L.envs[m];
   const int j = threadIdx.x, H = L.H;
   float* h1 = sh;
-  float* h2 = sh + H;
+  float* h2 = sh + ((H + 3) & ~3);
   if (j < H) {
     const float s1 = ordered_strided_sum<16>(L.partial + (int64_t)m * H + j, (int64_t)L.M * H, L.splits);
     h1[j] = relu(s1 + L.b1[j]);
@@ -379,13 +419,18 @@ __global__ __launch_bounds__(256) void policy_dense_kernel(const float* X, const
 hipError_t launch_policy(const WorldDev& w, const PolicyLaunch& l, hipStream_t s, LaunchEvents* ev) {
   if (l.M <= 0) return hipSuccess;
   const dim3 g1((l.M + kRows - 1) / kRows, (l.H + kCols - 1) / kCols, l.splits);
-  timed_launch(ev, true, false, policy_l1_kernel, g1, dim3(256), 0, s, w, l);
+  // Stages of 64 values where the RGB part and each chunk are whole stages;
+  // frames of an odd multiple of 32 pixels and chunks of an odd number of steps
+  // take stages of 32 (a barrier per 16 MFMAs).
+  const bool whole = l.krgb % 64 == 0 && l.kchunk % 64 == 0;
+  if (whole) timed_launch(ev, true, false, policy_l1_kernel<64>, g1, dim3(256), 0, s, w, l);
+  else timed_launch(ev, true, false, policy_l1_kernel<32>, g1, dim3(256), 0, s, w, l);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (!l.layered) {
     const int threads = (l.H + 63) / 64 * 64;
-    timed_launch(ev, false, true, policy_head_kernel, dim3(l.M), dim3(threads), (uint32_t)(2 * l.H * sizeof(float)), s,
-                 w, l);
+    const uint32_t lds = (uint32_t)((2 * l.H + 4) * sizeof(float));
+    timed_launch(ev, false, true, policy_head_kernel, dim3(l.M), dim3(threads), lds, s, w, l);
     return hipGetLastError();
   }
   // h1, then layer 2 into the partials (free again once h1 is made), h2,

@@ -1481,7 +1481,8 @@ extern "C" int vuda_policy_set(vuda_world* w, const vuda_policy_desc* d) {
   // W1 [K][H] -> [K / 32][H][32]: the 32 weights of a unit for one MFMA
   // step of k are contiguous, and one step's weights of all units form one
   // contiguous panel (in 64 x 64 blocks: both sides stay in cache at H = 4096)
-  std::vector<uint16_t> w1t((size_t)(K * H));
+  // (one more panel, of zeros: layer 1 asks for its fragments a step ahead)
+  std::vector<uint16_t> w1t((size_t)((K + 32) * H));
   for (int64_t k0 = 0; k0 < K; k0 += 64)
     for (int64_t h0 = 0; h0 < H; h0 += 64)
       for (int64_t k = k0; k < std::min(K, k0 + 64); ++k)
