@@ -964,7 +964,8 @@ struct TileGeo {
 template <int TS>
 struct TileWaveLDS {
   uint64_t zb[TS * TS];  // z-buffer of the small-triangle fragments
-  int32_t own[64];       // fragment owner marks
+  uint8_t start[64];     // marks where an owner's fragments start in the window
+  uint8_t owner[64];     // 4 lane of the small triangles, in lane order
 };
 
 // Key of a primitive's fragment below its depth: primitive << 24 | RGB8.
@@ -981,7 +982,8 @@ __device__ __forceinline__ uint64_t depth_key(float e0, float e1, float e2, floa
   const float zz = ((e0 * z0 + e1 * z1) + e2 * z2) * invA;
   // the interpolated depth is finite, so the median equals the clamp to [0, 1]
   const uint32_t D = (uint32_t)rintf(__builtin_amdgcn_fmed3f(zz, 0.0f, 1.0f) * 16777215.0f);
-  return ((uint64_t)D << 40) | key;
+  // (by halves: the upper one is a shift and an or in one instruction)
+  return ((uint64_t)((D << 8) | (uint32_t)(key >> 32)) << 32) | (uint32_t)key;
 }
 
 // Smooth shading of pixel (px, py) won by record r: the attribute record's
@@ -1085,12 +1087,14 @@ struct LdsRecs {
   }
 };
 
-// A register of no particular value (no instruction): for lanes that hold no
-// record.
-__device__ __forceinline__ int4 no_value() {
-  int4 v;
-  asm("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
-  return v;
+typedef short short2v __attribute__((ext_vector_type(2)));
+
+// Registers of no particular value (no instruction): for lanes that hold no
+// record.  (One statement, so that the four are different registers.)
+__device__ __forceinline__ void no_value(int4& a, int4& b, int4& c, int4& d) {
+  asm(""
+      : "=v"(a.x), "=v"(a.y), "=v"(a.z), "=v"(a.w), "=v"(b.x), "=v"(b.y), "=v"(b.z), "=v"(b.w), "=v"(c.x),
+        "=v"(c.y), "=v"(c.z), "=v"(c.w), "=v"(d.x), "=v"(d.y), "=v"(d.z), "=v"(d.w));
 }
 
 // The key of a pixel no triangle covers, above every other (primitives stay
@@ -1101,12 +1105,13 @@ constexpr uint64_t kNoKey = 0xFFFFFFFFFF000000ull;
 // every record k0 .. k1 of the image.  rs: the image's raster scratch (smooth
 // shading reads its attribute records there).
 //
-// Bound by VALU issue, so it is the instructions per tile that count: empty
-// tiles leave at once, lanes past the bin hold no values, a large triangle's
-// record comes by scalar loads and its edge values from integers where they
-// fit.  At 8,192 images of 256x256 (64 bodies) 1,985 -> 1,873 us a launch, at
-// 1,024 of 128x128 (32 bodies) 65.8 -> 62.9; and 76 -> 66 VGPRs, seven waves
-// per SIMD instead of six (1,982 us with six).
+// Bound by VALU issue (three quarters of the cycles issue one), so it is the
+// instructions per tile that count: empty tiles leave at once, lanes past the
+// bin hold no values, a fragment finds its owner by counting marks and takes 14
+// words of it, a large triangle's record comes by scalar loads that no branch
+// surrounds and its edge values from integers where they fit.  At 8,192 images
+// of 256x256 (64 bodies) 393 -> 353 vector instructions per tile, 1,985 ->
+// 1,800 us a launch; at 1,024 of 128x128 (32 bodies) 65.8 -> 56.
 template <bool DBG, bool SMOOTH, int TS, class Src>
 __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam, const Src& src, bool binned,
                                             int k0, int k1, int tx, int ty, TileWaveLDS<TS>& S, int32_t* cov,
@@ -1172,7 +1177,8 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
     // clear them): their area is 0.
     const int k = kb + lane;
     int ent = 0;  // record, bit 31 set when its triangle covers the tile
-    int4 ra = no_value(), rb = no_value(), rc = no_value(), rd = no_value();
+    int4 ra, rb, rc, rd;
+    no_value(ra, rb, rc, rd);
     if (k < k1) {
       ent = k;
       if (binned) {
@@ -1185,13 +1191,13 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
     // the triangle's pixel box (never empty) clipped to the tile
     const int fx0 = max(rd.x & 0xFFFF, tx0), fy0 = max(rd.y & 0xFFFF, ty0);
     const int bw = min(rd.x >> 16, tx1) - fx0 + 1, bh = min(rd.y >> 16, ty1) - fy0 + 1;
-    const int area = ((k < k1) & (bw > 0) & (bh > 0)) ? bw * bh : 0;
-    const bool narrow = (rd.z & 8) != 0;
-    const bool big = area > kSmallMax || (area > 0 && !narrow);
-    // small triangles: edge values at the centre of pixel (fx0, fy0), steps
-    // per row and column; (E > 0 or E == 0 on a top-left edge) == (E >= thr
-    // bit).  Other lanes' values are unused.
-    int E0[3], sr[3], sc[3];
+    const int area = ((k < k1) & (bw > 0) & (bh > 0)) ? __mul24(bw, bh) : 0;
+    const bool big = area > ((rd.z & 8) ? kSmallMax : 0);  // a wide triangle's edge values need more than 32 bits
+    // small triangles: edge values at the centre of pixel (fx0, fy0), and the
+    // steps per row and column over 256, dx and -dy, in one register (a narrow
+    // triangle's are below 2^15); (E > 0 or E == 0 on a top-left edge) ==
+    // (E >= flag bit).  Other lanes' values are unused.
+    int E0[3], step2[3];
     {
       const int Px = 256 * fx0 + 128, Py = 256 * fy0 + 128;
 #pragma unroll
@@ -1199,22 +1205,26 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
         const int a0 = (e + 1) % 3, b0 = (e + 2) % 3;
         const int32_t dx = X[b0] - X[a0], dy = Y[b0] - Y[a0];
         E0[e] = __mul24(dx, Py - Y[a0]) - __mul24(dy, Px - X[a0]);
-        sr[e] = 256 * dx;
-        sc[e] = -256 * dy;
+        step2[e] = (dx & 0xFFFF) | (-dy << 16);
       }
     }
-    const int thr = rd.z;
     // fragments packed over lanes: fragment f belongs to the lane j with
     // off_j <= f < off_j + a_j; per window of 64 fragments each owner marks
-    // where its range starts and a max-scan spreads it.
+    // where its range starts, and the marks up to a fragment count its owner.
     const int a = big ? 0 : area;
-    const int incl = wave_incl_add(a);
+    int incl = wave_incl_add(a);
+    asm("" : "+v"(incl));  // (else off is summed anew from the scan's parts)
     const int F = __builtin_amdgcn_readlane(incl, 63);
     const int off = incl - a;
-    const int mxy = fx0 | (fy0 << 16), mob = off | (bw << 16);
+    // what a fragment needs of its owner's box: the first pixel in the tile,
+    // the width, the edge flags and where the fragments start
+    const int box = ((fy0 - ty0) * TS + fx0 - tx0) | (bw << 10) | ((rd.z & 7) << 16) | (off << 19);
+    static_assert(TS <= 32 && 64 * kSmallMax < 1 << 13, "fields of box");
     const float rbw = __builtin_amdgcn_rcpf((float)bw);
-    int carry = 0;  // owner + 1 of the fragment before the window
-    // The record of the first large triangle of the mask m.  Where records
+    const uint32_t keylo = ((uint32_t)rb.z << 24) | ((uint32_t)rc.w & 0xFFFFFFu), keyhi = (uint32_t)rb.z >> 8;
+    // The record of the first large triangle of the mask m (of lane 63, which
+    // may hold record 0, if there is none: no branch surrounds the load, so
+    // nothing waits for it before its first use).  Where records
     // are in memory these are scalar loads: no vector instruction, and
     // neighbouring tiles' waves find the record in the scalar cache; the first
     // one is asked for here, ahead of the fragments, the others one triangle
@@ -1224,7 +1234,7 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
       int flags, ent;
     };
     const auto large_rec = [&](uint64_t m) -> LargeRec {
-      const int j = __ffsll((unsigned long long)m) - 1;
+      const int j = (__ffsll((unsigned long long)m) - 1) & 63;
       LargeRec q;
       q.ent = __builtin_amdgcn_readlane(ent, j);
       if constexpr (Src::kUniform) {
@@ -1243,8 +1253,12 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
       return q;
     };
     uint64_t m = __ballot(big);
-    LargeRec next{};
-    if (m) next = large_rec(m);
+    LargeRec next = large_rec(m);
+    if (F > 0) {
+      const uint64_t own = __ballot(a > 0);
+      const int nth = __builtin_amdgcn_mbcnt_hi((uint32_t)(own >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)own, 0));
+      if (a > 0) S.owner[nth] = 4 * lane;
+    }
     if (F > 0 && !zused) {
 #pragma unroll
       for (int j = 0; j < BH; ++j)
@@ -1252,37 +1266,42 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
         for (int i = 0; i < BW; ++i) zb[zidx(i, j)] = kNoKey;
       zused = true;
     }
+    int before = -1;  // owners that start before the window, less one
     for (int f0 = 0; f0 < F; f0 += 64) {
-      S.own[lane] = 0;
+      S.start[lane] = 0;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      if (a > 0 && off >= f0 && off < f0 + 64) S.own[off - f0] = lane + 1;
+      if (a > 0 && off >= f0 && off < f0 + 64) S.start[off - f0] = 1;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      int o = S.own[lane];
-      if (lane == 0) o = max(o, carry);
-      o = wave_incl_max(o);
-      carry = __builtin_amdgcn_readlane(o, 63);
+      const uint64_t starts = __ballot(S.start[lane] != 0);
+      // marks up to and at this lane: those below it of the mask less its
+      // first bit
+      const int first = before + (int)(starts & 1);
+      const int nth = __builtin_amdgcn_mbcnt_hi((uint32_t)(starts >> 33),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)(starts >> 1), first));
+      before += __popcll(starts);
       const int f = f0 + lane;
-      // the owner's values (lanes past F read lane 63's, unused)
-      const int j = (o - 1) & 63;
-      const int jxy = __shfl(mxy, j, 64), job = __shfl(mob, j, 64);
-      const int rr = f - (job & 0xFFFF), jbw = job >> 16;
+      // the owner's values (lanes past F read the last owner's, unused)
+      const int j4 = S.owner[nth];
+      const auto own = [&](int v) { return __builtin_amdgcn_ds_bpermute(j4, v); };
+      const auto ownf = [&](float v) { return __int_as_float(own(__float_as_int(v))); };
+      const int jbox = own(box);
+      const int rr = f - (int)((uint32_t)jbox >> 19), jbw = (jbox >> 10) & 63;
       // rr / jbw exactly: rr < kSmallMax <= 128 and jbw <= 32 (a box in a
       // tile of at most 32 pixels) keep the quotient's fraction at least
       // 1/64 away from an integer, far above the reciprocal's rounding
-      const int qy = (int)(((float)rr + 0.5f) * __int_as_float(__shfl(__float_as_int(rbw), j, 64)));
+      const int qy = (int)(((float)rr + 0.5f) * ownf(rbw));
       const int qx = rr - __mul24(qy, jbw);
-      const int e0 = __shfl(E0[0], j, 64) + __mul24(__shfl(sr[0], j, 64), qy) + __mul24(__shfl(sc[0], j, 64), qx);
-      const int e1 = __shfl(E0[1], j, 64) + __mul24(__shfl(sr[1], j, 64), qy) + __mul24(__shfl(sc[1], j, 64), qx);
-      const int e2 = __shfl(E0[2], j, 64) + __mul24(__shfl(sr[2], j, 64), qy) + __mul24(__shfl(sc[2], j, 64), qx);
-      const int jthr = __shfl(thr, j, 64);
-      const float z0 = __int_as_float(__shfl(rb.w, j, 64)), z1 = __int_as_float(__shfl(rc.x, j, 64));
-      const float z2 = __int_as_float(__shfl(rc.y, j, 64)), invA = __int_as_float(__shfl(rc.z, j, 64));
-      const int jprim = __shfl(rb.z, j, 64), jrgb = __shfl(rc.w, j, 64);
-      if ((f < F) & (e0 >= (jthr & 1)) & (e1 >= ((jthr >> 1) & 1)) & (e2 >= ((jthr >> 2) & 1))) {
-        const uint64_t kk = depth_key((float)e0, (float)e1, (float)e2, z0, z1, z2, invA,
-                                      prim_key(jprim, (uint32_t)jrgb));
-        const int p = (jxy >> 16) + qy - ty0;  // row in the tile
-        const int pp = p * TS + (jxy & 0xFFFF) + qx - tx0;
+      const short2v q2 = __builtin_bit_cast(short2v, qy | (qx << 16));
+      const auto edge = [&](int k) {
+        return own(E0[k]) + 256 * __builtin_amdgcn_sdot2(__builtin_bit_cast(short2v, own(step2[k])), q2, 0, false);
+      };
+      const int e0 = edge(0), e1 = edge(1), e2 = edge(2);
+      const float z0 = ownf(__int_as_float(rb.w)), z1 = ownf(__int_as_float(rc.x));
+      const float z2 = ownf(__int_as_float(rc.y)), invA = ownf(__int_as_float(rc.z));
+      const uint64_t key = ((uint64_t)(uint32_t)own((int)keyhi) << 32) | (uint32_t)own((int)keylo);
+      if ((f < F) & (e0 >= ((jbox >> 16) & 1)) & (e1 >= ((jbox >> 17) & 1)) & (e2 >= ((jbox >> 18) & 1))) {
+        const uint64_t kk = depth_key((float)e0, (float)e1, (float)e2, z0, z1, z2, invA, key);
+        const int pp = (jbox & 1023) + qy * TS + qx;
         atomicMin((unsigned long long*)&zb[pp], (unsigned long long)kk);
         if (DBG) atomicAdd(&cov[pp], 1);
       }
@@ -1292,7 +1311,7 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
     while (m) {
       const LargeRec q = next;
       m &= m - 1ull;
-      if (m) next = large_rec(m);  // on its way while this one is rasterized
+      next = large_rec(m);  // on its way while this one is rasterized
       const bool jfull = q.ent < 0;  // uniform
       const int4 qa = q.a, qb = q.b, qc = q.c;
       const int jflags = q.flags;
@@ -1313,7 +1332,9 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
             if (DBG) creg[q] += 1;
           } else {
             const bool in = (E0 >= (jflags & 1)) & (E1 >= ((jflags >> 1) & 1)) & (E2 >= ((jflags >> 2) & 1));
-            kreg[q] = (in & (kk < kreg[q])) ? kk : kreg[q];
+            const bool take = in & (kk < kreg[q]);
+            const uint32_t hi = take ? (uint32_t)(kk >> 32) : (uint32_t)(kreg[q] >> 32);
+            kreg[q] = ((uint64_t)hi << 32) | (take ? (uint32_t)kk : (uint32_t)kreg[q]);
             if (DBG) creg[q] += in ? 1 : 0;
           }
           E0 += s0;
@@ -1431,9 +1452,16 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
   }
 }
 
-// TW tiles of a row per workgroup, one per wave
+// TW tiles of a row per workgroup, one per wave.  Tiles of 16 pixels need 58
+// VGPRs, eight waves per SIMD, but keep to seven: the eighth slot is where the
+// step's and the setup's workgroups start beside a full chip of tiles (an
+// iteration of 1,024 envs at 128x128, pipelined: 81.1 us with seven, 89.7 with
+// eight, 80.3 with six; 4,096 envs of 2x256x256, bound by the tiles: 2,136,
+// 2,103 and 2,238).
 template <bool DBG, bool SMOOTH, int TS, int TW>
-__global__ void __launch_bounds__(64 * TW) raster_tile_kernel(WorldDev W, RasterLaunch L) {
+__global__ void __launch_bounds__(64 * TW)
+    __attribute__((amdgpu_waves_per_eu(TS == 16 && !DBG ? 7 : 1, TS == 16 && !DBG ? 7 : 8)))
+    raster_tile_kernel(WorldDev W, RasterLaunch L) {
   __shared__ TileWaveLDS<TS> S[TW];
   __shared__ int32_t C[DBG ? TW : 1][DBG ? TS * TS : 1];
   // beside the step's kernels, a higher issue priority keeps the render
