@@ -372,9 +372,10 @@ int vuda_world_info(vuda_world* w, int32_t* n_envs, int64_t* n_bodies, int32_t* 
  *                              most n (with 4 bin entries each; less LDS per
  *                              workgroup); an image with more records or bin
  *                              entries passes them through the raster scratch
- *   VUDA_TUNE_TILE_WAVES       1, 2 (default) or 4: tiles of a row per tile-kernel
- *                              workgroup, one per wave (smaller workgroups fit
- *                              beside the step's on shared CUs)
+ *   VUDA_TUNE_TILE_WAVES       1, 2 (default) or 4: tiles of a row that a tile-kernel
+ *                              workgroup works on at a time, one per wave
+ *                              (smaller workgroups fit beside the step's on
+ *                              shared CUs)
  *   VUDA_TUNE_TILE_PRIORITY    0..3: instruction-issue priority of the tile
  *                              kernel's waves relative to the step's
  * None of the others changes any output bit.  Returns VUDA_EINVAL for unknown keys

@@ -21,9 +21,9 @@
 //      edge functions where its box in the tile is large, flagged when the
 //      triangle covers the whole tile.
 //   Each wave keeps the survivors it finds to itself from step 3 on.
-// raster_tile_kernel, one wave per tile and one, two or four tiles of a row
-//   per workgroup; a lane owns four horizontally adjacent pixels.  The bin is read in batches of 64
-//   records.  Small triangles (at most kSmallMax pixels of their box in the
+// raster_tile_kernel, one, two or four waves per workgroup over a run of tiles
+//   of a row, each wave a tile at a time; a lane owns four horizontally
+//   adjacent pixels.  The bin is read in batches of 64 records.  Small triangles (at most kSmallMax pixels of their box in the
 //   tile) are expanded into fragments, one pixel per lane across several
 //   triangles, whose keys meet in an LDS z-buffer through atomic minimum;
 //   large ones are tested by every lane on its own four pixels, keeping the
@@ -1452,7 +1452,8 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
   }
 }
 
-// TW tiles of a row per workgroup, one per wave.  Tiles of 16 pixels need 58
+// A job, a run of tiles of a row, per workgroup of TW waves, which take its
+// tiles in turn.  Tiles of 16 pixels need 58
 // VGPRs, eight waves per SIMD, but keep to seven: the eighth slot is where the
 // step's and the setup's workgroups start beside a full chip of tiles (an
 // iteration of 1,024 envs at 128x128, pipelined: 81.1 us with seven, 89.7 with
@@ -1472,13 +1473,14 @@ __global__ void __launch_bounds__(64 * TW)
     case 3: __builtin_amdgcn_s_setprio(3); break;
     default: break;
   }
-  // The tile's bookkeeping is uniform and takes three rounds of loads (the
-  // job, the camera, then the image's header and the tile's bin range
+  // A wave's bookkeeping is uniform and takes three rounds of loads (the job,
+  // the camera, then the image's header and the bin ranges of the first tiles
   // together) before the first bin entry is read.
   const int2 job = uniform_ld(L.tiles + blockIdx.x);
   if (job.x < 0) return;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  if (wave > (job.x >> kJobWavesShift)) return;  // past the row's last tile; no workgroup barrier follows
+  const int last = job.x >> kJobTilesShift;  // of the job's tiles
+  if (wave > last) return;  // past the row's last tile; no workgroup barrier follows
   const CamDev* cp = W.cams + (job.x & kJobCamMask);
   CamDev cam;  // the fields the tile pass reads
   cam.w = uniform_ld(&cp->w);
@@ -1491,16 +1493,23 @@ __global__ void __launch_bounds__(64 * TW)
   cam.rs_attr = uniform_ld(&cp->rs_attr);
   cam.rs_tuv = uniform_ld(&cp->rs_tuv);
   const int ntx = (cam.w + TS - 1) / TS;
-  const int tx = (job.y & 0xFFFF) + wave, ty = job.y >> 16;
+  const int tx = job.y & 0xFFFF, ty = job.y >> 16;
   const unsigned char* rs = W.rscratch + cam.rs_off + (int64_t)L.parity * cam.rs_total;
   // the tile table has room for the image's tiles at the smallest tile
-  // edge, so its entry is read before the header says the image is binned
+  // edge, so its entries are read before the header says the image is binned
   const int2 hdr = uniform_ld((const int2*)rs);
-  const int2 te = uniform_ld((const int2*)(rs + 64) + (ty * ntx + tx));
+  const int2* table = (const int2*)(rs + 64) + (ty * ntx + tx);
+  int2 te = uniform_ld(table + wave), next = uniform_ld(table + min(wave + TW, last));
   const bool binned = hdr.y != 0;
-  const int k0 = binned ? te.x : 0, k1 = binned ? te.x + te.y : hdr.x;
   const GlobalRecs src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
-  raster_tile<DBG, SMOOTH, TS>(W, cam, src, binned, k0, k1, tx, ty, S[wave], DBG ? C[wave] : nullptr, rs);
+  for (int t = wave;; t += TW) {
+    const int2 after = uniform_ld(table + min(t + 2 * TW, last));
+    const int k0 = binned ? te.x : 0, k1 = binned ? te.x + te.y : hdr.x;
+    raster_tile<DBG, SMOOTH, TS>(W, cam, src, binned, k0, k1, tx + t, ty, S[wave], DBG ? C[wave] : nullptr, rs);
+    if (t + TW > last) return;
+    te = next;
+    next = after;
+  }
 }
 
 // The tiles wave, wave + nw, ... of an image whose setup is done, from

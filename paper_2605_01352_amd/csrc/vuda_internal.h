@@ -225,15 +225,15 @@ struct PhysLaunch {
 };
 
 // Tile-kernel job: the camera id in the low bits, the number of the row's
-// tiles the workgroup takes, less one, above them.
-constexpr int kJobWavesShift = 28;
-constexpr int32_t kJobCamMask = (1 << kJobWavesShift) - 1;
+// tiles the workgroup takes (at most 8), less one, above them.
+constexpr int kJobTilesShift = 28;
+constexpr int32_t kJobCamMask = (1 << kJobTilesShift) - 1;
 
 struct RasterLaunch {
   const int32_t* work;     // camera ids, LPT order (setup kernel, one workgroup each)
   int32_t n_work;
-  const int2* tiles;       // tile kernel: per workgroup (camera | (n - 1) << kJobWavesShift,
-                           // tx | ty << 16): the n <= tile_waves tiles tx .. tx + n - 1 of
+  const int2* tiles;       // tile kernel: per workgroup (camera | (n - 1) << kJobTilesShift,
+                           // tx | ty << 16): the n tiles tx .. tx + n - 1 of
                            // tile row ty; -1 for padding entries
   int32_t n_tile_groups;
   int32_t max_verts;       // over the listed cameras' envs
@@ -250,7 +250,7 @@ struct RasterLaunch {
   int32_t tpl_words;       // Templates::words
   int32_t smooth;          // per-pixel shading of interpolated vertex normals
   int32_t tile_shift;      // raster tiles of edge 1 << tile_shift (8, 16 or 32 pixels)
-  int32_t tile_waves;      // tile kernel: tiles (one per wave) per workgroup, 1, 2 or 4
+  int32_t tile_waves;      // tile kernel: waves per workgroup (wave i takes tiles i, i + tile_waves, ...), 1, 2 or 4
   // fused kernel only (raster_fused_plan): LDS bytes reserved for the tile
   // pass's z-buffers, compact records and bin entries an image keeps in LDS
   int32_t lds_zone0, lrec_cap, lbin_cap;

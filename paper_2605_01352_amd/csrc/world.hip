@@ -845,6 +845,25 @@ void vuda_world::invalidate_lists() {
   graphs.clear();
 }
 
+// Tiles of a row that one tile-kernel job takes, on `waves` waves, when `left`
+// tiles (these among them) are not yet in a job.  A wave that goes on to the
+// next tile of a row has its image's bookkeeping at hand and the tile's bin
+// range on its way, where a new one waits for three rounds of loads.  The last
+// four tiles per wave slot (7 per SIMD) go one to a wave, so that the launch
+// ends evenly; a run stays shorter than the row, else one job holds a whole row
+// of the ground or of the sky; and a single wave takes two at most (images of
+// 200x200: 118 us a launch with two, 127 with four).  Tile pass in us, one tile
+// a wave and so: 1,024 images of 128x128 57.1 and 56.5, 2,048 129 and 115.5,
+// 2,048 of 256x256 452 and 386, 8,192 of 256x256 1,816 and 1,653, 48 of 640x480
+// 83.1 and 75.6; whole rows: 2,048 of 128x128 128.8, 16,384 of 64x64 354 where
+// one tile a wave takes 332.
+static int32_t tile_run(int32_t waves, int32_t row, int64_t left) {
+  constexpr int64_t kEnd = 4 * 7 * 4 * 256;
+  int32_t per = 1;
+  while (left > kEnd && per < (waves == 1 ? 2 : 4) && 2 * per * waves <= 8 && 2 * per * waves < row) per *= 2;
+  return per * waves;
+}
+
 int vuda_world::get_list(int phase, int32_t lo, int32_t hi, const WorkList** out) {
   const auto key = std::make_tuple(phase, lo, hi);
   WorkList& L = lists[key];
@@ -904,21 +923,28 @@ int vuda_world::get_list(int phase, int32_t lo, int32_t hi, const WorkList** out
   L.n = (int32_t)ids.size();
   L.n_groups = 0;
   if (phase == VUDA_PHASE_RENDER && !ids.empty()) {
-    // Tile-kernel jobs of tile_waves tiles of a row.  Workgroups are handed to the 8 XCDs
-    // round-robin, so the setup workgroup of image i runs on XCD i mod 8;
-    // its tiles get job indices of the same residue, where that XCD's L2
-    // still holds the image's records and bins.
+    // Tile-kernel jobs of a run of tiles of a row.  Workgroups are handed to
+    // the 8 XCDs round-robin, so the setup workgroup of image i runs on XCD
+    // i mod 8; its tiles get job indices of the same residue, where that
+    // XCD's L2 still holds the image's records and bins.
     constexpr int kXcd = 8;
+    int64_t left = 0;  // tiles not yet in a job
+    for (int32_t id : ids) {
+      const CamDev& cd = cam_host[id];
+      left += (int64_t)(((cd.w - 1) >> tune.tile_shift) + 1) * (((cd.h - 1) >> tune.tile_shift) + 1);
+    }
     std::vector<std::vector<int2>> per(kXcd);
     for (size_t i = 0; i < ids.size(); ++i) {
       const CamDev& cd = cam_host[ids[i]];
       const int ts = 1 << tune.tile_shift;
       const int32_t ntx = (cd.w + ts - 1) >> tune.tile_shift, nty = (cd.h + ts - 1) >> tune.tile_shift;
       if (ids[i] > kJobCamMask) return fail(VUDA_EINVAL, "camera id %d beyond the tile job's range", ids[i]);
+      const int32_t run = tile_run(tune.tile_waves, ntx, left);
+      left -= (int64_t)ntx * nty;
       for (int32_t ty = 0; ty < nty; ++ty)
-        for (int32_t tx = 0; tx < ntx; tx += tune.tile_waves) {
-          const int32_t n = std::min(tune.tile_waves, ntx - tx);
-          per[i % kXcd].push_back(make_int2(ids[i] | ((n - 1) << kJobWavesShift), tx | (ty << 16)));
+        for (int32_t tx = 0; tx < ntx; tx += run) {
+          const int32_t n = std::min(run, ntx - tx);
+          per[i % kXcd].push_back(make_int2(ids[i] | ((n - 1) << kJobTilesShift), tx | (ty << 16)));
         }
     }
     size_t len = 0;
