@@ -215,6 +215,7 @@ extern "C" int vuda_autotune(vuda_world* w, int32_t steps, const char* cache_pat
     c.split = out->cu_split;
     c.sched = out->schedule;
     c.tune.raster_threads = out->raster_threads;
+    c.tune.raster_threads_default = false;
     c.tune.rec_cap = out->rec_cap;
     c.tune.phys_persistent = out->phys_persistent;
     c.tune.raster_persistent = out->raster_persistent;
@@ -252,6 +253,7 @@ extern "C" int vuda_autotune(vuda_world* w, int32_t steps, const char* cache_pat
   bs.split = 0.0f;
   bs.sched = VUDA_SCHED_SERIAL;
   bs.tune = saved;
+  bs.tune.raster_threads_default = false;  // the trials run at the size they name
   double best_serial = -1.0;
   for (int fused : {0, 1})
     for (int rt : {256, 512}) {

@@ -82,6 +82,7 @@ struct WorkList {
 
 struct Tuning {
   int32_t raster_threads = 256;
+  bool raster_threads_default = true;  // not asked for: a setup launch may take another size
   int32_t rec_cap = 0;  // bin entries an image may use (0: its whole capacity)
   int32_t phys_persistent = 0;
   int32_t raster_persistent = 0;
@@ -252,7 +253,8 @@ struct vuda_world {
   int range_parity(int32_t lo, int32_t hi, int* parity);
   int check_range(int32_t lo, int32_t hi);
   int enqueue_physics(const vuda::WorkList& L, int parity, int nsteps, hipStream_t s, vuda::LaunchEvents* ev);
-  int raster_launch_of(const vuda::WorkList& L, int parity, int32_t* queue, vuda::RasterLaunch* out);
+  // setup: for the setup or the tile kernel (not the fused one)
+  int raster_launch_of(const vuda::WorkList& L, int parity, int32_t* queue, bool setup, vuda::RasterLaunch* out);
   // the fused raster launch of a render list; *lds = 0 when the two-kernel
   // path renders it (fused off, smooth shading, near-plane clipping, or an
   // env too large for LDS)

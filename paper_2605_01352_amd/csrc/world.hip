@@ -1007,7 +1007,7 @@ int vuda_world::enqueue_physics(const WorkList& L, int parity, int nsteps, hipSt
   return VUDA_OK;
 }
 
-int vuda_world::raster_launch_of(const WorkList& L, int parity, int32_t* queue, RasterLaunch* out) {
+int vuda_world::raster_launch_of(const WorkList& L, int parity, int32_t* queue, bool setup, RasterLaunch* out) {
   RasterLaunch rl;
   rl.work = L.dptr;
   rl.n_work = L.n;
@@ -1029,8 +1029,21 @@ int vuda_world::raster_launch_of(const WorkList& L, int parity, int32_t* queue, 
   rl.tile_shift = tune.tile_shift;
   rl.tile_waves = tune.tile_waves;
   rl.lds_zone0 = rl.lrec_cap = rl.lbin_cap = 0;
-  const size_t lds = raster_lds_bytes(rl);
+  size_t lds = raster_lds_bytes(rl);
   const size_t kLdsMax = 160 * 1024;
+  // Where no size was asked for, a setup of at most two images per CU (one
+  // beside the other phases) takes 512 threads: the chip has room for the
+  // waves, and an image's chain of passes is shorter (250 images of 17 bodies
+  // at 64x64 13.3 us, 15.4 with 256; 512 of 64 bodies 24.5 and 28.5; 48 of
+  // 640x480 35.7 and 47.2; an iteration of 256 envs of 64 bodies beside
+  // physics 64.9 and 71.6).  With more images the waves crowd each other out
+  // (1,024 of 16 bodies 28.5 and 21.0; 500 beside physics 61.4 and 59.5).
+  if (setup && tune.raster_threads_default && mode != 1 && L.n <= (mode == 0 ? 512 : 256)) {
+    rl.threads = 512;
+    const size_t wide = raster_lds_bytes(rl);
+    if (wide <= kLdsMax) lds = wide;
+    else rl.threads = tune.raster_threads;
+  }
   if (lds > kLdsMax)
     return fail(VUDA_EOVERFLOW, "raster setup needs %zu bytes of LDS (max %zu)", lds, kLdsMax);
   if (lds > lds_configured) {
@@ -1046,7 +1059,7 @@ int vuda_world::fused_launch_of(const WorkList& L, int parity, int32_t* queue, R
   // vertex-cache indices and primitives travel in 16 bits of a compact record
   if (!tune.raster_fused || near_clip || smooth || L.max_verts > 65536 || L.max_tris > 65536) return VUDA_OK;
   RasterLaunch rl;
-  int rc = raster_launch_of(L, parity, queue, &rl);
+  int rc = raster_launch_of(L, parity, queue, false, &rl);
   if (rc) return rc;
   const size_t need = raster_fused_plan(&rl, dev.winners != nullptr, tune.fused_recs);
   if (need == 0) return VUDA_OK;
@@ -1079,7 +1092,7 @@ int vuda_world::enqueue_kernel(int kind, const WorkList& L, int parity, int nste
     return VUDA_OK;
   }
   RasterLaunch rl;
-  int rc = raster_launch_of(L, parity, queue, &rl);
+  int rc = raster_launch_of(L, parity, queue, true, &rl);
   if (rc) return rc;
   // the setup that ends a step (its own queue slot) runs at the step's priority
   if (kind == kKernelSetup) rl.prio = queue == queues + 1 ? tune.phys_prio : 0;
@@ -2183,6 +2196,7 @@ extern "C" int vuda_set_tuning(vuda_world* w, int32_t key, int32_t value) {
     case VUDA_TUNE_RASTER_THREADS:
       if (value < 64 || value > 1024 || value % 64) return fail(VUDA_EINVAL, "raster threads %d", value);
       w->tune.raster_threads = value;
+      w->tune.raster_threads_default = false;
       break;
     case VUDA_TUNE_REC_CAP:
       if (value < 0) return fail(VUDA_EINVAL, "bin limit %d", value);
