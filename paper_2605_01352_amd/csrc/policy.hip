@@ -247,11 +247,13 @@ __device__ __forceinline__ float ordered_strided_sum(const float* p, int64_t str
   return acc;
 }
 
-// sum_{i < n} x[i] w[i * stride] in i order (x in LDS, on 16 bytes), loads
-// kBatch at a time
-template <int kBatch>
-__device__ __forceinline__ float ordered_dot(const float* x, const float* w, int64_t stride, int n) {
-  float acc = 0.0f;
+// acc[e] = sum_{i < n} x[e pitch + i] w[i * stride] in i order (x in LDS, rows
+// on 16 bytes), loads kBatch at a time
+template <int kBatch, int kEnvs>
+__device__ __forceinline__ void ordered_dots(const float* x, int pitch, const float* w, int64_t stride, int n,
+                                             float (&acc)[kEnvs]) {
+#pragma unroll
+  for (int e = 0; e < kEnvs; ++e) acc[e] = 0.0f;
   int i = 0;
   // (one copy of the batch: the kernel runs each line a few times per launch,
   // and unrolled further it waits for its instructions)
@@ -261,17 +263,22 @@ __device__ __forceinline__ float ordered_dot(const float* x, const float* w, int
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) v[u] = w[(i + u) * stride];
 #pragma unroll
-    for (int u = 0; u < kBatch; u += 4) {
-      const float4 q = *(const float4*)(x + i + u);
-      acc = acc + q.x * v[u];
-      acc = acc + q.y * v[u + 1];
-      acc = acc + q.z * v[u + 2];
-      acc = acc + q.w * v[u + 3];
-    }
+    for (int u = 0; u < kBatch; u += 4)
+#pragma unroll
+      for (int e = 0; e < kEnvs; ++e) {
+        const float4 q = *(const float4*)(x + e * pitch + i + u);
+        acc[e] = acc[e] + q.x * v[u];
+        acc[e] = acc[e] + q.y * v[u + 1];
+        acc[e] = acc[e] + q.z * v[u + 2];
+        acc[e] = acc[e] + q.w * v[u + 3];
+      }
   }
 #pragma unroll 1
-  for (; i < n; ++i) acc = acc + x[i] * w[i * stride];
-  return acc;
+  for (; i < n; ++i) {
+    const float v = w[i * stride];
+#pragma unroll
+    for (int e = 0; e < kEnvs; ++e) acc[e] = acc[e] + x[e * pitch + i] * v;
+  }
 }
 
 __device__ __forceinline__ float relu(float v) { return v > 0.0f ? v : 0.0f; }
@@ -281,33 +288,49 @@ __device__ __forceinline__ float action_of(float y, float a_max) {
   return a_max * __builtin_amdgcn_fmed3f(y, -1.0f, 1.0f);
 }
 
-// Layers 2 and 3, one workgroup per env (blockDim = H rounded up to 64,
+// Layers 2 and 3 of kEnvs envs per workgroup (blockDim = H rounded up to 64,
 // at most 1024): the split-K partials added in split order, then every unit
-// on its own lane, its dot product in index order.  The reads bound it: W2
-// from L2 by each workgroup (268 MB at 1,024 envs of H = 256), the partials
-// (33 MB at 250 envs in 128 splits) from memory.  Layer 1 and head take 69.5
-// and 31.6 us there, 74 and 31.9 with h read a word at a time; with batches of
-// 64 or of two in flight, or four envs per workgroup, the head alone took 20 to
-// 32 us where it takes 16 to 24.  (Splitting each sum over more lanes was
-// slower too, and would reorder it.)
+// on its own lane, its dot products in index order.  The reads bound it: W2
+// from L2 by each workgroup (268 MB a launch at 1,024 envs of H = 256 and one
+// env each, 4.3 GB at H = 1,024: layer 1 and head 237 us, 167 with two), the
+// partials (33 MB at 250 envs in 128 splits) from memory.  Batches of 64 loads
+// or of two in flight were slower (the head alone 20 us where it takes 16).
+// (Splitting each sum over more lanes was slower too, and would reorder it.)
+template <int kEnvs>
 __global__ __launch_bounds__(1024) void policy_head_kernel(WorldDev W, PolicyLaunch L) {
-  extern __shared__ __align__(16) float sh[];  // h1 [H], h2 [H], each from a multiple of 4
-  const int m = blockIdx.x;
-  if (m >= L.M) return;
-  const int env = L.envs[m];
-  const int j = threadIdx.x, H = L.H;
+  extern __shared__ __align__(16) float sh[];  // h1, h2 [kEnvs][pitch]
+  const int m0 = blockIdx.x * kEnvs;
+  if (m0 >= L.M) return;
+  const int j = threadIdx.x, H = L.H, pitch = (H + 3) & ~3;
   float* h1 = sh;
-  float* h2 = sh + ((H + 3) & ~3);
+  float* h2 = sh + kEnvs * pitch;
+  // (rows past M, in a ragged last workgroup, repeat the last one and are not
+  // written)
   if (j < H) {
-    const float s1 = ordered_strided_sum<16>(L.partial + (int64_t)m * H + j, (int64_t)L.M * H, L.splits);
-    h1[j] = relu(s1 + L.b1[j]);
+#pragma unroll
+    for (int e = 0; e < kEnvs; ++e) {
+      const int m = min(m0 + e, L.M - 1);
+      const float s1 = ordered_strided_sum<16>(L.partial + (int64_t)m * H + j, (int64_t)L.M * H, L.splits);
+      h1[e * pitch + j] = relu(s1 + L.b1[j]);
+    }
   }
   __syncthreads();
-  if (j < H) h2[j] = relu(ordered_dot<32>(h1, L.w2 + j, H, H) + L.b2[j]);
+  if (j < H) {
+    float acc[kEnvs];
+    ordered_dots<32, kEnvs>(h1, pitch, L.w2 + j, H, H, acc);
+#pragma unroll
+    for (int e = 0; e < kEnvs; ++e) h2[e * pitch + j] = relu(acc[e] + L.b2[j]);
+  }
   __syncthreads();
-  for (int q = j; q < L.A; q += blockDim.x)
-    W.actions[(int64_t)env * L.A + q] = action_of(ordered_dot<32>(h2, L.w3 + q, L.A, H) + L.b3[q], L.a_max);
-  if (j == 0) W.act_on[env] = 1;
+  // one (env, action) pair per lane
+  for (int i = j; i < kEnvs * L.A; i += blockDim.x) {
+    const int e = kEnvs == 1 ? 0 : i / L.A, q = i - e * L.A;
+    float acc[1];
+    ordered_dots<32, 1>(h2 + e * pitch, pitch, L.w3 + q, L.A, H, acc);
+    if (kEnvs == 1 || m0 + e < L.M)
+      W.actions[(int64_t)L.envs[m0 + e] * L.A + q] = action_of(acc[0] + L.b3[q], L.a_max);
+  }
+  if (j < kEnvs && m0 + j < L.M) W.act_on[L.envs[m0 + j]] = 1;
 }
 
 // ---- layers 2 and 3 as batched products (H > 1024) ----
@@ -429,8 +452,16 @@ hipError_t launch_policy(const WorldDev& w, const PolicyLaunch& l, hipStream_t s
   if (e != hipSuccess) return e;
   if (!l.layered) {
     const int threads = (l.H + 63) / 64 * 64;
-    const uint32_t lds = (uint32_t)((2 * l.H + 4) * sizeof(float));
-    timed_launch(ev, false, true, policy_head_kernel, dim3(l.M), dim3(threads), lds, s, w, l);
+    // Two envs per workgroup where the weights' reads count more than the
+    // workgroups (layer 1 and head in us, one env and two: 1,024 at H = 256
+    // 74 and 67, 600 at 512 71 and 61, 256 at 1,024 88 and 81; 512 at 256 32.8
+    // and 33.3, 250 at 256 31.4 and 34.2, 1,000 at 100 28.0 and 30.4; four were
+    // slower everywhere).
+    const int envs = (int64_t)l.M * l.H >= 1 << 18 ? 2 : 1;
+    const dim3 g((l.M + envs - 1) / envs), b(threads);
+    const uint32_t lds = (uint32_t)(2 * envs * ((l.H + 3) & ~3) * sizeof(float));
+    if (envs == 2) timed_launch(ev, false, true, policy_head_kernel<2>, g, b, lds, s, w, l);
+    else timed_launch(ev, false, true, policy_head_kernel<1>, g, b, lds, s, w, l);
     return hipGetLastError();
   }
   // h1, then layer 2 into the partials (free again once h1 is made), h2,

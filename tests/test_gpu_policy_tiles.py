@@ -1,5 +1,6 @@
-"""GPU parity of layer 1's stages of 32 and 64 observation values, through the
-C ABI, at ragged batches, hidden sizes and chunk counts.
+"""GPU parity of layer 1's stages of 32 and 64 observation values and of the
+head's one and two envs per workgroup, through the C ABI, at ragged batches,
+hidden sizes and chunk counts.
 
 Gate: the oracle's float32 error bound on the actions (as in
 test_gpu_policy.py), on frames checked to be identical.
@@ -29,3 +30,16 @@ def test_layer1_stages(width, height, envs, hidden):
         w.step(nsteps=5)
         w.set_policy(P)
         check_actions(w, s, P, range(s.n_envs), f"policy {envs} envs {width}x{height} H{hidden}")
+
+
+# two envs per workgroup (at least 2^18 hidden units over the batch): an odd
+# batch, a hidden size that is no multiple of 4 or of 64, more and fewer
+# actions than lanes; and the last batch that takes one
+@pytest.mark.parametrize("envs,hidden,bodies", [(257, 1024, 2), (513, 515, 40), (512, 513, 1), (511, 512, 3)])
+def test_head_envs_per_workgroup(envs, hidden, bodies):
+    s = sg.make_scene(1700 + envs, [bodies] * envs, 8, mixed=True)
+    P = sg.policy_weights(33, 8, 8, hidden, bodies)
+    with vuda.World(s) as w:
+        w.step(nsteps=5)
+        w.set_policy(P)
+        check_actions(w, s, P, [0, 1, 63, 64, envs - 2, envs - 1], f"policy {envs} envs H{hidden}")
