@@ -238,7 +238,8 @@ int vuda_cosched(vuda_world* w, float cu_split);
 /*
  * Enqueue `nsteps` physics steps of envs [env_lo, env_hi) and return (the
  * paper's step_async).  Step t of an env reads its state buffer t%2 and
- * writes (t+1)%2.  Dependencies are stream-ordered: the step waits for the
+ * writes (t+1)%2; a launch carries an env through up to 64 steps of the call
+ * and writes the state of the last one.  Dependencies are stream-ordered: the step waits for the
  * last enqueued step of the world (state read) and the last enqueued render
  * (which may read the buffer being overwritten).  All envs of the range must
  * have taken the same number of steps modulo 2 (VUDA_EINVAL otherwise).
@@ -326,7 +327,7 @@ int vuda_world_info(vuda_world* w, int32_t* n_envs, int64_t* n_bodies, int32_t* 
  *                              workgroups as the GPU holds at once (the
  *                              kernel's occupancy per CU times the CU count)
  *   VUDA_TUNE_RASTER_PERSISTENT  the same for camera images
- *   VUDA_TUNE_GRAPHS           1: each (phase, env range, parity) launch is
+ *   VUDA_TUNE_GRAPHS           1: each (phase, env range, parity, steps) launch is
  *                              captured once into a hipGraph and replayed
  *   VUDA_TUNE_PHYS_PRIORITY    0..3: instruction-issue priority of the step's
  *                              waves (physics, and the raster setup that ends

@@ -1,8 +1,9 @@
-// Rigid-body physics step for gfx950: one workgroup per env, one lane per body.
+// Rigid-body physics step for gfx950: a wave per env (two above 64 bodies), one
+// lane per body.
 //
-// One launch advances every listed env by one step of `substeps` substeps,
-// reading state buffer `parity` and writing buffer 1 - parity once; the
-// substeps run out of LDS and registers.  Per substep:
+// One launch advances every listed env by `nsteps` steps of `substeps`
+// substeps, reading state buffer `parity` and writing the last step's buffer
+// once; the substeps run out of LDS and registers.  Per substep:
 //   1. publish p, v, omega and R(q) of every body to LDS;
 //   2. broadphase on a uniform grid hashed into 2^ceil(log2 2N) buckets
 //      (Teschner et al. 2003 XOR-prime hash).  A bucket is a bitset of

@@ -909,13 +909,12 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   }
 }
 
-// Held to 72 VGPRs (seven waves per SIMD), as many as a tile wave takes, so
-// that a slot a tile wave leaves can take one of its waves when the render
-// overlaps the next step.  Bound by latency: at 1,024 images of 540 visible
-// triangles (128 threads each) it takes 37.9 us alone against 37.1 at 80 VGPRs,
-// but the co-scheduled iteration 85.8 us against 90.5 (at 4,096 envs of two
-// 256x256 cameras 2,230 against 2,221; at 2,048 envs of mixed sizes 275 against
-// 270).
+// Held to 72 VGPRs (seven waves per SIMD), so that a slot a tile wave leaves can
+// take one of its waves when the render overlaps the next step.  Bound by
+// latency: at 1,024 images of 540 visible triangles (128 threads each) it takes
+// 37.9 us alone, 37.1 at 80 VGPRs, but the pipelined iteration 81 us against 88
+// (4,096 envs of two 256x256 cameras and 2,048 envs of mixed sizes measure the
+// same either way).
 template <bool CLIP>
 __global__ void __attribute__((amdgpu_waves_per_eu(7))) raster_setup_kernel(WorldDev W, RasterLaunch L) {
   extern __shared__ __align__(16) unsigned char lds[];
