@@ -85,7 +85,7 @@ __host__ __device__ inline SetupLayout setup_layout(int max_bodies, int max_vert
   L.body = o;   o += 80 * L.nmax;
   L.vis = o;    o += align16(2 * L.vis_cap * (threads / 64));
   L.cvis = o;   o += near_clip ? align16(40 * kClipRecs) : 0;  // near-plane pieces: X[3] Y[3] z[3], primitive
-  L.own = o;    o += 4 * threads;
+  L.own = o;    o += 2 * threads;
   L.pmap = o;   o += align16(max_tris);   // primitive -> body map of the env
   if (o < zone0) o = align16(zone0);
   L.vxy = o;    o += align16(8 * L.vmax);  // (X, Y) per vertex
@@ -364,16 +364,9 @@ __device__ __forceinline__ int wave_incl_add(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return x;
 }
-// (unsigned: 0 is then the maximum's identity, and each step one instruction)
-__device__ __forceinline__ int wave_incl_max(int v) {
-  uint32_t x = (uint32_t)v;
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
-  return (int)x;
+// lanes of the mask m below this one
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
 // Exclusive prefix sum over the workgroup of one value per thread.
@@ -576,7 +569,8 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   float* Vz = (float*)(lds + Lo.vz);
   uint16_t* vis = (uint16_t*)(lds + Lo.vis) + wave * Lo.vis_cap;  // this wave's survivors
   int32_t* cvis = (int32_t*)(lds + Lo.cvis);  // 10 words per piece
-  int32_t* own = (int32_t*)(lds + Lo.own) + 64 * wave;  // this wave's owner marks
+  uint8_t* start = lds + Lo.own + 128 * wave;  // this wave's marks where an owner's pairs start in the window
+  uint8_t* owner = start + 64;                 // and 4 lane of the owners, in lane order
   int32_t* tcount = (int32_t*)(lds + Lo.tiles);
   int32_t* toff = tcount + Lo.tw;
   int32_t* tend = toff + Lo.tw + 1;
@@ -682,8 +676,7 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
       }
     }
     const uint64_t m = __ballot(keep);
-    const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-    if (keep) vis[nmine + below] = (uint16_t)pr;
+    if (keep) vis[nmine + lanes_below(m)] = (uint16_t)pr;
     nmine += __popcll(m);
   }
   };
@@ -830,40 +823,45 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
     if (!binned) continue;
     // Every (triangle, tile of its box) pair takes a lane: pair f belongs to
     // the lane j with off_j <= f < off_j + n_j, found by marking where each
-    // range starts and spreading the marks with a max-scan.  A lane walking
-    // its triangle's tiles one after the other left the others waiting for
-    // the longest: the pass took 28,000 of 70,000 cycles at 540 triangles.
+    // range starts and counting the marks (as the tile pass finds a fragment's
+    // triangle).  A lane walking its triangle's tiles one after the other left
+    // the others waiting for the longest: the pass took 28,000 of 70,000 cycles
+    // at 540 triangles.
     // A pair's entry is rejected if the triangle's edges miss the tile, and
     // flagged if they cover it, where its box in the tile holds more than
     // kSmallMax pixels (the tile kernel goes over the whole tile then; a
     // smaller one is expanded into its box's pixels there anyway).
     const int cnt = q.nx * q.ny;
-    const int incl = wave_incl_add(cnt);
+    int incl = wave_incl_add(cnt);
+    asm("" : "+v"(incl));  // (else off is summed anew from the scan's parts)
     const int pairs = __builtin_amdgcn_readlane(incl, 63);
     const int off = incl - cnt;
     const float rnx = __builtin_amdgcn_rcpf((float)q.nx);
     const int bxx = q.x0 | (q.x1 << 16), byy = q.y0 | (q.y1 << 16);
-    int carry = 0;  // owner + 1 of the pair before the window
+    const uint64_t have = __ballot(cnt > 0);
+    if (cnt > 0) owner[lanes_below(have)] = 4 * lane;
+    int before = -1;  // owners that start before the window, less one
     for (int f0 = 0; f0 < pairs; f0 += 64) {
-      own[lane] = 0;
+      start[lane] = 0;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      if (cnt > 0 && off >= f0 && off < f0 + 64) own[off - f0] = lane + 1;
+      if (cnt > 0 && off >= f0 && off < f0 + 64) start[off - f0] = 1;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      int o = own[lane];
-      if (lane == 0) o = max(o, carry);
-      o = wave_incl_max(o);
-      carry = __builtin_amdgcn_readlane(o, 63);
+      const uint64_t starts = __ballot(start[lane] != 0);
+      const int nth = before + (int)(starts & 1) + lanes_below(starts >> 1);  // marks up to and at this lane
+      before += __popcll(starts);
+      const int j4 = owner[nth];
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       const int f = f0 + lane;
-      const int j = (o - 1) & 63;
-      const int k = f - __shfl(off, j, 64);
-      const int jnx = __shfl(q.nx, j, 64);
+      const auto own = [&](int v) { return __builtin_amdgcn_ds_bpermute(j4, v); };
+      const int k = f - own(off);
+      const int xx = own(bxx), yy = own(byy);
+      const int jx0 = (xx & 0xFFFF) >> tsh, jy0 = (yy & 0xFFFF) >> tsh;
+      const int jnx = (xx >> 16 >> tsh) - jx0 + 1;
       // k / jnx exactly: k < 2^18 tiles and jnx <= 512, so the quotient's
       // fraction is at least 1/1024 away from an integer and its rounding
       // error below 2^-12
-      const int qy = (int)(((float)k + 0.5f) * __int_as_float(__shfl(__float_as_int(rnx), j, 64)));
-      const int tx = __shfl(q.tx0, j, 64) + k - qy * jnx, ty = __shfl(q.ty0, j, 64) + qy;
-      const int xx = __shfl(bxx, j, 64), yy = __shfl(byy, j, 64);
+      const int qy = (int)(((float)k + 0.5f) * __int_as_float(own(__float_as_int(rnx))));
+      const int tx = jx0 + k - qy * jnx, ty = jy0 + qy;
       const int px = tx << tsh, py = ty << tsh;
       const int bx0 = max(xx & 0xFFFF, px), bx1 = min(xx >> 16, px + TS - 1);
       const int by0 = max(yy & 0xFFFF, py), by1 = min(yy >> 16, py + TS - 1);
@@ -874,11 +872,11 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
         int32_t JX[3], JY[3];
 #pragma unroll
         for (int v = 0; v < 3; ++v) {
-          JX[v] = __shfl(t.X[v], j, 64);
-          JY[v] = __shfl(t.Y[v], j, 64);
+          JX[v] = own(t.X[v]);
+          JY[v] = own(t.Y[v]);
         }
-        const bool narrow = (__shfl(flags, j, 64) & 8) != 0;
-        const bool alone = jnx == 1 && __shfl(q.ny, j, 64) == 1;  // a single tile is never missed
+        const bool narrow = (own(flags) & 8) != 0;
+        const bool alone = jnx == 1 && yy >> 16 >> tsh == jy0;  // a single tile is never missed
         if (large && !alone) {
           if (narrow) cls = tile_class<int32_t>(JX, JY, bx0, bx1, by0, by1);
           else cls = tile_class<double>(JX, JY, bx0, bx1, by0, by1);
@@ -887,7 +885,7 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
       if (live && cls != 0) {
         const bool whole = cls == 2 && bx0 == px && by0 == py && bx1 == min(Wd - 1, px + TS - 1) &&
                            by1 == min(Ht - 1, py + TS - 1);
-        const int jr = first + base + j;
+        const int jr = first + base + (j4 >> 2);
         bout[atomicAdd(&tend[ty * ntx + tx], 1)] = (uint16_t)(jr | (whole ? 0x8000 : 0));
       }
     }
@@ -1255,8 +1253,7 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
     LargeRec next = large_rec(m);
     if (F > 0) {
       const uint64_t own = __ballot(a > 0);
-      const int nth = __builtin_amdgcn_mbcnt_hi((uint32_t)(own >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)own, 0));
-      if (a > 0) S.owner[nth] = 4 * lane;
+      if (a > 0) S.owner[lanes_below(own)] = 4 * lane;
     }
     if (F > 0 && !zused) {
 #pragma unroll
