@@ -577,27 +577,46 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
   int32_t* misc = (int32_t*)(lds + Lo.misc);
   const Tpl T = tpl_view(W.tpl, (const uint32_t*)(lds + Lo.tpl));
 
-  // 1. templates, primitive map and bodies
+  // 1. templates, primitive map and bodies.  A thread asks for all it needs of
+  // a body, and for its first quads of the templates and the map, before it
+  // uses any (held together, else the compiler loads and waits one by one: at
+  // 1,024 images 6,600 cycles of 64,500).
   for (int b = tid; b < n; b += nthr) {
     const int g = ed.body_off + b;
-    float R[9];
-    quat_rot(st[QW * cap + g], st[QX * cap + g], st[QY * cap + g], st[QZ * cap + g], R, 1);
-    B.R[b] = make_float4(R[0], R[1], R[2], st[PX * cap + g]);
-    B.R[S + b] = make_float4(R[3], R[4], R[5], st[PY * cap + g]);
-    B.R[2 * S + b] = make_float4(R[6], R[7], R[8], st[PZ * cap + g]);
+    float s7[7] = {st[QW * cap + g], st[QX * cap + g], st[QY * cap + g], st[QZ * cap + g],
+                   st[PX * cap + g], st[PY * cap + g], st[PZ * cap + g]};
     const float* bx = W.box + 6 * (int64_t)g;
-    B.e[b] = make_float4(bx[0], bx[1], bx[2], 0.0f);
-    B.id[b] = make_int4(W.vert_base[g], W.prim_base[g], W.albedo[g], W.type[g]);
-  }
-  {
-    const int4* src = (const int4*)W.tpl->data;
-    int4* dst = (int4*)(lds + Lo.tpl);
-    for (int i = tid; i < L.tpl_words / 4; i += nthr) dst[i] = src[i];
-    const int4* ps = (const int4*)(W.prim_body + ed.prim_map);
-    int4* pd = (int4*)(lds + Lo.pmap);
-    for (int i = tid; i < (ntris + 15) / 16; i += nthr) pd[i] = ps[i];
+    float x = bx[0], y = bx[1], z = bx[2];
+    int vb = W.vert_base[g], pb = W.prim_base[g], al = W.albedo[g], ty = W.type[g];
+    asm volatile("" : "+v"(s7[0]), "+v"(s7[1]), "+v"(s7[2]), "+v"(s7[3]), "+v"(s7[4]), "+v"(s7[5]), "+v"(s7[6]),
+                      "+v"(x), "+v"(y), "+v"(z), "+v"(vb), "+v"(pb), "+v"(al), "+v"(ty));
+    float R[9];
+    quat_rot(s7[0], s7[1], s7[2], s7[3], R, 1);
+    B.R[b] = make_float4(R[0], R[1], R[2], s7[4]);
+    B.R[S + b] = make_float4(R[3], R[4], R[5], s7[5]);
+    B.R[2 * S + b] = make_float4(R[6], R[7], R[8], s7[6]);
+    B.e[b] = make_float4(x, y, z, 0.0f);
+    B.id[b] = make_int4(vb, pb, al, ty);
   }
   int body_next = gvmap[min(tid, ed.n_verts - 1)];
+  {
+    const int4* tsrc = (const int4*)W.tpl->data;
+    const int4* psrc = (const int4*)(W.prim_body + ed.prim_map);
+    int4* tdst = (int4*)(lds + Lo.tpl);
+    int4* pdst = (int4*)(lds + Lo.pmap);
+    const int nt = L.tpl_words / 4, np = (ntris + 15) / 16;  // at least 1 each
+    const int t0 = min(tid, nt - 1), t1 = min(tid + nthr, nt - 1), p0 = min(tid, np - 1), p1 = min(tid + nthr, np - 1);
+    int4 a = tsrc[t0], b = tsrc[t1], c = psrc[p0], d = psrc[p1];
+    asm volatile("" : "+v"(a.x), "+v"(a.y), "+v"(a.z), "+v"(a.w), "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w),
+                      "+v"(c.x), "+v"(c.y), "+v"(c.z), "+v"(c.w), "+v"(d.x), "+v"(d.y), "+v"(d.z), "+v"(d.w));
+    // (threads past the end write the last quad again)
+    tdst[t0] = a;
+    tdst[t1] = b;
+    pdst[p0] = c;
+    pdst[p1] = d;
+    for (int i = tid + 2 * nthr; i < nt; i += nthr) tdst[i] = tsrc[i];
+    for (int i = tid + 2 * nthr; i < np; i += nthr) pdst[i] = psrc[i];
+  }
   const bool tiled = ntiles <= Lo.tw;
   if (tid == 0) misc[3] = misc[5] = 0;
   if (tiled)
