@@ -929,9 +929,9 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
 // Held to 72 VGPRs (seven waves per SIMD), so that a slot a tile wave leaves can
 // take one of its waves when the render overlaps the next step.  Bound by
 // latency: at 1,024 images of 540 visible triangles (128 threads each) it takes
-// 37.9 us alone, 37.1 at 80 VGPRs, but the pipelined iteration 81 us against 88
-// (4,096 envs of two 256x256 cameras and 2,048 envs of mixed sizes measure the
-// same either way).
+// 36.7 us; when it took 37.9, and 37.1 at 80 VGPRs, the pipelined iteration was
+// 81 us with the one and 88 with the other (now 77; 4,096 envs of two 256x256
+// cameras and 2,048 envs of mixed sizes measure the same either way).
 template <bool CLIP>
 __global__ void __attribute__((amdgpu_waves_per_eu(7))) raster_setup_kernel(WorldDev W, RasterLaunch L) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -1127,7 +1127,8 @@ constexpr uint64_t kNoKey = 0xFFFFFFFFFF000000ull;
 // words of it, a large triangle's record comes by scalar loads that no branch
 // surrounds and its edge values from integers where they fit.  At 8,192 images
 // of 256x256 (64 bodies) 393 -> 353 vector instructions per tile, 1,985 ->
-// 1,800 us a launch; at 1,024 of 128x128 (32 bodies) 65.8 -> 56.
+// 1,800 us a launch (1,635 in runs of tiles); at 1,024 of 128x128 (32 bodies)
+// 65.8 -> 56.
 template <bool DBG, bool SMOOTH, int TS, class Src>
 __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam, const Src& src, bool binned,
                                             int k0, int k1, int tx, int ty, TileWaveLDS<TS>& S, int32_t* cov,
