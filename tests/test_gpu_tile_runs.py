@@ -14,9 +14,9 @@ from tests.gpu_util import say
 pytestmark = pytest.mark.gpu
 
 
-# 8-pixel tiles: 160 images of up to 256 tiles, 36,000 in all, so that the
-# first ones (the largest, then by id) are in runs of 2, 4 and 8 tiles and the
-# last in single ones; rows of 1, 2, 3, 5, 9, 13, 15 and 16 tiles
+# 8-pixel tiles: 180 images of up to 256 tiles, over 40,000 in all, so that the
+# first ones (the largest, then by id) are in runs of 2 or 8 tiles and the last
+# 28,672 tiles in single ones; rows of 1, 2, 3, 5, 9, 13, 15 and 16 tiles
 @pytest.mark.parametrize("waves", [1, 2, 4])
 @pytest.mark.parametrize("smooth", [False, True])
 def test_tile_runs(waves, smooth):
