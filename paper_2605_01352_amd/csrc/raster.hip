@@ -1068,8 +1068,14 @@ __device__ __forceinline__ uint32_t smooth_color(const int4* grec, const float4*
 // kernel): 16-byte records and bins in LDS, the corners read from the
 // vertex cache and the pixel box recomputed, so that fetch() returns the
 // four quads of the 64-byte record.
+// kScalar: a wave may read one record with scalar loads, which is for records
+// that an earlier kernel wrote (the tile kernel).  Scalar loads neither see nor
+// wait for vector stores of the kernel they are in, not even across a workgroup
+// barrier, so the fused kernel, which writes the records it reads, takes them
+// from its lanes' registers.
+template <bool kScalar>
 struct GlobalRecs {
-  static constexpr bool kUniform = true;  // a wave can read one record with scalar loads
+  static constexpr bool kUniform = kScalar;
   const int4* rec;
   const uint16_t* bins;
   __device__ __forceinline__ int bin(int k) const { return bins[k]; }
@@ -1517,7 +1523,7 @@ __global__ void __launch_bounds__(64 * TW)
   const int2* table = (const int2*)(rs + 64) + (ty * ntx + tx);
   int2 te = uniform_ld(table + wave), next = uniform_ld(table + min(wave + TW, last));
   const bool binned = hdr.y != 0;
-  const GlobalRecs src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
+  const GlobalRecs<true> src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
   for (int t = wave;; t += TW) {
     const int2 after = uniform_ld(table + min(t + 2 * TW, last));
     const int k0 = binned ? te.x : 0, k1 = binned ? te.x + te.y : hdr.x;
@@ -1534,6 +1540,7 @@ template <bool DBG, int TS, class Src>
 __device__ __forceinline__ void fused_tiles(const WorldDev& W, const CamDev& cam, const Src& src, bool binned,
                                             int nrec, const int32_t* toff, const int32_t* tend, int wave,
                                             int nw, TileWaveLDS<TS>* S, int32_t* C, const unsigned char* rs) {
+  static_assert(!Src::kUniform, "the records are written by this kernel");
   const int ntx = (cam.w + TS - 1) / TS, ntiles = ntx * ((cam.h + TS - 1) / TS);
   for (int t = wave; t < ntiles; t += nw) {
     const int k0 = binned ? toff[t] : 0, k1 = binned ? tend[t] : nrec;
@@ -1580,7 +1587,7 @@ __global__ void __launch_bounds__(1024) raster_fused_kernel(WorldDev W, RasterLa
                         (const uint16_t*)(lds + Lo.lbin), cam.w, cam.h};
       fused_tiles<DBG, TS>(W, cam, src, binned, nrec, toff, tend, wave, nw, S, C, rs);
     } else {
-      const GlobalRecs src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
+      const GlobalRecs<false> src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
       fused_tiles<DBG, TS>(W, cam, src, binned, nrec, toff, tend, wave, nw, S, C, rs);
     }
     if (L.persistent == 0) return;
