@@ -700,8 +700,10 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       // position: a pair in contact range now was then within the sum of
       // its radii plus half the margin, and the other half covers rounding
       // (positions under 1000 m, where it is below 0.1 mm).  The retest is
-      // the same expression, so the candidate set is the same bits.
-      const bool use_sup = SUP && n > 32;
+      // the same expression, so the candidate set is the same bits.  With the
+      // grid forced, this branch is the fallback of a substep with a far cell:
+      // substep 0 may have run on the grid and built no superset.
+      const bool use_sup = SUP && n > 32 && !use_grid;
       bool retest = false;
       if constexpr (SUP) {
         bool risky = true;
