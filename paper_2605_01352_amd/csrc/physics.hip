@@ -557,9 +557,13 @@ __device__ __forceinline__ bool env_any(bool v) {
   }
 }
 
-template <int N, bool FR, bool EE, bool SUP>
-__device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc, int env,
+// RETRY: an env whose pairs pass the capacities leaves without a trace (its
+// state is written at the end only) and the caller steps it again with more;
+// else it is flagged.  Returns whether the env left so.
+template <int N, bool RETRY, bool FR, bool EE, bool SUP>
+__device__ bool step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc, int env,
                          int parity, int nsteps, int broadphase) {
+  static_assert(!RETRY || N == 64, "the wave leaves as one, past no barrier");
   constexpr int NW = PhysLDS<N>::NW;
   // Lanes of this env: N consecutive threads.  At N = 32 two envs share a
   // wave, each in one half: their compactions count within the half, and
@@ -590,7 +594,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
   EnvDev ed{};
   if (env >= 0) ed = uniform_copy(W.envs + env);  // a scalar load where the env is the wave's
   const int n = ed.n_bodies;
-  if (N >= 64 && n <= 0) return;  // all of the env's waves; a half-wave env of no bodies does nothing below
+  if (N >= 64 && n <= 0) return false;  // all of the env's waves; a half-wave env of no bodies does nothing below
   const int b0 = ed.body_off;
   const bool own = tid < n;
   const int64_t cap = W.cap_bodies;
@@ -906,7 +910,10 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
         }
       }
     }
-    if (ctotal > PhysLDS<N>::CAPC) bad = true;
+    if (ctotal > PhysLDS<N>::CAPC) {
+      if constexpr (RETRY) return true;
+      bad = true;
+    }
     env_sync<N>();
     // 4a. the pairs with a sphere and the spheres on the ground, one per
     // lane; box pairs are queued.  A pair in contact takes the next free
@@ -1035,7 +1042,10 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     }
     env_sync<N>();
     if (N > 64) kcnt = s.kcnt;
-    if (kcnt > PhysLDS<N>::CAPK) bad = true;
+    if (kcnt > PhysLDS<N>::CAPK) {
+      if constexpr (RETRY) return true;
+      bad = true;
+    }
     // 5. gather in sorted pair order, then the ground, then integrate.
     // Candidates are taken four at a time so that each level of lookups
     // (candidate index, slot, sums) issues its loads together.
@@ -1183,6 +1193,7 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     if (!fin) raise_flag(W, env, kFlagNonFinite);
   }
   if (bad && tid == 0 && env >= 0) raise_flag(W, env, kFlagContactOverflow);
+  return false;
 }
 
 // FR: friction; EE: edge-edge points of box pairs; SUP: the step's candidate
@@ -1191,7 +1202,12 @@ __device__ void step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
 // threads holds two envs at N = 32, one at N = 64.  At N = 128 a workgroup of
 // two waves holds one env of more than 64 bodies (the list's first n_big, which
 // the list's order puts in front) or two smaller ones, a wave each: with two
-// waves for every env, 1,500 envs of 4 to 128 bodies took 107 us a step.
+// waves for every env, 1,500 envs of 4 to 128 bodies took 107 us a step.  A
+// smaller env that passes the pair capacities of one wave is stepped again by
+// both with theirs, so that every env of a launch has those of its largest.
+// (Room for them in the one-wave layout, 48 KB for two envs in place of 37 KB
+// and three workgroups per CU in place of four: 4 steps of those 1,500 envs and
+// their load 809 us against 689.)
 template <int N, bool FR, bool EE, bool SUP>
 __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, PhysConsts pc, PhysLaunch L) {
   constexpr int P = N == 64 ? 1 : 2;  // envs per workgroup (N = 128: beyond the first n_big)
@@ -1200,7 +1216,7 @@ __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, Ph
     PhysLDS<N> big;
     PhysLDS<kSmall> small[P];
   } sh;
-  __shared__ int32_t next;
+  __shared__ int32_t next, again[2];
   // The step is latency-bound; a higher issue priority shortens it when it
   // shares CUs with the render phase.
   switch (L.prio) {
@@ -1222,14 +1238,24 @@ __global__ __launch_bounds__(N < 64 ? 64 : N) void physics_kernel(WorldDev W, Ph
       __syncthreads();
     }
     if (wi >= items) return;
-    if (N == 128 && wi < big) {
-      step_env<N, FR, EE, SUP>(sh.big, W, pc, uniform_ld(L.work + wi), L.parity, L.nsteps, L.broadphase);
-    } else {
+    const bool two = N == 128 && wi < big;  // an env for both waves
+    const int first = two ? wi : big + P * (wi - big);
+    if (!two) {
       int sub = P == 1 ? 0 : (int)threadIdx.x / kSmall;
       if (N == 128) sub = __builtin_amdgcn_readfirstlane(sub);
-      const int item = big + P * (wi - big) + sub;
-      step_env<kSmall, FR, EE, SUP>(sh.small[sub], W, pc, item < L.n_work ? uniform_ld(L.work + item) : -1, L.parity,
-                                    L.nsteps, L.broadphase);
+      const int item = first + sub;
+      const bool left = step_env<kSmall, N == 128, FR, EE, SUP>(sh.small[sub], W, pc,
+                                                                item < L.n_work ? uniform_ld(L.work + item) : -1,
+                                                                L.parity, L.nsteps, L.broadphase);
+      if (N == 128) again[sub] = left;
+    }
+    if constexpr (N == 128) {
+      __syncthreads();  // the two-wave layout takes the LDS of both envs
+      for (int q = 0; q < (two ? 1 : P); ++q) {
+        if (!two && __builtin_amdgcn_readfirstlane(again[q]) == 0) continue;
+        step_env<N, false, FR, EE, SUP>(sh.big, W, pc, uniform_ld(L.work + first + q), L.parity, L.nsteps, L.broadphase);
+        __syncthreads();
+      }
     }
     if (!L.persistent) return;
     __syncthreads();  // the next env reuses the LDS
