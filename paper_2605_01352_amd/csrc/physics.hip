@@ -110,7 +110,7 @@ struct PhysLDS {
   float kres[9][CAPK];    // SF xyz, Ti xyz, Tj xyz of each pair in contact
   float estage[9][N / 16];        // terms of the edge-edge point of each 16-lane group
   float gres[6][N];       // ground force and torque of each body
-  int32_t scan[NW + 1];
+  uint32_t scan[NW + 1];
   float red[NW];
   int32_t kcnt, ncc;
 };
@@ -121,50 +121,50 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 // Exclusive prefix sum over the workgroup (thread order); *total gets the sum.
 // Inclusive wave64 prefix sum with DPP row shifts and row broadcasts (VALU
 // only); lanes reading outside their row take 0.
-__device__ __forceinline__ int wave_incl_add(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+__device__ __forceinline__ uint32_t wave_incl_add(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return x;
 }
 
 // Inclusive prefix sum within each 32-lane half of the wave (row shifts and
 // the broadcast of row 0 into row 1, row 2 into row 3).
-__device__ __forceinline__ int half_incl_add(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+__device__ __forceinline__ uint32_t half_incl_add(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
   return x;
 }
 
 // Exclusive prefix sum over the N lanes of one env (thread order); *total
 // gets the env's sum.
 template <int N>
-__device__ __forceinline__ int block_excl_scan(int v, int32_t* tmp, int* total) {
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
   constexpr int NW = N > 64 ? N / 64 : 1;
   const int lane = lane_id();
   if (N == 32) {
-    const int x = half_incl_add(v);
+    const uint32_t x = half_incl_add(v);
     *total = __shfl(x, (lane & 32) + 31, 64);
     return x - v;
   }
-  const int x = wave_incl_add(v);
+  const uint32_t x = wave_incl_add(v);
   if (NW == 1) {
-    *total = __builtin_amdgcn_readlane(x, 63);
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
     return x - v;
   }
   const int wv = threadIdx.x >> 6;
   if (lane == 63) tmp[wv] = x;
   __syncthreads();
-  int base = 0, tot = 0;
+  uint32_t base = 0, tot = 0;
 #pragma unroll
   for (int k = 0; k < NW; ++k) {
-    int t = tmp[k];
+    const uint32_t t = tmp[k];
     if (k < wv) base += t;
     tot += t;
   }
@@ -885,17 +885,19 @@ __device__ bool step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
     }
     // 3. compaction: one scan places the candidate rows in a list sorted by
     // (i, j) and both kinds of ground contact in theirs (candidates in the
-    // low 16 bits, at most N (N - 1) / 2; then 8 bits each)
+    // low 16 bits, at most N (N - 1) / 2; then 8 bits each, unsigned: 128 cubes
+    // on the ground reach the top bit)
     int ctotal, ngs, ngc;
     {
-      int total;
-      const int at = block_excl_scan<N>(ccount | (gsph ? 1 << 16 : 0) | (gcube ? 1 << 24 : 0), s.scan, &total);
-      const int cstart = at & 0xFFFF;
-      ctotal = total & 0xFFFF;
-      ngs = (total >> 16) & 0xFF;
-      ngc = (int)((uint32_t)total >> 24);
+      uint32_t total;
+      const uint32_t at =
+          block_excl_scan<N>((uint32_t)ccount | (gsph ? 1u << 16 : 0u) | (gcube ? 1u << 24 : 0u), s.scan, &total);
+      const int cstart = (int)(at & 0xFFFF);
+      ctotal = (int)(total & 0xFFFF);
+      ngs = (int)((total >> 16) & 0xFF);
+      ngc = (int)(total >> 24);
       if (gsph) s.gsl[(at >> 16) & 0xFF] = (uint8_t)tid;
-      if (gcube) s.gcl[(uint32_t)at >> 24] = (uint8_t)tid;
+      if (gcube) s.gcl[at >> 24] = (uint8_t)tid;
       s.cstart[tid] = cstart;
       int pos = cstart;
 #pragma unroll
@@ -1152,10 +1154,10 @@ __device__ bool step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       int cnt = gc ? 1 : 0;
       const int c0 = s.cstart[tid];
       for (int c = c0; c < c0 + ccount; ++c) cnt += (c < PhysLDS<N>::CAPC && s.kslot[c] != kNoSlot) ? 1 : 0;
-      int tot;
-      const int off = block_excl_scan<N>(cnt, s.scan, &tot);
+      uint32_t tot;
+      const int off = (int)block_excl_scan<N>((uint32_t)cnt, s.scan, &tot);
       int32_t* dst = W.contacts + ((int64_t)(env < 0 ? 0 : env) * pc.substeps + sub_i) * (1 + 2 * W.pair_cap);
-      if (tid == 0 && env >= 0) dst[0] = tot;
+      if (tid == 0 && env >= 0) dst[0] = (int32_t)tot;
       if (own) {
         int pos = off, c = c0;
 #pragma unroll
