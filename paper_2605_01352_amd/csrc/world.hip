@@ -1889,9 +1889,20 @@ static int fetch_depth_metric(vuda_world* w, int32_t lo, int32_t hi, float* dst,
   return w->check_flags();
 }
 
+// Whether p is memory of the device, which its kernels can write: not of another
+// GPU (which may not be open to this one), not the host's, and on whole words.
+static bool kernel_writable(const void* p, int device) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == device && (uintptr_t)p % 4 == 0;
+}
+
 // State rows of envs [lo, hi) from each env's current buffer, on the null
 // stream, which the caller has ordered after the world's work: straight into
-// dst on the device, or into pinned memory and from there to a host dst.
+// a dst in this GPU's memory, else into pinned memory and from there to dst.
 // One kernel turns the component arrays into rows; 13 copies to the host and
 // a transpose there measured 0.5 ms at 1,024 envs of 32 bodies.
 int vuda_world::fetch_state(int32_t lo, int32_t hi, float* dst, bool on_device) {
@@ -1902,7 +1913,8 @@ int vuda_world::fetch_state(int32_t lo, int32_t hi, float* dst, bool on_device) 
   if (total == 0) return VUDA_OK;
   float* rows = dst;
   int64_t room = total;
-  if (!on_device) {
+  const bool direct = on_device && kernel_writable(dst, device);
+  if (!direct) {
     int rc = reserve_pin(kRowBytes * (size_t)total);
     if (rc) return rc;
     rows = (float*)pin;
@@ -1911,7 +1923,10 @@ int vuda_world::fetch_state(int32_t lo, int32_t hi, float* dst, bool on_device) 
   int64_t pos = 0, at = 0;  // bodies handed out, bodies waiting in `rows`
   const auto flush = [&]() -> int {
     HIPCHK(hipStreamSynchronize(nullptr));
-    if (!on_device) memcpy(dst + pos * kStateComps, rows, kRowBytes * (size_t)at);
+    if (on_device && !direct)
+      HIPCHK(hipMemcpy(dst + pos * kStateComps, rows, kRowBytes * (size_t)at, hipMemcpyHostToDevice));
+    else if (!direct)
+      memcpy(dst + pos * kStateComps, rows, kRowBytes * (size_t)at);
     pos += at;
     at = 0;
     return VUDA_OK;
