@@ -262,7 +262,10 @@ int vuda_wait(vuda_world* w, int32_t phase);
  * Copy results of envs [env_lo, env_hi) into dst (`dst_bytes` long; host
  * memory, or device memory if dst_on_device).  Stream-ordered after all
  * enqueued work, and synchronous on return.  The layout is given with the
- * VUDA_FETCH_* selectors; fetch size queries: vuda_fetch_bytes.
+ * VUDA_FETCH_* selectors; fetch size queries: vuda_fetch_bytes.  State rows
+ * for the host, here and in vuda_load_state, pass through pinned host memory
+ * that the world keeps (allocated when first needed and grown as needed, 16 MiB
+ * at most, which larger transfers go through in pieces).
  *
  * VUDA_FETCH_DEPTH_METRIC converts the 24-bit depth on the GPU: a camera
  * whose view-projection rows satisfy row2 = alpha row3 + beta e4 (every

@@ -1796,23 +1796,28 @@ static void state_runs(const vuda_world* w, int32_t lo, int32_t hi, std::vector<
   }
 }
 
-// Pinned staging of state rows: enough for `bytes`, at most kPinMax.
-constexpr size_t kPinMax = (size_t)16 << 20;
+// Pinned staging of state rows: room for `bytes`, or for less (kPinMax at most,
+// and what the host gives): its users go through it in pieces.  It grows at
+// least twofold, so that growing requests seldom allocate, and a larger one is
+// at hand before the old one goes.  VUDA_ENOMEM only without any.
+constexpr size_t kPinMin = (size_t)4 << 10, kPinMax = (size_t)16 << 20;
 constexpr size_t kRowBytes = 4 * kStateComps;
 
 int vuda_world::reserve_pin(size_t bytes) {
-  bytes = std::min(bytes, kPinMax);
-  if (bytes <= pin_cap) return VUDA_OK;
-  if (pin) HIPCHK(hipHostFree(pin));
-  pin = nullptr;
-  pin_cap = 0;
-  hipError_t e = hipHostMalloc((void**)&pin, bytes, hipHostMallocDefault);
-  if (e != hipSuccess) {
+  if (std::min(bytes, kPinMax) <= pin_cap) return VUDA_OK;
+  hipError_t e = hipSuccess;
+  for (size_t n = std::min(std::max({bytes, 2 * pin_cap, kPinMin}), kPinMax); n > pin_cap && n >= kPinMin; n /= 2) {
+    unsigned char* p = nullptr;
+    e = hipHostMalloc((void**)&p, n, hipHostMallocDefault);
+    if (e == hipSuccess) {
+      if (pin) (void)hipHostFree(pin);
+      pin = p;
+      pin_cap = n;
+      return VUDA_OK;
+    }
     (void)hipGetLastError();
-    return fail(VUDA_ENOMEM, "hipHostMalloc(%zu): %s", bytes, hipGetErrorString(e));
   }
-  pin_cap = bytes;
-  return VUDA_OK;
+  return pin ? VUDA_OK : fail(VUDA_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
 }
 
 // Metric depth of the cameras of the active envs in [lo, hi), in fetch
@@ -1875,8 +1880,7 @@ static int fetch_depth_metric(vuda_world* w, int32_t lo, int32_t hi, float* dst,
     out = w->metric_buf;
   }
   const size_t cam_bytes = sizeof(MetricCam) * cams.size();
-  int rc = w->reserve_pin(cam_bytes);
-  if (rc) return rc;
+  (void)w->reserve_pin(cam_bytes);
   if (cam_bytes <= w->pin_cap) {
     memcpy(w->pin, cams.data(), cam_bytes);
     HIPCHK(hipMemcpyAsync(w->metric_cams, w->pin, cam_bytes, hipMemcpyHostToDevice, nullptr));
