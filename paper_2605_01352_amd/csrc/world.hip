@@ -1353,13 +1353,18 @@ extern "C" int vuda_render(vuda_world* w, int32_t lo, int32_t hi) {
 // scan that found none; only then are the flags read back.  (A copy of the
 // flags at every wait and fetch measured 15-20 us, more than a small batch's
 // frame takes to render.)  The word is cleared before the scan: a flag that a
-// running kernel raises meanwhile raises it again.
+// running kernel raises meanwhile raises it again, and a scan that fails leaves
+// it raised.
 int vuda_world::check_flags() {
   if (__atomic_load_n(any_flag, __ATOMIC_ACQUIRE) == 0) return VUDA_OK;
-  __atomic_store_n(any_flag, 0u, __ATOMIC_SEQ_CST);
   uint32_t any = 0;
   std::vector<uint32_t> fl(cap_envs);
-  HIPCHK(copy_now(fl.data(), dev.env_flags, 4 * (size_t)cap_envs, hipMemcpyDeviceToHost));
+  __atomic_store_n(any_flag, 0u, __ATOMIC_SEQ_CST);
+  const hipError_t err = copy_now(fl.data(), dev.env_flags, 4 * (size_t)cap_envs, hipMemcpyDeviceToHost);
+  if (err != hipSuccess) {
+    __atomic_store_n(any_flag, 1u, __ATOMIC_RELEASE);
+    return hip_fail(err, "flags");
+  }
   int first = -1;
   for (int32_t e = 0; e < cap_envs; ++e) {
     if (fl[e] && first < 0) first = e;
