@@ -847,20 +847,36 @@ void vuda_world::invalidate_lists() {
 
 // Tiles of a row that one tile-kernel job takes, on `waves` waves, when `left`
 // tiles (these among them) are not yet in a job.  A wave that goes on to the
-// next tile of a row has its image's bookkeeping at hand and the tile's bin
-// range on its way, where a new one waits for three rounds of loads.  The last
-// four tiles per wave slot (7 per SIMD) go one to a wave, so that the launch
-// ends evenly; a run stays shorter than the row, else one job holds a whole row
-// of the ground or of the sky; and a single wave takes two at most (images of
-// 200x200: 118 us a launch with two, 127 with four).  Tile pass in us, one tile
-// a wave and so: 1,024 images of 128x128 57.1 and 56.5, 2,048 129 and 115.5,
-// 2,048 of 256x256 452 and 386, 8,192 of 256x256 1,816 and 1,653, 48 of 640x480
-// 83.1 and 75.6; whole rows: 2,048 of 128x128 128.8, 16,384 of 64x64 354 where
-// one tile a wave takes 332.
-static int32_t tile_run(int32_t waves, int32_t row, int64_t left) {
+// next tile of a row has its image's bookkeeping at hand, where a new one waits
+// for three rounds of loads; a job of several tiles is also a coarser piece of
+// the launch.  Tile pass in us, one tile a wave and runs, two waves a workgroup
+// (flat; smooth shading):
+//   tiles of 16, rows of 13 and more: 1,500 images of 200x200 194 and 186; 316
+//     and 321.  1,024 of 256x256 212 and 195; 328 and 326.  100 of 640x480 61
+//     and 52; 107 and 101.
+//   rows of 10 and 12, where a run of 8 leaves a short end: 1,500 of 150x150 112
+//     and 126; 202 and 221.  1,500 of 180x150 143 and 138; 237 and 250.  So none.
+//   shorter rows, in runs of 4: 2,500 of 100x100 84 and 81; 164 and 163.  2,048 of
+//     128x128 95 and 95; 173 and 177, and beside physics 2,048 envs of 64x64 to
+//     256x256 an iteration of 265 and 262.  One wave a workgroup, in runs of 2:
+//     2,048 of 128x128 97 and 105; 175 and 184.  So not on one wave.
+//   tiles of 8, whose bookkeeping is most of their work: 8,192 of 64x64 236 and
+//     204; 317 and 287.  2,048 of 64x64 to 256x256 393 and 311; 487 and 422.
+//   tiles of 32: 2,048 of 256x256 440 and 413, but 837 and 842; 500 of 560x100
+//     in four waves 65 and 72; 125 and 155.  So none.
+// The last four tiles per wave slot go one to a wave, so that the launch ends
+// evenly: the slots of the whole chip at seven waves per SIMD, which is the
+// 16-pixel kernel's count (8-pixel tiles have eight; with 32,768 or 65,536
+// single ones their pass measured the same or up to 2% more; on a stream with a
+// CU mask the even end is longer than it need be).  A run stays shorter than the
+// row, else one job holds a whole row of the ground or of the sky; and a single
+// wave takes two at most (images of 200x200: 118 us a launch with two, 127 with
+// four).
+static int32_t tile_run(int32_t waves, int32_t shift, int32_t row, int64_t left) {
   constexpr int64_t kEnd = 4 * 7 * 4 * 256;
+  if (left <= kEnd || shift == 5 || (shift == 4 && row <= 12 && (row > 8 || waves == 1))) return waves;
   int32_t per = 1;
-  while (left > kEnd && per < (waves == 1 ? 2 : 4) && 2 * per * waves <= 8 && 2 * per * waves < row) per *= 2;
+  while (per < (waves == 1 ? 2 : 4) && 2 * per * waves <= 8 && 2 * per * waves < row) per *= 2;
   return per * waves;
 }
 
@@ -939,13 +955,21 @@ int vuda_world::get_list(int phase, int32_t lo, int32_t hi, const WorkList** out
       const int ts = 1 << tune.tile_shift;
       const int32_t ntx = (cd.w + ts - 1) >> tune.tile_shift, nty = (cd.h + ts - 1) >> tune.tile_shift;
       if (ids[i] > kJobCamMask) return fail(VUDA_EINVAL, "camera id %d beyond the tile job's range", ids[i]);
-      const int32_t run = tile_run(tune.tile_waves, ntx, left);
+      const int32_t run = tile_run(tune.tile_waves, tune.tile_shift, ntx, left);
       left -= (int64_t)ntx * nty;
-      for (int32_t ty = 0; ty < nty; ++ty)
-        for (int32_t tx = 0; tx < ntx; tx += run) {
+      const auto jobs = [&](int32_t tx0, int32_t tx1, int32_t ty) {
+        for (int32_t tx = tx0; tx < tx1; tx += run) {
           const int32_t n = std::min(run, ntx - tx);
           per[i % kXcd].push_back(make_int2(ids[i] | ((n - 1) << kJobTilesShift), tx | (ty << 16)));
         }
+      };
+      // Runs: the whole ones of the image, then what is left of its rows.  The
+      // hardware hands workgroups to the engines of an XCD in turn, and long
+      // and short ones in alternation would give some engines only long ones
+      // (1,500 images of 200x200, smooth: 361 us row by row, 321 like this).
+      const int32_t whole = run > tune.tile_waves ? ntx / run * run : ntx;
+      for (int32_t ty = 0; ty < nty; ++ty) jobs(0, whole, ty);
+      for (int32_t ty = 0; ty < nty; ++ty) jobs(whole, ntx, ty);
     }
     size_t len = 0;
     for (auto& v : per) len = std::max(len, v.size());
