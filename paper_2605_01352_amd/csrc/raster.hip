@@ -1532,15 +1532,23 @@ __global__ void __launch_bounds__(64 * TW)
   // edge, so its entries are read before the header says the image is binned
   const int2 hdr = uniform_ld((const int2*)rs);
   const int2* table = (const int2*)(rs + 64) + (ty * ntx + tx);
-  int2 te = uniform_ld(table + wave), next = uniform_ld(table + min(wave + TW, last));
+  // The bin ranges of a run's next two tiles are asked for ahead of their turn,
+  // but for 8-pixel tiles, whose single ones lost more by the extra loads (a wait
+  // for a scalar load takes in every one under way) than runs gained: 5,600
+  // images of 64x64 in single tiles 144 us ahead and 137 not, in runs 127 and 120;
+  // 400 of 256x256 153 and 143, 125 and 119.
+  constexpr bool kAhead = TS > 8;
+  int2 te = uniform_ld(table + wave), next = te;
+  if constexpr (kAhead) next = uniform_ld(table + min(wave + TW, last));
   const bool binned = hdr.y != 0;
   const GlobalRecs<true> src{(const int4*)(rs + cam.rs_recs), (const uint16_t*)(rs + cam.rs_bins)};
   for (int t = wave;; t += TW) {
-    const int2 after = uniform_ld(table + min(t + 2 * TW, last));
+    int2 after = te;
+    if constexpr (kAhead) after = uniform_ld(table + min(t + 2 * TW, last));
     const int k0 = binned ? te.x : 0, k1 = binned ? te.x + te.y : hdr.x;
     raster_tile<DBG, SMOOTH, TS>(W, cam, src, binned, k0, k1, tx + t, ty, S[wave], DBG ? C[wave] : nullptr, rs);
     if (t + TW > last) return;
-    te = next;
+    te = kAhead ? next : uniform_ld(table + t + TW);
     next = after;
   }
 }
