@@ -1022,7 +1022,9 @@ __device__ bool step_env(PhysLDS<N>& s, const WorldDev& W, const PhysConsts& pc,
       s.stage[6][tid] = pq.tj.x; s.stage[7][tid] = pq.tj.y; s.stage[8][tid] = pq.tj.z;
       // edge-edge point (after the 16 vertex points in the pair's order)
       bool ehit = false;
-      if constexpr (EE) ehit = edge_point<N, FR>(s, pair, lane & 15, lane, i, j, pc);
+      // (not where the wave holds ground cubes alone)
+      if constexpr (EE)
+        if (__ballot(pair)) ehit = edge_point<N, FR>(s, pair, lane & 15, lane, i, j, pc);
       const uint64_t hm = __ballot(hit && pair);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       const int g0 = lane & 48;  // the pair's first lane in the wave
