@@ -927,13 +927,19 @@ __device__ void setup_image(unsigned char* lds, const SetupLayout& Lo, const Wor
 }
 
 // Held to 72 VGPRs (seven waves per SIMD), so that a slot a tile wave leaves can
-// take one of its waves when the render overlaps the next step.  Bound by
-// latency: at 1,024 images of 540 visible triangles (128 threads each) it takes
-// 36.7 us; when it took 37.9, and 37.1 at 80 VGPRs, the pipelined iteration was
-// 81 us with the one and 88 with the other (now 77; 4,096 envs of two 256x256
-// cameras and 2,048 envs of mixed sizes measure the same either way).
+// take one of its waves when the render overlaps the next step.  The price is 13
+// VGPRs spilled to scratch, and 112 SGPRs to lanes of VGPRs (299 of its 1,544
+// vector instructions move them).  Bound by latency: at 1,024 images of 540
+// visible triangles (128 threads each) it takes 36.7 us; when it took 37.9, and
+// 37.1 at 80 VGPRs, the pipelined iteration was 81 us with the one and 88 with the
+// other (now 77; 4,096 envs of two 256x256 cameras and 2,048 envs of mixed sizes
+// measure the same either way).  With the cut of the near plane seven waves spill
+// 22 VGPRs and 133 SGPRs and lose, so it has 80 (six waves): the setup of 1,024
+// images of 64x64, 8 bodies, 18.4 us against 19.8 with 72; 1,920 of 256x256, 20
+// bodies, 45.6 against 49.9; the pipelined iteration of 1,024 envs of 32 bodies
+// 76.4 against 78.8, of 2,048 envs of mixed sizes 213 and 228.
 template <bool CLIP>
-__global__ void __attribute__((amdgpu_waves_per_eu(7))) raster_setup_kernel(WorldDev W, RasterLaunch L) {
+__global__ void __attribute__((amdgpu_waves_per_eu(CLIP ? 6 : 7))) raster_setup_kernel(WorldDev W, RasterLaunch L) {
   extern __shared__ __align__(16) unsigned char lds[];
   // At the end of a step this kernel shares CUs with the render's tile
   // waves; a higher issue priority keeps its chains of dependent steps moving.
