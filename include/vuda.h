@@ -317,8 +317,9 @@ int vuda_world_info(vuda_world* w, int32_t* n_envs, int64_t* n_bodies, int32_t* 
 /*
  * Launch-shape knobs (the autotuner's search space).  Keys:
  *   VUDA_TUNE_RASTER_THREADS   raster workgroup size, multiple of 64 (default 256;
- *                              until it is set, setup launches of few images
- *                              take 512: at most 512, or 256 co-scheduled)
+ *                              until it is set, setup launches of few images of
+ *                              many primitives take 512: at most 512 images, or
+ *                              256 co-scheduled)
  *   VUDA_TUNE_REC_CAP          tile-bin entries an image may use (0: its whole
  *                              capacity, 4 per primitive of its env); an image
  *                              needing more is rendered without bins, each

@@ -1055,14 +1055,20 @@ int vuda_world::raster_launch_of(const WorkList& L, int parity, int32_t* queue, 
   rl.lds_zone0 = rl.lrec_cap = rl.lbin_cap = 0;
   size_t lds = raster_lds_bytes(rl);
   const size_t kLdsMax = 160 * 1024;
-  // Where no size was asked for, a setup of at most two images per CU (one
-  // beside the other phases) takes 512 threads: the chip has room for the
-  // waves, and an image's chain of passes is shorter (250 images of 17 bodies
-  // at 64x64 13.3 us, 15.4 with 256; 512 of 64 bodies 24.5 and 28.5; 48 of
-  // 640x480 35.7 and 47.2; an iteration of 256 envs of 64 bodies beside
-  // physics 64.9 and 71.6).  With more images the waves crowd each other out
-  // (1,024 of 16 bodies 28.5 and 21.0; 500 beside physics 61.4 and 59.5).
-  if (setup && tune.raster_threads_default && mode != 1 && L.n <= (mode == 0 ? 512 : 256)) {
+  // Where no size was asked for, a setup of few images with enough primitives for
+  // the threads takes 512: the chip has room for the waves, and an image's chain of
+  // passes is shorter.  Serialized, up to two images for each of the 256 CUs; us
+  // with 256 threads and with 512: 256 images of 64x64 and 20 bodies (922
+  // primitives) 13.1 and 10.7, of 256x256 and 64 bodies 25.9 and 19.4; 512 of the
+  // same 14.5 and 13.7, 28.3 and 23.4.  With fewer primitives the barriers of idle
+  // waves cost more: 256 images of 370 10.5 and 10.1, 512 of 370 11.8 and 12.8, 256
+  // of 186 9.4 and 9.9.  With more images the waves crowd each other out (1,024 of
+  // 16 bodies 21.0 and 28.5).  Beside other phases up to an image for each CU, an
+  // iteration: 256 images of 256x256 and 64 bodies 58.8 and 55.9, of 20 bodies 47.6
+  // and 47.3, but of 64x64 and 20 bodies 36.9 and 38.4, so from 1,024 primitives on
+  // (500 images 59.5 and 61.4).
+  const int32_t least = mode != 0 ? 1024 : L.n <= 256 ? 256 : 512;
+  if (setup && tune.raster_threads_default && mode != 1 && L.n <= (mode == 0 ? 512 : 256) && L.max_tris > least) {
     rl.threads = 512;
     const size_t wide = raster_lds_bytes(rl);
     if (wide <= kLdsMax) lds = wide;
