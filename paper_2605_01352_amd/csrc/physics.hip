@@ -5,11 +5,12 @@
 // substeps, reading state buffer `parity` and writing the last step's buffer
 // once; the substeps run out of LDS and registers.  Per substep:
 //   1. publish p, v, omega and R(q) of every body to LDS;
-//   2. broadphase on a uniform grid hashed into 2^ceil(log2 2N) buckets
-//      (Teschner et al. 2003 XOR-prime hash).  A bucket is a bitset of
-//      bodies; each body ORs the buckets of its cell and the 13 cells of the
-//      half shell, tests the distance of every body found and records the
-//      pair (i < j) in a per-row bitset;
+//   2. broadphase: each lane finds its body's neighbours as a bitmask.  Up to 64
+//      bodies all pairs, the lanes taking slices of the bodies by broadcast
+//      loads; above, a uniform grid hashed into 2^ceil(log2 2N) buckets
+//      (Teschner et al. 2003 XOR-prime hash): a bucket is a bitset of bodies,
+//      and each body ORs the buckets of its cell and the 13 cells of the half
+//      shell and tests the distance of every body found;
 //   3. candidate rows are compacted into a pair list sorted by (i, j) with a
 //      workgroup prefix scan of the row popcounts;
 //   4. narrowphase: a pair with a sphere (one contact point at most) on one

@@ -456,11 +456,16 @@ hipError_t launch_policy(const WorldDev& w, const PolicyLaunch& l, hipStream_t s
   if (e != hipSuccess) return e;
   if (!l.layered) {
     const int threads = (l.H + 63) / 64 * 64;
-    // Two envs per workgroup where the weights' reads count more than the
-    // workgroups (layer 1 and head in us, one env and two: 1,024 at H = 256
-    // 74 and 67, 600 at 512 71 and 61, 256 at 1,024 88 and 81; 512 at 256 32.8
-    // and 33.3, 250 at 256 31.4 and 34.2, 1,000 at 100 28.0 and 30.4; four were
-    // slower everywhere).
+    // Two envs per workgroup, which halve the reads of the weights, from 2^18 hidden
+    // units over the batch on.  Layer 1 and head in us, one env and two (frames of
+    // 64x64 up to hidden 512, of 8x8 above): 1,024 at H = 256 40.7 and 36.8, 600 at
+    // 512 68.6 and 60.0, 410 at 640 48.9 and 38.0, 300 at 1,024 101 and 67, 4,096 at
+    // 64 15.8 and 15.3; from there on two were faster at every size measured.  Below
+    // it one is ahead while it gives each CU a workgroup or each SIMD two waves at
+    // most (256 at 256 31.5 and 35.0, 512 at 256 32.4 and 32.6, 256 at 512 41.0 and
+    // 42.0, 192 at 1,024 66.1 and 67.2), two once it gives them more (1,000 at 256
+    // 41.0 and 36.8, 800 at 256 46.6 and 43.1, 300 at 512 51.9 and 45.0): the line
+    // leaves those to one.  Four envs were slower everywhere.
     const int envs = (int64_t)l.M * l.H >= 1 << 18 ? 2 : 1;
     const dim3 g((l.M + envs - 1) / envs), b(threads);
     const uint32_t lds = (uint32_t)(2 * envs * ((l.H + 3) & ~3) * sizeof(float));

@@ -1492,8 +1492,8 @@ __device__ __forceinline__ void raster_tile(const WorldDev& W, const CamDev& cam
 }
 
 // A job, a run of tiles of a row, per workgroup of TW waves, which take its
-// tiles in turn.  Tiles of 16 pixels need 58
-// VGPRs, eight waves per SIMD, but keep to seven: the eighth slot is where the
+// tiles in turn.  Tiles of 16 pixels could run eight waves per SIMD, but keep to
+// seven (and take 69 VGPRs of the 72 that leaves): the eighth slot is where the
 // step's and the setup's workgroups start beside a full chip of tiles (an
 // iteration of 1,024 envs at 128x128, pipelined: 81.1 us with seven, 89.7 with
 // eight, 80.3 with six; 4,096 envs of 2x256x256, bound by the tiles: 2,136,

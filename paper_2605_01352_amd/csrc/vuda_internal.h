@@ -215,7 +215,7 @@ struct PhysLaunch {
   int32_t n_work;
   int32_t n_big;           // the listed envs of more than 64 bodies: the first ones
   int32_t max_bodies;      // over the listed envs
-  int32_t parity;          // buffer read; writes 1 - parity
+  int32_t parity;          // buffer read; writes (parity + nsteps) & 1
   int32_t nsteps;
   int32_t persistent;      // 0: one workgroup per env; >0: that many resident workgroups
   int32_t* queue;          // persistent work counter (one int), nullable otherwise
