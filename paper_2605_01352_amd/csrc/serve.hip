@@ -105,6 +105,7 @@ constexpr int32_t kTickIters = 8;
 // last step it holds, and the env-steps it serves.
 struct Tick {
   hipEvent_t ev[2] = {nullptr, nullptr};
+  uint64_t stream_gen = 0;  // of the streams the events are on
   int nev = 0;
   std::vector<int32_t> finishing;  // first env slot of each
   int64_t env_steps = 0;
@@ -245,6 +246,7 @@ int vuda_server::reap(bool block, int32_t* ncomp) {
   if (inflight.empty()) return 0;
   Tick& t = inflight.front();
   for (int k = 0; k < t.nev; ++k) {
+    if (t.stream_gen != w->stream_gen) break;  // its streams are gone, their work done
     const hipError_t q = block ? hipEventSynchronize(t.ev[k]) : hipEventQuery(t.ev[k]);
     if (q == hipErrorNotReady) return 0;
     if (q != hipSuccess) return hip_fail(q, "tick event");
@@ -369,6 +371,7 @@ extern "C" int vuda_serve_tick(vuda_server* s, int32_t* n_completed) {
       }
     }
     t.nev = s->w->mark(t.ev);
+    t.stream_gen = s->w->stream_gen;
     if (t.nev < 0) return VUDA_EHIP;
     s->inflight.push_back(std::move(t));
   } else {

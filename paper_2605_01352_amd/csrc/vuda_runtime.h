@@ -189,6 +189,7 @@ struct vuda_world {
   hipStream_t s_setup = nullptr;  // raster setup of the pipelined schedule (the step's CUs)
   int mode = 0;
   float cu_split = 0.0f;
+  uint64_t stream_gen = 0;  // changes with the streams; work on earlier ones has completed
 
   // dependency events per env: the last step, and the last render of each
   // buffer; render_state_ev: the last render of each buffer whose kernels
@@ -203,6 +204,11 @@ struct vuda_world {
   // after; tev_used[k] launches recorded since the last read
   std::vector<hipEvent_t> tev[vuda::kKernelKinds];
   size_t tev_used[vuda::kKernelKinds] = {0, 0, 0, 0, 0};
+  // launch times read from events since dropped (drop_events), not reported yet
+  struct {
+    int64_t n;
+    double sum, max;
+  } times[vuda::kKernelKinds] = {};
   // per env: the raster scratch of its current state buffer holds that
   // state's setup
   std::vector<uint8_t> setup_ok;
@@ -245,6 +251,8 @@ struct vuda_world {
   hipError_t copy_now(void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
   hipError_t fill_now(void* dst, int value, size_t bytes);
   int init_events();
+  int read_times(int kind);
+  int drop_events();
   int new_event(hipStream_t s, int64_t* id);
   int reserve_event(int64_t* id, hipEvent_t* ev);
   int wait_event(hipStream_t s, int64_t id);

@@ -687,6 +687,9 @@ static void cu_masks(int n_cu, float split, std::vector<uint32_t>& sim, std::vec
 int vuda_world::make_streams(float split) {
   HIPCHK(hipSetDevice(device));
   if (!s_serial) HIPCHK(hipStreamCreateWithFlags(&s_serial, hipStreamNonBlocking));
+  const int rc = drop_events();
+  if (rc) return rc;
+  ++stream_gen;
   destroy_streams();
   mode = 0;
   cu_split = 0.0f;
@@ -783,14 +786,54 @@ extern "C" int vuda_cosched(vuda_world* w, float cu_split) {
   if (rc) return rc;
   for (auto& g : w->graphs) (void)hipGraphExecDestroy(g.second);
   w->graphs.clear();
-  rc = w->make_streams(cu_split == 1.0f ? 0.0f : cu_split);
-  // every earlier event has completed (drained): forget them
-  std::fill(w->step_ev.begin(), w->step_ev.end(), -1);
-  for (int q = 0; q < 2; ++q) {
-    std::fill(w->render_ev[q].begin(), w->render_ev[q].end(), -1);
-    std::fill(w->render_state_ev[q].begin(), w->render_state_ev[q].end(), -1);
+  return w->make_streams(cu_split == 1.0f ? 0.0f : cu_split);
+}
+
+// Add the durations of the timed launches of a kernel to `times`, and have
+// their events free for the next ones.
+int vuda_world::read_times(int kind) {
+  const size_t n = tev_used[kind];
+  if (n == 0) return VUDA_OK;
+  HIPCHK(hipEventSynchronize(tev[kind][2 * n - 1]));
+  for (size_t i = 0; i < n; ++i) {
+    float ms = 0.0f;
+    HIPCHK(hipEventElapsedTime(&ms, tev[kind][2 * i], tev[kind][2 * i + 1]));
+    times[kind].n += 1;
+    times[kind].sum += ms;
+    times[kind].max = std::max(times[kind].max, (double)ms);
   }
-  return rc;
+  tev_used[kind] = 0;
+  return VUDA_OK;
+}
+
+// No event outlives the stream it was last recorded on: the runtime looks at
+// that stream again when the event is waited for, and answered
+// hipErrorCapturedEvent for events of streams since destroyed.  Before the
+// streams go (the world is idle) every event goes, the timed launches read.
+int vuda_world::drop_events() {
+  for (int k = 0; k < kKernelKinds; ++k) {
+    const int rc = read_times(k);
+    if (rc) return rc;
+    for (auto& e : tev[k]) (void)hipEventDestroy(e);
+    tev[k].clear();
+  }
+  for (auto& e : evpool) (void)hipEventDestroy(e);
+  evpool.clear();
+  next_event = 0;
+  std::fill(step_ev.begin(), step_ev.end(), -1);
+  for (int q = 0; q < 2; ++q) {
+    std::fill(render_ev[q].begin(), render_ev[q].end(), -1);
+    std::fill(render_state_ev[q].begin(), render_state_ev[q].end(), -1);
+  }
+  for (auto& kv : lists)
+    for (ListBuf& b : kv.second.buf) {
+      for (hipEvent_t& e : b.fence) {
+        if (e) (void)hipEventDestroy(e);
+        e = nullptr;
+      }
+      b.nfence = 0;
+    }
+  return VUDA_OK;
 }
 
 // Event pool: ids grow monotonically; slot id % size is reused after making
@@ -2362,22 +2405,13 @@ extern "C" int vuda_kernel_times(vuda_world* w, int32_t kernel, int64_t* launche
   if (!w) return fail(VUDA_EINVAL, "null world");
   if (kernel < VUDA_KERNEL_PHYSICS || kernel > VUDA_KERNEL_RASTER_FUSED) return fail(VUDA_EINVAL, "kernel %d", kernel);
   const int k = kernel - VUDA_KERNEL_PHYSICS;
-  const size_t n = w->tev_used[k];
-  double sum = 0.0, mx = 0.0;
-  if (n) {
-    HIPCHK(hipSetDevice(w->device));
-    HIPCHK(hipEventSynchronize(w->tev[k][2 * n - 1]));
-    for (size_t i = 0; i < n; ++i) {
-      float ms = 0.0f;
-      HIPCHK(hipEventElapsedTime(&ms, w->tev[k][2 * i], w->tev[k][2 * i + 1]));
-      sum += ms;
-      mx = ms > mx ? ms : mx;
-    }
-  }
-  w->tev_used[k] = 0;
-  if (launches) *launches = (int64_t)n;
-  if (total_ms) *total_ms = sum;
-  if (max_ms) *max_ms = mx;
+  HIPCHK(hipSetDevice(w->device));
+  const int rc = w->read_times(k);
+  if (rc) return rc;
+  if (launches) *launches = w->times[k].n;
+  if (total_ms) *total_ms = w->times[k].sum;
+  if (max_ms) *max_ms = w->times[k].max;
+  w->times[k] = {};
   return VUDA_OK;
 }
 
